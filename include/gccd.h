@@ -181,8 +181,9 @@ int gccd_stats(gccd_ctx* c, gccd_stats_t* out);
  * thread, and per event a chunk count near the one that gives about 64
  * workgroups per compute unit, picked so that the event's tiles split into
  * chunks as nearly equal as possible.  With one target per thread in the
- * default precision, source tiles farther than the targets' box half-diagonal
- * are summed in the expanded-square form (see gccd_set_precision).  The
+ * default precision, pairs farther than a fifth of the targets' box
+ * half-diagonal are summed in the expanded-square form (see
+ * gccd_set_precision).  The
  * split changes the FP32 summation order; the targets per thread change the
  * workgroups' origins and so the rounding of the pair differences.  Applies
  * to the current load and later ones; synchronises the stream.
@@ -225,19 +226,17 @@ int gccd_autotune(gccd_ctx* c, int32_t* targets_per_thread, int32_t* source_chun
  * differences, r^2, r^-3 (hardware reciprocal square root, cubed) and the
  * per-tile sums in FP32; they differ in the origin the coordinates are
  * rounded relative to and in how the difference of a pair is formed.
- *   DEFAULT   origin at the centre of each workgroup's targets; pairs closer
- *             than a quarter of the target's distance from that origin
- *             (at most a quarter of the targets' half-diagonal rho)
- *             recomputed from the residuals of the coordinates (the fast,
- *             bounded mode).  With one target per thread, source tiles whose box is
- *             farther than rho from the targets' box take r^2 + eps^2 as
- *             (|s|^2 + eps^2) + |t|^2 - 2 t.s and the sum as t sum w - sum s w
- *             (one VALU operation fewer per pair; at most about 5e-6
- *             relative error per term there); and in a load whose work
- *             items fit in one round of workgroups (a small cloud), tiles
- *             within rho/4 take the compensated difference in every pair
- *             instead of the per-pair check
- *   BLOCK     the same origins, no close-pair recomputation
+ *   DEFAULT   origin at the centre of each workgroup's targets.  With one
+ *             target per thread, blocks of 16 targets and 16 sources whose
+ *             boxes are farther apart than rho/5 (rho: the targets'
+ *             half-diagonal) take r^2 + eps^2 as (|s|^2 + eps^2) + |t|^2 -
+ *             2 t.s on the matrix cores (FP32 factors as three bf16 parts,
+ *             FP32 sums) and the sum as t sum w - sum s w; all other pairs
+ *             take the difference of coordinates and residuals.  With 2 or 4
+ *             targets per thread, differences of the coordinates, those of
+ *             pairs closer than a quarter of the target's distance from the
+ *             origin recomputed with the residuals
+ *   BLOCK     the same origins, differences of the coordinates alone
  *   EVENT     one origin per event (the centre of its sources' bounding
  *             box), no recomputation
  *   ABSOLUTE  no origin: FP32 absolute coordinates, as the paper stores them

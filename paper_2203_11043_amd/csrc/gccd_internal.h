@@ -56,7 +56,7 @@ struct FieldArgs {
     const uint32_t* ev_active;  // [E] travelling holes of each event (first in its segment)
     const uint32_t* ev_tile;    // [E+1] first source tile of each event
     uint32_t one_event_n;       // > 0: a single event of this many carriers (slot 0,
-                                // tile 0), whose offsets the expanded kernel need not read
+                                // tile 0), whose offsets the matrix kernel need not read
     int32_t targets_all;        // 1: every carrier of the event is a target
     int32_t sources_all;        // 1: every carrier is a source, else the travelling ones
     const double* px;           // positions in list-slot order (gathered)
@@ -71,8 +71,6 @@ struct FieldArgs {
     uint32_t pstride;
     const uint32_t* n_items;    // persistent launch: the item count, in device memory
     uint32_t* queue;            // persistent launch: [0] next item (zero before the launch)
-    int32_t near_compensated;   // one target per thread, default precision: tiles within
-                                // rho/4 take the compensated difference (small launches)
     int32_t count_items;        // 1: the launch is sized to the item capacity and a
                                 // workgroup past *n_items leaves at once (graph schedule)
     int32_t unit;               // sources per staged tile of the one-target-per-thread

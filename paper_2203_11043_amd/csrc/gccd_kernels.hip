@@ -1,6 +1,7 @@
 // HIP kernels (gfx950 / CDNA4) of the charge-transport hot path of
 // Avalos & Sofo Haro, arXiv 2203.11043:
-//   field_tiles   -- Eq. (6), softened all-pairs Coulomb field (the O(N^2) part)
+//   field_tiles_matrix, field_tiles -- Eq. (6), softened all-pairs Coulomb field
+//                    (the O(N^2) part)
 //   step_update   -- Eqs. (1)-(4) and the z check of Sec. III.B, fused per carrier
 //   load_prepare  -- load-time boundary handling
 //   make_keys, count_active, gather_tiles -- the spatially sorted carrier list
@@ -110,6 +111,41 @@ __device__ __forceinline__ float uniform(float v) {
     return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(v)));
 }
 
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+
+// Brackets a run of transcendental instructions (see diff_group).
+__device__ __forceinline__ void transcendental_begin() {
+    __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_s_setprio(3);
+}
+__device__ __forceinline__ void transcendental_end() {
+    __builtin_amdgcn_s_setprio(0);
+    __builtin_amdgcn_sched_barrier(0);
+}
+
+// f as three bf16 values h, m, l, each the rest rounded to nearest: 8 + 8 + 8
+// bits hold the 24 of an FP32 value exactly.  Pairs as a matrix operand takes
+// them (first in the low half).
+struct Bf16x3 {
+    uint32_t hh, hm, ml;
+};
+__device__ __forceinline__ uint32_t pack_bf16(float a, float b) {
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2{a, b}), bf16x2));
+}
+__device__ __forceinline__ Bf16x3 split_bf16(float f) {
+    Bf16x3 p;
+    p.hh = pack_bf16(f, f);
+    const float r = f - __uint_as_float(p.hh & 0xFFFF0000u);
+    p.hm = pack_bf16(f, r);
+    p.ml = pack_bf16(r, r - __uint_as_float(p.hm & 0xFFFF0000u));
+    return p;
+}
+
 __device__ __forceinline__ double wave_min(double v) {
 #pragma unroll
     for (int m = 32; m >= 1; m >>= 1) v = fmin(v, __shfl_xor(v, m));
@@ -148,6 +184,31 @@ __device__ __forceinline__ bool exact_push(ExactList& L, uint32_t tgt, uint32_t 
     return true;
 }
 
+// The term of source slot s at target slot t, in FP64, to the close sums.
+__device__ __forceinline__ void exact_add(const FieldArgs& a, uint32_t t, uint32_t s) {
+    const double dx = a.px[t] - a.px[s], dy = a.py[t] - a.py[s], dz = a.pz[t] - a.pz[s];
+    double q = fma(dx, dx, a.eps2d);
+    q = fma(dy, dy, q);
+    q = fma(dz, dz, q);
+    const double w = a.acc_scale / (q * sqrt(q));
+    unsigned long long* c = a.close + t;
+    atomicAdd(c, (unsigned long long)__double2ll_rn(dx * w));
+    atomicAdd(c + a.pstride, (unsigned long long)__double2ll_rn(dy * w));
+    atomicAdd(c + 2 * (size_t)a.pstride, (unsigned long long)__double2ll_rn(dz * w));
+}
+
+// The matrix kernel keeps one list per wave, filled without atomics: the
+// wave counts its entries in a scalar register and each lane finds its place
+// from the ballot.  (In the dense core of a cloud two of five turns of the
+// near loop record a pair, and the atomic's round trip through LDS stalled
+// the wave each time.)
+constexpr int kWaveCap = 512;
+
+struct WaveList {
+    uint32_t src[kWaveCap];
+    uint8_t tgt[kWaveCap];  // target's index in the item's block
+};
+
 // Called by every lane of the workgroup after the item's last barrier;
 // targets of the item are slots off + tbase + tgt, sources slots off + src.
 // Leaves the list empty for the next item (whose first barrier orders the
@@ -156,18 +217,8 @@ __device__ __forceinline__ void exact_flush(const FieldArgs& a, ExactList& L, ui
                                             uint32_t tbase) {
     const uint32_t cnt = min(L.n, (uint32_t)kExactCap);
     if (cnt == 0) return;  // uniform: every lane reads L.n after the same barrier
-    for (uint32_t i = threadIdx.x; i < cnt; i += blockDim.x) {
-        const uint32_t t = off + tbase + L.tgt[i], s = off + L.src[i];
-        const double dx = a.px[t] - a.px[s], dy = a.py[t] - a.py[s], dz = a.pz[t] - a.pz[s];
-        double q = fma(dx, dx, a.eps2d);
-        q = fma(dy, dy, q);
-        q = fma(dz, dz, q);
-        const double w = a.acc_scale / (q * sqrt(q));
-        unsigned long long* c = a.close + t;
-        atomicAdd(c, (unsigned long long)__double2ll_rn(dx * w));
-        atomicAdd(c + a.pstride, (unsigned long long)__double2ll_rn(dy * w));
-        atomicAdd(c + 2 * (size_t)a.pstride, (unsigned long long)__double2ll_rn(dz * w));
-    }
+    for (uint32_t i = threadIdx.x; i < cnt; i += blockDim.x)
+        exact_add(a, off + tbase + L.tgt[i], off + L.src[i]);
     __syncthreads();
     if (threadIdx.x == 0) L.n = 0;
 }
@@ -209,8 +260,7 @@ __device__ __forceinline__ void exact_flush(const FieldArgs& a, ExactList& L, ui
 // FP32 additions that follow it would carry about 10u of that into the
 // target's field.  They are summed exactly instead (exact_push): the close-pair
 // radius is at least that distance, so these pairs always take the checked
-// path, and tiles that can hold them are never summed in the unchecked or the
-// expanded form.
+// path, and tiles that can hold them are never summed unchecked.
 //
 // The other GCCD_PRECISION_* modes change the origin (one per event, or
 // none: absolute coordinates) or the difference formation (hi parts only,
@@ -585,217 +635,153 @@ __global__ __launch_bounds__(kFieldThreads) void field_tiles(FieldArgs a) {
     }
 }
 
-// Default precision, one target per lane: the far tiles in the expanded form.
-//
-// For a source tile whose bounding box lies more than rho from the box of
-// the wave's targets (rho: the half-diagonal of the workgroup's targets, whose
-// centre is the origin), every pair has |d| > rho, and the pair sum is taken
-// from
-//     |d|^2 + eps^2 = (|s|^2 + eps^2) + |t|^2 - 2 t.s,
-//     sum d w = t sum w - sum s w,          w = (|d|^2 + eps^2)^{-3/2},
-// with s and t the hi parts relative to the workgroup origin.  The staged
-// tile holds -2 s and S = |s|^2 + eps^2 (rounded once from FP64), so a pair
-// costs an add, three FMAs for r^2, the reciprocal square root cubed and
-// four accumulations -- 11 VALU against 12 for the difference form.  The
-// expansion loses accuracy to cancellation: the partial results of r^2 are
-// bounded by (|s| + |t|)^2 <= (2 rho + |d|)^2 <= 9 |d|^2, so r^2 carries at
-// most 45u relative error and the term about 68u, plus the 8u of the dropped
-// lo parts (as for the difference form at |d| > rho): below 5e-6 in all.
-// The final t sum w - sum s w cancels by at most (|t| + |s|)/|d| <= 3, which
-// scales the FP32 summation error of those tiles by that factor.  It is
-// formed in FP64 from the FP32 sums.
-//
-// Tiles within rho of the wave's box take the difference form exactly as
-// field_tiles<1, DEFAULT> does (the sources' hi parts recovered from -2 s by
-// an exact halving inside the FMA), with the same close-pair rule (tiles
-// within rho/4 of the wave's box checked pair by pair against a quarter of
-// each target's distance from the origin; a tile farther than that holds no
-// close pair of the wave, so the unchecked sum is the same), so in a launch
-// that fills the GPU
-// the close pairs -- and whole small events, which have no far tiles -- are
-// summed bit for bit as by that kernel.  Small loads differ on purpose: see
-// COMP below.
-// CHECK: pairs closer than the lane's radius (rc2, at least acc2 for a target,
-// 0 for a padding lane) are recomputed with the lo parts, and those below acc2
-// (source slot src of the event) are recorded for exact summation.
-template <bool CHECK>
-__device__ __forceinline__ void diff_pair(const FieldArgs& a, ExactList& xl, uint32_t src,
-                                          const float* __restrict__ lxp,
-                                          const float* __restrict__ lyp,
-                                          const float* __restrict__ lzp, uint32_t k, float m2x,
-                                          float m2y, float m2z, float thx, float thy, float thz,
-                                          float tlx, float tly, float tlz, float eps2, float rc2,
-                                          float& bx, float& by, float& bz) {
-    // thx + 0.5 (-2 s_x) rounds once, to the same value as thx - s_x
-    float dx = __builtin_fmaf(m2x, 0.5f, thx);
-    float dy = __builtin_fmaf(m2y, 0.5f, thy);
-    float dz = __builtin_fmaf(m2z, 0.5f, thz);
-    float r2 = __builtin_fmaf(dx, dx, eps2);
-    r2 = __builtin_fmaf(dy, dy, r2);
-    r2 = __builtin_fmaf(dz, dz, r2);
-    if (CHECK && __builtin_expect(__ballot(r2 < rc2) != 0ull, 0)) {
-        const float nlx = lxp[k], nly = lyp[k], nlz = lzp[k];
-        if (r2 < rc2) {
-            dx += tlx - nlx;
-            dy += tly - nly;
-            dz += tlz - nlz;
-            r2 = __builtin_fmaf(dx, dx, eps2);
-            r2 = __builtin_fmaf(dy, dy, r2);
-            r2 = __builtin_fmaf(dz, dz, r2);
+// One source quadruple of a near block in the compensated difference form:
+// sources k .. k + 3 of the staged tile (sources src .. src + 3 of the event)
+// at the lane's target, number tgt of the block.  The four reciprocal square
+// roots stand together at raised wave priority: a compute unit issues the
+// full-rate FP32 instructions of two waves at once only while neither has a
+// transcendental next, so single ones spread through the stream cost every wave
+// that pairing (measured, far pairs: 40.3 cycles per wave and source spread,
+// 37.5 grouped by four at raised priority).  One compare with the smallest of
+// the four r^2 rules out pairs below acc2 (a compare issues at half rate),
+// which are recorded for exact summation.  e2 is the softening and rx the
+// exact-sum limit (0 for a lane without a target) in vector registers (an
+// instruction with a scalar operand does not pair either).
+__device__ __forceinline__ void comp_quad(WaveList& xl, uint32_t& nx, uint32_t tgt, uint32_t src,
+                                          const float (&hl)[6][kTile], uint32_t k, float thx,
+                                          float thy, float thz, float tlx, float tly, float tlz,
+                                          float e2, float rx, float& bx, float& by, float& bz) {
+    const f32x4 x4 = *reinterpret_cast<const f32x4*>(&hl[0][k]);
+    const f32x4 y4 = *reinterpret_cast<const f32x4*>(&hl[1][k]);
+    const f32x4 z4 = *reinterpret_cast<const f32x4*>(&hl[2][k]);
+    const f32x4 a4 = *reinterpret_cast<const f32x4*>(&hl[3][k]);
+    const f32x4 b4 = *reinterpret_cast<const f32x4*>(&hl[4][k]);
+    const f32x4 c4 = *reinterpret_cast<const f32x4*>(&hl[5][k]);
+    float dx[4], dy[4], dz[4], r2[4], inv[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+        // thx + 0.5 (-2 s_x) rounds once, to the same value as thx - s_x
+        dx[u] = __builtin_fmaf(x4[u], 0.5f, thx) + (tlx - a4[u]);
+        dy[u] = __builtin_fmaf(y4[u], 0.5f, thy) + (tly - b4[u]);
+        dz[u] = __builtin_fmaf(z4[u], 0.5f, thz) + (tlz - c4[u]);
+        r2[u] = __builtin_fmaf(dx[u], dx[u], e2);
+        r2[u] = __builtin_fmaf(dy[u], dy[u], r2[u]);
+        r2[u] = __builtin_fmaf(dz[u], dz[u], r2[u]);
+    }
+    const float m = fminf(fminf(r2[0], r2[1]), fminf(r2[2], r2[3]));
+    if (__builtin_expect(__ballot(m < rx) != 0ull, 0)) {
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const bool rec = r2[u] < rx && r2[u] > e2;
+            const uint64_t who = __ballot(rec);
+            if (who) {
+                const uint32_t i =
+                    nx + __builtin_amdgcn_mbcnt_hi((uint32_t)(who >> 32),
+                                                   __builtin_amdgcn_mbcnt_lo((uint32_t)who, 0u));
+                if (rec && i < (uint32_t)kWaveCap) {
+                    xl.src[i] = src + (uint32_t)u;
+                    xl.tgt[i] = (uint8_t)tgt;
+                    dx[u] = dy[u] = dz[u] = 0.0f;
+                }
+                nx = min(nx + (uint32_t)__popcll(who), (uint32_t)kWaveCap);
+            }
         }
-        if (r2 < fminf(a.acc2, rc2) && r2 > eps2 && exact_push(xl, threadIdx.x, src))
-            dx = dy = dz = 0.0f;
     }
-    const float inv = __builtin_amdgcn_rsqf(r2);
-    const float w = inv * inv * inv;
-    bx = __builtin_fmaf(dx, w, bx);
-    by = __builtin_fmaf(dy, w, by);
-    bz = __builtin_fmaf(dz, w, bz);
-}
-
-// Difference form with the lo parts in every pair (the compensated
-// difference of the COMPENSATED mode); pairs below acc2 are recorded for
-// exact summation.
-__device__ __forceinline__ void comp_pair(const FieldArgs& a, ExactList& xl, uint32_t src,
-                                          float m2x, float m2y,
-                                          float m2z, float lx, float ly, float lz, float thx,
-                                          float thy, float thz, float tlx, float tly, float tlz,
-                                          float eps2, float rc2, float& bx, float& by,
-                                          float& bz) {
-    float dx = __builtin_fmaf(m2x, 0.5f, thx) + (tlx - lx);
-    float dy = __builtin_fmaf(m2y, 0.5f, thy) + (tly - ly);
-    float dz = __builtin_fmaf(m2z, 0.5f, thz) + (tlz - lz);
-    float r2 = __builtin_fmaf(dx, dx, eps2);
-    r2 = __builtin_fmaf(dy, dy, r2);
-    r2 = __builtin_fmaf(dz, dz, r2);
-    if (__builtin_expect(__ballot(r2 < fminf(a.acc2, rc2)) != 0ull, 0)) {
-        if (r2 < fminf(a.acc2, rc2) && r2 > eps2 && exact_push(xl, threadIdx.x, src))
-            dx = dy = dz = 0.0f;
+    transcendental_begin();
+#pragma unroll
+    for (int u = 0; u < 4; ++u) inv[u] = __builtin_amdgcn_rsqf(r2[u]);
+    transcendental_end();
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+        const float w = inv[u] * inv[u] * inv[u];
+        bx = __builtin_fmaf(dx[u], w, bx);
+        by = __builtin_fmaf(dy[u], w, by);
+        bz = __builtin_fmaf(dz[u], w, bz);
     }
-    const float inv = __builtin_amdgcn_rsqf(r2);
-    const float w = inv * inv * inv;
-    bx = __builtin_fmaf(dx, w, bx);
-    by = __builtin_fmaf(dy, w, by);
-    bz = __builtin_fmaf(dz, w, bz);
 }
 
-__device__ __forceinline__ void comp_tile(const FieldArgs& a, ExactList& xl, uint32_t src0,
-                                          const float* __restrict__ mxp, const float* __restrict__ myp,
-                                          const float* __restrict__ mzp, const float* __restrict__ lxp,
-                                          const float* __restrict__ lyp, const float* __restrict__ lzp,
-                                          uint32_t cnt, float thx, float thy, float thz, float tlx,
-                                          float tly, float tlz, float eps2, float rc2, float& bx,
-                                          float& by, float& bz) {
-    uint32_t k = 0;
-    for (; k + 4 <= cnt; k += 4) {
-        const float4 x4 = *reinterpret_cast<const float4*>(mxp + k);
-        const float4 y4 = *reinterpret_cast<const float4*>(myp + k);
-        const float4 z4 = *reinterpret_cast<const float4*>(mzp + k);
-        const float4 a4 = *reinterpret_cast<const float4*>(lxp + k);
-        const float4 b4 = *reinterpret_cast<const float4*>(lyp + k);
-        const float4 c4 = *reinterpret_cast<const float4*>(lzp + k);
-        comp_pair(a, xl, src0 + k + 0, x4.x, y4.x, z4.x, a4.x, b4.x, c4.x, thx, thy, thz, tlx, tly, tlz, eps2,
-                  rc2, bx, by, bz);
-        comp_pair(a, xl, src0 + k + 1, x4.y, y4.y, z4.y, a4.y, b4.y, c4.y, thx, thy, thz, tlx, tly, tlz, eps2,
-                  rc2, bx, by, bz);
-        comp_pair(a, xl, src0 + k + 2, x4.z, y4.z, z4.z, a4.z, b4.z, c4.z, thx, thy, thz, tlx, tly, tlz, eps2,
-                  rc2, bx, by, bz);
-        comp_pair(a, xl, src0 + k + 3, x4.w, y4.w, z4.w, a4.w, b4.w, c4.w, thx, thy, thz, tlx, tly, tlz, eps2,
-                  rc2, bx, by, bz);
-    }
-    for (; k < cnt; ++k)
-        comp_pair(a, xl, src0 + k, mxp[k], myp[k], mzp[k], lxp[k], lyp[k], lzp[k], thx, thy, thz,
-                  tlx, tly, tlz, eps2, rc2, bx, by, bz);
-}
+// Default precision, one target per lane.  The wave's 64 targets are four groups
+// of 16 (as the matrix cores take them), a source tile up to 16 groups of 16,
+// and each of the 64 pairs of groups is summed in one of two forms, chosen by
+// the gap between the groups' bounding boxes:
+//
+// Far (gap above kFarFraction rho, rho the half-diagonal of the workgroup's
+// targets, whose centre is the origin):
+//     r^2 = (|s|^2 + eps^2) + |t|^2 - 2 t.s    on the matrix cores,
+//     sum d w = t sum w - sum s w,             w = (r^2)^{-3/2},
+// with s and t the hi parts.  One v_mfma_f32_16x16x32_bf16 gives r^2 of a
+// block, which leaves 6 VALU instructions and the reciprocal square root per
+// pair.  Every FP32 factor is held as three bf16 parts (exactly its 24 bits);
+// the products of parts are exact and accumulated in FP32, and those of order
+// 2^-27 (second with third part and below) are left out, so r^2 carries fewer
+// roundings than a chain of FP32 operations (a 256-source tile against 64-bit
+// sums: largest error 2.7e-7 against 7.6e-7, rms 7.6e-8 against 2.4e-7).  The
+// partial results of r^2 are at most (|s| + |t|)^2 <= ((2 + f)/f)^2 |d|^2 = 121
+// |d|^2 at f = kFarFraction = 1/5, reached only by pairs at the very edge of the
+// far region.  t sum w - sum s w is formed per tile, before its terms meet
+// those of other tiles.
+//
+// Near (all others): the compensated difference (hi and lo parts) in every
+// pair, and the exact sum for pairs within kExactRadius eps.  No pair needs a
+// test against a close-pair radius, so the loop has no branch that a dense cloud
+// takes.
+//
+// Share of near pairs: 0.01 of a 1e5-hole cloud, 0.04 of 2e4, 0.08 of 1e4, 0.6 of
+// 1000.  Error against the FP64 mode (2-norm of the field): 3.1e-8 at 1e5 holes,
+// 3.8e-8 at 2e4, 5.0e-8 on a 400-cloud batch; a VALU kernel that took r^2 as four
+// FP32 operations per pair in tiles beyond rho and checked differences within
+// measured 7.2e-8, 9.7e-8 and 1.1e-7.
+//
+// What bounds it: VALU issue.  The far loop runs at 24.7 cycles per wave and
+// source (2.4 GHz; its launch run twice over the same groups, minus once), of
+// which the reciprocal square root takes 8.1 and six full-rate instructions
+// 14.4; the matrix instructions run beside the transcendentals.  The VALU form
+// of the same pair took 40.  Per launch, that kernel against this one: 1000 holes 16.1
+// and 12.2 us, 1e4 60 and 46 us, 1e5 2.53 and 1.89 ms, 3e5 21.9 and 16.4 ms, the
+// 62354-hole track 1.17 and 0.87 ms, 400 clouds of 200-20000 holes 5.2 and 4.5
+// ms.  The rest of a launch is staging, classification and the barrier of each
+// tile.
+//
+// The 32 products of the contraction: eight for each of the lanes' four
+// quarters q (A: source lane % 16, B: target lane % 16):
+//   q = 0, 1, 2:  -2 s_q as (h, m, m, l, h, h)  with  t_q as (h, h, m, h, m, l)
+//   q = 3:        |s|^2 + eps^2 the same way    with  (1, 1, 0, 1, 0, 0)
+// and 1, 1 with |t|^2's parts (h, m in q = 0, l in q = 1).  A lane's A operand
+// takes eight bytes of LDS; D holds sources 4 q .. 4 q + 3 of target lane % 16,
+// so a lane sums four sources of each of four targets, and the quarters' sums are
+// added after each tile (blocked summation).
+//
+// Four waves per SIMD: 128 registers hold four groups' operands, r^2 and sums.
+// Two groups at a time in 96 registers (five waves) spill and measured 8 %
+// slower at 3e5 holes.
+constexpr double kFarFraction = 0.2;
+// A padding source: its r^-3 underflows to 0 in either form.
+constexpr float kPadS = 3.0e38f;  // |s|^2
+constexpr float kPadX = 2.0e19f;  // -2 s_x of the difference form
 
-template <bool CHECK>
-__device__ __forceinline__ void diff_tile(const FieldArgs& a, ExactList& xl, uint32_t src0,
-                                          const float* __restrict__ mxp,
-                                          const float* __restrict__ myp,
-                                          const float* __restrict__ mzp,
-                                          const float* __restrict__ lxp,
-                                          const float* __restrict__ lyp,
-                                          const float* __restrict__ lzp, uint32_t cnt, float thx,
-                                          float thy, float thz, float tlx, float tly, float tlz,
-                                          float eps2, float rc2, float& bx, float& by,
-                                          float& bz) {
-    uint32_t k = 0;
-    for (; k + 4 <= cnt; k += 4) {
-        const float4 x4 = *reinterpret_cast<const float4*>(mxp + k);
-        const float4 y4 = *reinterpret_cast<const float4*>(myp + k);
-        const float4 z4 = *reinterpret_cast<const float4*>(mzp + k);
-        diff_pair<CHECK>(a, xl, src0 + k + 0, lxp, lyp, lzp, k + 0, x4.x, y4.x, z4.x, thx, thy, thz, tlx, tly, tlz,
-                         eps2, rc2, bx, by, bz);
-        diff_pair<CHECK>(a, xl, src0 + k + 1, lxp, lyp, lzp, k + 1, x4.y, y4.y, z4.y, thx, thy, thz, tlx, tly, tlz,
-                         eps2, rc2, bx, by, bz);
-        diff_pair<CHECK>(a, xl, src0 + k + 2, lxp, lyp, lzp, k + 2, x4.z, y4.z, z4.z, thx, thy, thz, tlx, tly, tlz,
-                         eps2, rc2, bx, by, bz);
-        diff_pair<CHECK>(a, xl, src0 + k + 3, lxp, lyp, lzp, k + 3, x4.w, y4.w, z4.w, thx, thy, thz, tlx, tly, tlz,
-                         eps2, rc2, bx, by, bz);
-    }
-    for (; k < cnt; ++k)
-        diff_pair<CHECK>(a, xl, src0 + k, lxp, lyp, lzp, k, mxp[k], myp[k], mzp[k], thx, thy, thz, tlx, tly, tlz,
-                         eps2, rc2, bx, by, bz);
-}
-
-__device__ __forceinline__ void expanded_pair(float m2x, float m2y, float m2z, float S, float T,
-                                              float thx, float thy, float thz, float& sw,
-                                              float& sx, float& sy, float& sz) {
-    float r2 = S + T;
-    r2 = __builtin_fmaf(thz, m2z, r2);
-    r2 = __builtin_fmaf(thy, m2y, r2);
-    r2 = __builtin_fmaf(thx, m2x, r2);
-    const float inv = __builtin_amdgcn_rsqf(r2);
-    const float w = inv * inv * inv;
-    sw += w;
-    sx = __builtin_fmaf(m2x, w, sx);
-    sy = __builtin_fmaf(m2y, w, sy);
-    sz = __builtin_fmaf(m2z, w, sz);
-}
-
-// One work item.  Every lane of the workgroup calls it with the same item;
-// it returns early only for an item without targets, before any barrier, and
-// otherwise ends after a barrier, so the LDS can take the next item at once.
-struct ExpandedLds {
-    float sh[2][7][kTile];  // staged: -2 s_x, -2 s_y, -2 s_z, |s|^2 + eps^2, lo_x, lo_y, lo_z
-    double box[6][kFieldThreads / 64];
-    double tbox[2][6];      // bounding box of the staged source tile
-    ExactList xl;           // close pairs of the item
+struct MatrixLds {
+    struct Tile {
+        float hl[6][kTile];           // -2 s_x, -2 s_y, -2 s_z, lo_x, lo_y, lo_z
+        u32x2 pk[kTile / 16][4][16];  // bf16 parts (h, m), (m, l): [group][quarter][source]
+        float gbox[6][16];            // boxes of the 16-source groups, relative to the origin
+    } tile[2];
+    double box[6][kFieldThreads / 16];
+    WaveList xl[kFieldThreads / 64];  // close pairs of the item
 };
 
-// COMP: tiles closer than rho/4 to the targets take the compensated
-// difference in every pair instead of the per-pair check and its branch.
-// In a launch of at most one round of workgroups (a small cloud) nearly
-// every wave finds a close pair in such tiles, the branch is taken almost
-// always, and the branch-free form halves the launch; in a full GPU the
-// check is cheaper per pair.
-// The box bound k (0-2 low x, y, z; 3-5 high) of source tile t of UNIT
-// sources of the event whose 256-source tiles start at tile0: a 256-source
-// tile's own box, a 64-source quarter's, or the union of two quarters'.
-template <int UNIT>
-__device__ __forceinline__ double unit_bound(const FieldArgs& a, uint32_t tile0, uint32_t t,
-                                             int k) {
-    const size_t st = a.tile_stride;
-    if (UNIT == kTile) return a.tile_box[(size_t)k * st + tile0 + t];
-    if (UNIT == kTile / 4)
-        return a.tile_box[(size_t)(6 + 4 * k + (int)(t & 3u)) * st + tile0 + (t >> 2)];
-    const int q = 2 * (int)(t & 1u);
-    const double v0 = a.tile_box[(size_t)(6 + 4 * k + q) * st + tile0 + (t >> 1)];
-    const double v1 = a.tile_box[(size_t)(6 + 4 * k + q + 1) * st + tile0 + (t >> 1)];
-    return k < 3 ? fmin(v0, v1) : fmax(v0, v1);
+// The sum of v over the lanes of one column (lane % 16), in each of them.
+__device__ __forceinline__ float add_quarters(float v) {
+    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false,
+                                                    false);
+    const float h = __uint_as_float(r[0]) + __uint_as_float(r[1]);
+    const auto s = __builtin_amdgcn_permlane16_swap(__float_as_uint(h), __float_as_uint(h), false,
+                                                    false);
+    return __uint_as_float(s[0]) + __uint_as_float(s[1]);
 }
 
-// UNIT: sources per staged tile (256, 128 or 64; the work item's first,
-// step and end count such tiles).  Smaller tiles give a small cloud more
-// work items of fewer sources each; the LDS layout is the same.
-template <bool COMP, int UNIT>
-__device__ __forceinline__ void expanded_item(const FieldArgs& a, const FieldItem it,
-                                              ExpandedLds& L, uint32_t na0) {
-    auto& sh = L.sh;
-    auto& box = L.box;
-    auto& tbox = L.tbox;
-    // a single event (na0: its travelling holes, read with the item) needs
-    // no lookups before the targets' loads
+template <int UNIT>
+__device__ __forceinline__ void matrix_item(const FieldArgs& a, const FieldItem it, MatrixLds& L,
+                                            uint32_t na0) {
     const bool one = a.one_event_n != 0u;
     const uint32_t off = one ? 0u : a.ev_off[it.event];
     const uint32_t ne = one ? a.one_event_n : a.ev_off[it.event + 1] - off;
@@ -812,6 +798,7 @@ __device__ __forceinline__ void expanded_item(const FieldArgs& a, const FieldIte
     const uint32_t t_end = min(it.end, ntiles);
     const int tid = threadIdx.x;
     const int wave = tid >> 6, lane = tid & 63;
+    const int q = lane >> 4, col = lane & 15;
 
     const uint32_t ts = tbase + (uint32_t)tid;
     double px = 0.0, py = 0.0, pz = 0.0;
@@ -821,38 +808,62 @@ __device__ __forceinline__ void expanded_item(const FieldArgs& a, const FieldIte
         px = a.px[off + ts];
         py = a.py[off + ts];
         pz = a.pz[off + ts];
-        lo_x = hi_x = px;
-        lo_y = hi_y = py;
-        lo_z = hi_z = pz;
     }
-    lo_x = wave_min(lo_x);
-    lo_y = wave_min(lo_y);
-    lo_z = wave_min(lo_z);
-    hi_x = wave_max(hi_x);
-    hi_y = wave_max(hi_y);
-    hi_z = wave_max(hi_z);
-    // this wave's own 64 targets: each wave classifies the source tiles by
-    // their distance from its own box (at least their distance from the
-    // workgroup's), so a tile near only the other waves' targets is far here
-    const double wl_x = uniform(lo_x), wl_y = uniform(lo_y), wl_z = uniform(lo_z);
-    const double wh_x = uniform(hi_x), wh_y = uniform(hi_y), wh_z = uniform(hi_z);
-    if (lane == 0) {
-        box[0][wave] = lo_x;
-        box[1][wave] = lo_y;
-        box[2][wave] = lo_z;
-        box[3][wave] = hi_x;
-        box[4][wave] = hi_y;
-        box[5][wave] = hi_z;
-    }
-    __syncthreads();
+    // The boxes of the block's targets (origin, rho) and of this lane's group of
+    // 16, from which source groups are classified.  Where every target is a
+    // source, they are boxes of one source tile, which the list holds (the last
+    // block's may also hold sources that are no targets); else they are reduced
+    // from the positions.
+    double gl_x = INFINITY, gl_y = INFINITY, gl_z = INFINITY;
+    double gh_x = -INFINITY, gh_y = -INFINITY, gh_z = -INFINITY;
+    if (nt <= ns) {
+        const double* tb = a.tile_box + tile0 + it.blk;
+        const size_t st = a.tile_stride;
+        lo_x = tb[0];
+        lo_y = tb[st];
+        lo_z = tb[2 * st];
+        hi_x = tb[3 * st];
+        hi_y = tb[4 * st];
+        hi_z = tb[5 * st];
+        tb += (size_t)(30 + (tid >> 4)) * st;
+        gl_x = tb[0];
+        gl_y = tb[16 * st];
+        gl_z = tb[32 * st];
+        gh_x = tb[48 * st];
+        gh_y = tb[64 * st];
+        gh_z = tb[80 * st];
+    } else {
+        if (ts < nt) {
+            gl_x = gh_x = px;
+            gl_y = gh_y = py;
+            gl_z = gh_z = pz;
+        }
 #pragma unroll
-    for (int w = 0; w < kFieldThreads / 64; ++w) {
-        lo_x = fmin(lo_x, box[0][w]);
-        lo_y = fmin(lo_y, box[1][w]);
-        lo_z = fmin(lo_z, box[2][w]);
-        hi_x = fmax(hi_x, box[3][w]);
-        hi_y = fmax(hi_y, box[4][w]);
-        hi_z = fmax(hi_z, box[5][w]);
+        for (int k = 8; k >= 1; k >>= 1) {
+            gl_x = fmin(gl_x, __shfl_xor(gl_x, k));
+            gl_y = fmin(gl_y, __shfl_xor(gl_y, k));
+            gl_z = fmin(gl_z, __shfl_xor(gl_z, k));
+            gh_x = fmax(gh_x, __shfl_xor(gh_x, k));
+            gh_y = fmax(gh_y, __shfl_xor(gh_y, k));
+            gh_z = fmax(gh_z, __shfl_xor(gh_z, k));
+        }
+        if (col == 0) {
+            L.box[0][tid >> 4] = gl_x;
+            L.box[1][tid >> 4] = gl_y;
+            L.box[2][tid >> 4] = gl_z;
+            L.box[3][tid >> 4] = gh_x;
+            L.box[4][tid >> 4] = gh_y;
+            L.box[5][tid >> 4] = gh_z;
+        }
+        __syncthreads();
+        for (int w = 0; w < kFieldThreads / 16; ++w) {
+            lo_x = fmin(lo_x, L.box[0][w]);
+            lo_y = fmin(lo_y, L.box[1][w]);
+            lo_z = fmin(lo_z, L.box[2][w]);
+            hi_x = fmax(hi_x, L.box[3][w]);
+            hi_y = fmax(hi_y, L.box[4][w]);
+            hi_z = fmax(hi_z, L.box[5][w]);
+        }
     }
     lo_x = uniform(lo_x);
     lo_y = uniform(lo_y);
@@ -862,33 +873,19 @@ __device__ __forceinline__ void expanded_item(const FieldArgs& a, const FieldIte
     hi_z = uniform(hi_z);
     const double ox = 0.5 * (lo_x + hi_x), oy = 0.5 * (lo_y + hi_y), oz = 0.5 * (lo_z + hi_z);
     const double hx = 0.5 * (hi_x - lo_x), hy = 0.5 * (hi_y - lo_y), hz = 0.5 * (hi_z - lo_z);
-    // no expanded or unchecked tile may hold a pair closer than kExactRadius eps
-    const double rho2 = fmax(hx * hx + hy * hy + hz * hz, a.acc_box2);
-    const double rc2d = fmax(0.0625 * (hx * hx + hy * hy + hz * hz), a.acc_box2);  // (rho/4)^2
+    // no far or unchecked group may hold a pair closer than kExactRadius eps.  The
+    // group boxes are held in FP32 relative to the origin, which puts a gap off
+    // by a few 1e-7 of itself: the limits carry a margin of 1e-4.
+    const double rho2 = hx * hx + hy * hy + hz * hz;
+    const float far2 =
+        uniform((float)(1.0001 * fmax(kFarFraction * kFarFraction * rho2, a.acc_box2)));
+    const float glx = (float)(gl_x - ox), gly = (float)(gl_y - oy), glz = (float)(gl_z - oz),
+                ghx = (float)(gh_x - ox), ghy = (float)(gh_y - oy), ghz = (float)(gh_z - oz);
     const double eps2d = (double)a.eps2;
 
-    float thx, thy, thz, tlx, tly, tlz, T;
-    {
-        // lanes past the last target sit at the origin (their sums are unused)
-        const double rx = (ts < nt ? px : ox) - ox, ry = (ts < nt ? py : oy) - oy,
-                     rz = (ts < nt ? pz : oz) - oz;
-        thx = (float)rx;
-        thy = (float)ry;
-        thz = (float)rz;
-        tlx = (float)(rx - (double)thx);
-        tly = (float)(ry - (double)thy);
-        tlz = (float)(rz - (double)thz);
-        T = (float)((double)thx * thx + (double)thy * thy + (double)thz * thz);
-    }
-    // this lane's close-pair radius squared: a quarter of its target's
-    // distance from the origin, as in field_tiles, and at least the exact-sum
-    // radius (0 for the padding lanes)
-    const float rc2 = ts < nt ? fmaxf(0.0625f * T, a.acc2) : 0.0f;
-    float sw = 0.0f, sx = 0.0f, sy = 0.0f, sz = 0.0f;  // far tiles
-    float ex = 0.0f, ey = 0.0f, ez = 0.0f;              // near tiles
-
     double qx = 0.0, qy = 0.0, qz = 0.0;  // this lane's source of the next tile
-    double qb = 0.0;                      // lanes 0-5: one bound of that tile's box
+    double qb = 0.0;                      // lanes 0-95: one bound of one of its groups
+    const double ob = (tid >> 4) % 3 == 0 ? ox : (tid >> 4) % 3 == 1 ? oy : oz;  // its origin
     auto fetch = [&](uint32_t t) {
         const uint32_t i = t * UNIT + (uint32_t)tid;
         qx = ox;
@@ -899,102 +896,240 @@ __device__ __forceinline__ void expanded_item(const FieldArgs& a, const FieldIte
             qy = a.py[off + i];
             qz = a.pz[off + i];
         }
-        if (tid < 6) qb = unit_bound<UNIT>(a, tile0, t, tid);
+        if (tid < 96) {  // rows 30 + 16 k + g of the 256-source tile that holds tile t
+            const uint32_t s0 = t * UNIT;
+            const int g = min((tid & 15) + (int)((s0 & (kTile - 1)) >> 4), 15);
+            qb = a.tile_box[(size_t)(30 + (tid & ~15) + g) * a.tile_stride + tile0 + s0 / kTile];
+        }
     };
-    auto stage = [&](int b) {
-        if (tid < 6) tbox[b][tid] = qb;
+    auto stage = [&](uint32_t t, int b) {
+        MatrixLds::Tile& S = L.tile[b];
+        if (tid < 96) S.gbox[tid >> 4][tid & 15] = (float)(qb - ob);
         const double rx = qx - ox, ry = qy - oy, rz = qz - oz;
         const float fx = (float)rx, fy = (float)ry, fz = (float)rz;
-        sh[b][0][tid] = -2.0f * fx;
-        sh[b][1][tid] = -2.0f * fy;
-        sh[b][2][tid] = -2.0f * fz;
-        sh[b][3][tid] = (float)((double)fx * fx + (double)fy * fy + (double)fz * fz + eps2d);
-        sh[b][4][tid] = (float)(rx - (double)fx);
-        sh[b][5][tid] = (float)(ry - (double)fy);
-        sh[b][6][tid] = (float)(rz - (double)fz);
+        const float mx = -2.0f * fx, my = -2.0f * fy, mz = -2.0f * fz;
+        const bool valid = tid < UNIT && t * UNIT + (uint32_t)tid < ns;
+        S.hl[0][tid] = valid ? mx : kPadX;
+        S.hl[1][tid] = my;
+        S.hl[2][tid] = mz;
+        S.hl[3][tid] = (float)(rx - (double)fx);
+        S.hl[4][tid] = (float)(ry - (double)fy);
+        S.hl[5][tid] = (float)(rz - (double)fz);
+        float s2 = (float)fma((double)fx, (double)fx,
+                             fma((double)fy, (double)fy, fma((double)fz, (double)fz, eps2d)));
+        s2 = valid ? fminf(s2, kPadS) : kPadS;
+        const float v[4] = {mx, my, mz, s2};
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const Bf16x3 p = split_bf16(v[k]);
+            S.pk[tid >> 4][k][tid & 15] = u32x2{p.hm, p.ml};
+        }
     };
+    if (t_first < t_end) fetch(t_first);
+
+    // this lane's target (lanes past the last target sit at the origin, their
+    // sums unused), and its parts of the B operands of the wave's four groups
+    // of 16 targets
+    float thx, thy, thz, tlx, tly, tlz;
+    bf16x8 B[4];
+    {
+        const double rx = (ts < nt ? px : ox) - ox, ry = (ts < nt ? py : oy) - oy,
+                     rz = (ts < nt ? pz : oz) - oz;
+        thx = (float)rx;
+        thy = (float)ry;
+        thz = (float)rz;
+        tlx = (float)(rx - (double)thx);
+        tly = (float)(ry - (double)thy);
+        tlz = (float)(rz - (double)thz);
+        const float T =
+            fminf((float)((double)thx * thx + (double)thy * thy + (double)thz * thz), kPadS);
+        float(&tl)[6][kTile] = L.tile[1].hl;  // staged only after the first barrier below
+        tl[0][tid] = thx;
+        tl[1][tid] = thy;
+        tl[2][tid] = thz;
+        tl[3][tid] = T;
+        __syncthreads();
+        constexpr uint32_t kOne = 0x3F80u;  // 1.0 in bf16
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+            const int tg = wave * 64 + g * 16 + col;
+            const Bf16x3 c = split_bf16(tl[q < 3 ? q : 0][tg]);
+            const Bf16x3 tt = split_bf16(tl[3][tg]);
+            u32x4 w;
+            w[0] = q < 3 ? c.hh : kOne << 16 | kOne;
+            w[1] = q < 3 ? (c.ml & 0xFFFFu) | (c.hh << 16) : kOne << 16;
+            w[2] = q < 3 ? (c.hm >> 16) | (c.ml & 0xFFFF0000u) : 0u;
+            w[3] = q == 0 ? tt.hm : q == 1 ? tt.ml >> 16 : 0u;
+            B[g] = __builtin_bit_cast(bf16x8, w);
+        }
+    }
+    float e2 = a.eps2;
+    float rx = ts < nt ? a.acc2 : 0.0f;  // lanes past the last target record nothing
+    asm volatile("" : "+v"(e2), "+v"(rx));  // vector registers (see comp_quad)
+    float ex = 0.0f, ey = 0.0f, ez = 0.0f;
+    uint32_t nx = 0;  // pairs in this wave's list
 
     int buf = 0;
-    if (t_first < t_end) {
-        fetch(t_first);
-        stage(0);
-    }
+    if (t_first < t_end) stage(t_first, 0);
     __syncthreads();
     for (uint32_t t = t_first; t < t_end; t += step_t) {
         const uint32_t next = t + step_t;
         if (next < t_end) fetch(next);
+        const MatrixLds::Tile& S = L.tile[buf];
         const uint32_t cnt = min((uint32_t)UNIT, ns - t * UNIT);
-        const float* mxp = sh[buf][0];
-        const float* myp = sh[buf][1];
-        const float* mzp = sh[buf][2];
-        const double* tb = tbox[buf];
-        const double gx = fmax(0.0, fmax(tb[0] - wh_x, wl_x - tb[3]));
-        const double gy = fmax(0.0, fmax(tb[1] - wh_y, wl_y - tb[4]));
-        const double gz = fmax(0.0, fmax(tb[2] - wh_z, wl_z - tb[5]));
-        const double g2 = gx * gx + gy * gy + gz * gz;  // wave-uniform
-        if (g2 > rho2) {
-            const float* Sp = sh[buf][3];
-            float bw = 0.0f, bx = 0.0f, by = 0.0f, bz = 0.0f;
-            uint32_t k = 0;
-            for (; k + 4 <= cnt; k += 4) {
-                const float4 x4 = *reinterpret_cast<const float4*>(mxp + k);
-                const float4 y4 = *reinterpret_cast<const float4*>(myp + k);
-                const float4 z4 = *reinterpret_cast<const float4*>(mzp + k);
-                const float4 s4 = *reinterpret_cast<const float4*>(Sp + k);
-                expanded_pair(x4.x, y4.x, z4.x, s4.x, T, thx, thy, thz, bw, bx, by, bz);
-                expanded_pair(x4.y, y4.y, z4.y, s4.y, T, thx, thy, thz, bw, bx, by, bz);
-                expanded_pair(x4.z, y4.z, z4.z, s4.z, T, thx, thy, thz, bw, bx, by, bz);
-                expanded_pair(x4.w, y4.w, z4.w, s4.w, T, thx, thy, thz, bw, bx, by, bz);
-            }
-            for (; k < cnt; ++k)
-                expanded_pair(mxp[k], myp[k], mzp[k], Sp[k], T, thx, thy, thz, bw, bx, by, bz);
-            sw += bw;
-            sx += bx;
-            sy += by;
-            sz += bz;
-        } else {
-            float bx = 0.0f, by = 0.0f, bz = 0.0f;
-            if (g2 >= rc2d)
-                diff_tile<false>(a, L.xl, t * UNIT, mxp, myp, mzp, sh[buf][4], sh[buf][5], sh[buf][6], cnt,
-                                 thx, thy, thz, tlx, tly, tlz, a.eps2, rc2, bx, by, bz);
-            else if (COMP)
-                comp_tile(a, L.xl, t * UNIT, mxp, myp, mzp, sh[buf][4], sh[buf][5], sh[buf][6], cnt, thx,
-                          thy, thz, tlx, tly, tlz, a.eps2, rc2, bx, by, bz);
-            else
-                diff_tile<true>(a, L.xl, t * UNIT, mxp, myp, mzp, sh[buf][4], sh[buf][5], sh[buf][6], cnt,
-                                thx, thy, thz, tlx, tly, tlz, a.eps2, rc2, bx, by, bz);
-            ex += bx;
-            ey += by;
-            ez += bz;
+        // lane 16 g + c: target group g of the wave against source group c
+        uint64_t far_b;
+        uint32_t groups;
+        {
+            const float gx = fmaxf(0.0f, fmaxf(S.gbox[0][col] - ghx, glx - S.gbox[3][col]));
+            const float gy = fmaxf(0.0f, fmaxf(S.gbox[1][col] - ghy, gly - S.gbox[4][col]));
+            const float gz = fmaxf(0.0f, fmaxf(S.gbox[2][col] - ghz, glz - S.gbox[5][col]));
+            const float g2 = gx * gx + gy * gy + gz * gz;
+            const bool valid = (uint32_t)col * 16u < cnt;
+            groups = (uint32_t)__ballot(valid) & 0xFFFFu;
+            far_b = __ballot(valid && g2 > far2);
         }
-        if (next < t_end) stage(buf ^ 1);
+        const uint32_t far_g[4] = {(uint32_t)far_b & 0xFFFFu, (uint32_t)far_b >> 16,
+                                   (uint32_t)(far_b >> 32) & 0xFFFFu, (uint32_t)(far_b >> 48)};
+        uint32_t far_m = far_g[0] & far_g[1] & far_g[2] & far_g[3];  // far from all four
+        const uint32_t far_all = far_m;
+        if (far_b) {
+            f32x4 acc[4];  // of target group g: sums of w, -2 s_x w, -2 s_y w, -2 s_z w
+#pragma unroll
+            for (int g = 0; g < 4; ++g) acc[g] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+            auto source_group = [&](int grp, bf16x8& A, f32x4& x4, f32x4& y4, f32x4& z4) {
+                const u32x2 pw = S.pk[grp][q][col];
+                const u32x4 aw = {pw[0], pw[1],
+                                  __builtin_amdgcn_perm(pw[0], pw[0], 0x05040504u), 0x3F803F80u};
+                A = __builtin_bit_cast(bf16x8, aw);
+                x4 = *reinterpret_cast<const f32x4*>(&S.hl[0][grp * 16 + q * 4]);
+                y4 = *reinterpret_cast<const f32x4*>(&S.hl[1][grp * 16 + q * 4]);
+                z4 = *reinterpret_cast<const f32x4*>(&S.hl[2][grp * 16 + q * 4]);
+            };
+            auto r2_of = [&](const bf16x8& A, int g) {
+                return __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                    A, B[g], f32x4{0.0f, 0.0f, 0.0f, 0.0f}, 0, 0, 0);
+            };
+            auto add_terms = [&](int g, const f32x4& inv, const f32x4& x4, const f32x4& y4,
+                                 const f32x4& z4) {
+                // w of source u in element u ^ 1 of a register quadruple, opposite in
+                // parity to the coordinates' element u: an instruction whose three
+                // vector registers are all even or all odd takes twice as long
+                f32x4 w;
+#pragma unroll
+                for (int u = 0; u < 4; ++u) w[u ^ 1] = inv[u] * inv[u] * inv[u];
+                asm("" : "+v"(w));
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    acc[g][0] += w[u ^ 1];
+                    acc[g][1] = __builtin_fmaf(x4[u], w[u ^ 1], acc[g][1]);
+                    acc[g][2] = __builtin_fmaf(y4[u], w[u ^ 1], acc[g][2]);
+                    acc[g][3] = __builtin_fmaf(z4[u], w[u ^ 1], acc[g][3]);
+                }
+            };
+            while (far_m) {
+                const int grp = __builtin_ctz(far_m);
+                far_m &= far_m - 1u;
+                bf16x8 A;
+                f32x4 x4, y4, z4, d[4];
+                source_group(grp, A, x4, y4, z4);
+#pragma unroll
+                for (int g = 0; g < 4; ++g) d[g] = r2_of(A, g);
+#pragma unroll
+                for (int g = 0; g < 4; g += 2) {
+                    transcendental_begin();
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) d[g][u] = __builtin_amdgcn_rsqf(d[g][u]);
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) d[g + 1][u] = __builtin_amdgcn_rsqf(d[g + 1][u]);
+                    transcendental_end();
+                    add_terms(g, d[g], x4, y4, z4);
+                    add_terms(g + 1, d[g + 1], x4, y4, z4);
+                }
+            }
+#pragma unroll
+            for (int g = 0; g < 4; ++g) {
+                uint32_t m = far_g[g] & ~far_all;
+                while (m) {
+                    const int grp = __builtin_ctz(m);
+                    m &= m - 1u;
+                    bf16x8 A;
+                    f32x4 x4, y4, z4;
+                    source_group(grp, A, x4, y4, z4);
+                    f32x4 d = r2_of(A, g);
+                    transcendental_begin();
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) d[u] = __builtin_amdgcn_rsqf(d[u]);
+                    transcendental_end();
+                    add_terms(g, d, x4, y4, z4);
+                }
+            }
+            // add the quarters: lane 16 r + c ends with target c of group r
+            float tot[4];
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                auto add32 = [](float u, float v) {
+                    const auto r = __builtin_amdgcn_permlane32_swap(
+                        __float_as_uint(u), __float_as_uint(v), false, false);
+                    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+                };
+                auto add16 = [](float u, float v) {
+                    const auto r = __builtin_amdgcn_permlane16_swap(
+                        __float_as_uint(u), __float_as_uint(v), false, false);
+                    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+                };
+                tot[c] = add16(add32(acc[0][c], acc[2][c]), add32(acc[1][c], acc[3][c]));
+            }
+            // t sum w - sum s w of the tile, the second held as -2 sum s w
+            ex += __builtin_fmaf(thx, tot[0], 0.5f * tot[1]);
+            ey += __builtin_fmaf(thy, tot[0], 0.5f * tot[2]);
+            ez += __builtin_fmaf(thz, tot[0], 0.5f * tot[3]);
+        }
+        // near blocks: the lanes' targets of group g, each lane four sources of a group
+        for (int g = 0; g < 4; ++g) {
+            uint32_t m = groups & ~((uint32_t)(far_b >> (16 * g)) & 0xFFFFu);
+            if (m == 0u) continue;
+            const int tg = g * 16 + col;
+            const float hx_ = __shfl(thx, tg), hy_ = __shfl(thy, tg), hz_ = __shfl(thz, tg);
+            const float lx_ = __shfl(tlx, tg), ly_ = __shfl(tly, tg), lz_ = __shfl(tlz, tg);
+            const float rx_ = __shfl(rx, tg);
+            float bx = 0.0f, by = 0.0f, bz = 0.0f;
+            do {
+                // sources past the last one are staged too, far enough away to
+                // add nothing
+                const uint32_t k = (uint32_t)__builtin_ctz(m) * 16u + (uint32_t)q * 4u;
+                m &= m - 1u;
+                comp_quad(L.xl[wave], nx, (uint32_t)(wave * 64 + tg), t * UNIT + k, S.hl, k, hx_,
+                          hy_, hz_, lx_, ly_, lz_, e2, rx_, bx, by, bz);
+            } while (m);
+            const float tx = add_quarters(bx), ty = add_quarters(by), tz = add_quarters(bz);
+            ex += q == g ? tx : 0.0f;
+            ey += q == g ? ty : 0.0f;
+            ez += q == g ? tz : 0.0f;
+        }
+        if (next < t_end) stage(next, buf ^ 1);
         __syncthreads();
         buf ^= 1;
     }
-    exact_flush(a, L.xl, off, tbase);
+    for (uint32_t i = (uint32_t)lane; i < nx; i += 64)
+        exact_add(a, off + tbase + L.xl[wave].tgt[i], off + L.xl[wave].src[i]);
 
     if (ts < nt) {
-        // t sum w - sum s w, the second held as -2 sum s w
-        const float fx = (float)((double)thx * sw + 0.5 * (double)sx) + ex;
-        const float fy = (float)((double)thy * sw + 0.5 * (double)sy) + ey;
-        const float fz = (float)((double)thz * sw + 0.5 * (double)sz) + ez;
-        a.part[(size_t)(chunk * 3 + 0) * a.pstride + off + ts] = fx;
-        a.part[(size_t)(chunk * 3 + 1) * a.pstride + off + ts] = fy;
-        a.part[(size_t)(chunk * 3 + 2) * a.pstride + off + ts] = fz;
+        a.part[(size_t)(chunk * 3 + 0) * a.pstride + off + ts] = ex;
+        a.part[(size_t)(chunk * 3 + 1) * a.pstride + off + ts] = ey;
+        a.part[(size_t)(chunk * 3 + 2) * a.pstride + off + ts] = ez;
     }
 }
 
 // One workgroup per work item.
-template <bool COMP, int UNIT>
-__global__ __launch_bounds__(kFieldThreads) void field_tiles_expanded(FieldArgs a) {
-    // the item, the count and event 0's travelling holes are read together
-    // (the grid never exceeds the item capacity, so the item is in bounds)
+template <int UNIT>
+__global__ __launch_bounds__(kFieldThreads) __attribute__((amdgpu_waves_per_eu(4)))
+void field_tiles_matrix(FieldArgs a) {
     const FieldItem it = a.items[blockIdx.x];
     const uint32_t na0 = a.ev_active[0];
     if (a.count_items && blockIdx.x >= *a.n_items) return;  // the whole workgroup
-    __shared__ __align__(16) ExpandedLds L;
-    if (threadIdx.x == 0) L.xl.n = 0;  // ordered before any push by the item's first barrier
-    expanded_item<COMP, UNIT>(a, it, L, na0);
+    __shared__ __align__(16) MatrixLds L;
+    matrix_item<UNIT>(a, it, L, na0);
 }
 
 // Persistent form: a fixed grid of workgroups takes the items in list order
@@ -1002,21 +1137,20 @@ __global__ __launch_bounds__(kFieldThreads) void field_tiles_expanded(FieldArgs 
 // Every workgroup leaves once the counter has passed the end, so the grid
 // drains whatever the item count; the grid and the arguments stay the same
 // when the items are rebuilt, which lets a captured graph be replayed.
-template <bool COMP, int UNIT>
-__global__ __launch_bounds__(kFieldThreads) __attribute__((amdgpu_waves_per_eu(7)))
-void field_queue_expanded(FieldArgs a) {
-    __shared__ __align__(16) ExpandedLds L;
+template <int UNIT>
+__global__ __launch_bounds__(kFieldThreads) __attribute__((amdgpu_waves_per_eu(4)))
+void field_queue_matrix(FieldArgs a) {
+    __shared__ __align__(16) MatrixLds L;
     __shared__ uint32_t next;
     const uint32_t n_items = *a.n_items;
     const uint32_t na0 = a.ev_active[0];
-    if (threadIdx.x == 0) L.xl.n = 0;  // ordered before any push by the barriers below
     for (;;) {
         if (threadIdx.x == 0) next = atomicAdd(a.queue, 1u);
         __syncthreads();
         const uint32_t i = next;
         __syncthreads();  // every lane has read `next` before lane 0 writes it again
         if (i >= n_items) break;
-        expanded_item<COMP, UNIT>(a, a.items[i], L, na0);
+        matrix_item<UNIT>(a, a.items[i], L, na0);
     }
 }
 
@@ -1382,7 +1516,7 @@ static hipError_t launch_field_prec(const FieldArgs& a, int tpt, uint32_t n_item
 int field_queue_slots_per_cu() {
     int n = 0;
     if (hipOccupancyMaxActiveBlocksPerMultiprocessor(
-            &n, reinterpret_cast<const void*>(field_queue_expanded<false, kTile>), kFieldThreads,
+            &n, reinterpret_cast<const void*>(field_queue_matrix<kTile>), kFieldThreads,
             0) !=
         hipSuccess) {
         (void)hipGetLastError();
@@ -1406,7 +1540,7 @@ int field_slots_per_cu(int tpt, int precision) {
                 &n, reinterpret_cast<const void*>(field_tiles_f64<4>), kFieldThreads, 0);
     } else if (tpt == 1 && precision == GCCD_PRECISION_DEFAULT) {
         e = hipOccupancyMaxActiveBlocksPerMultiprocessor(
-            &n, reinterpret_cast<const void*>(field_tiles_expanded<false, kTile>), kFieldThreads, 0);
+            &n, reinterpret_cast<const void*>(field_tiles_matrix<kTile>), kFieldThreads, 0);
     } else if (tpt == 1) {
         e = hipOccupancyMaxActiveBlocksPerMultiprocessor(
             &n, reinterpret_cast<const void*>(field_tiles<1, GCCD_PRECISION_BLOCK>),
@@ -1434,19 +1568,15 @@ hipError_t launch_field(const FieldArgs& a, int tpt, int precision, uint32_t n_i
             return hipErrorInvalidValue;
         FieldArgs b = a;
         b.count_items = 1;
-        const bool c = b.near_compensated != 0;
         switch (b.unit) {
             case kTile / 4:
-                if (c) field_tiles_expanded<true, kTile / 4><<<grid_cap, kFieldThreads, 0, s>>>(b);
-                else field_tiles_expanded<false, kTile / 4><<<grid_cap, kFieldThreads, 0, s>>>(b);
+                field_tiles_matrix<kTile / 4><<<grid_cap, kFieldThreads, 0, s>>>(b);
                 break;
             case kTile / 2:
-                if (c) field_tiles_expanded<true, kTile / 2><<<grid_cap, kFieldThreads, 0, s>>>(b);
-                else field_tiles_expanded<false, kTile / 2><<<grid_cap, kFieldThreads, 0, s>>>(b);
+                field_tiles_matrix<kTile / 2><<<grid_cap, kFieldThreads, 0, s>>>(b);
                 break;
             case kTile:
-                if (c) field_tiles_expanded<true, kTile><<<grid_cap, kFieldThreads, 0, s>>>(b);
-                else field_tiles_expanded<false, kTile><<<grid_cap, kFieldThreads, 0, s>>>(b);
+                field_tiles_matrix<kTile><<<grid_cap, kFieldThreads, 0, s>>>(b);
                 break;
             default: return hipErrorInvalidValue;
         }
@@ -1456,19 +1586,15 @@ hipError_t launch_field(const FieldArgs& a, int tpt, int precision, uint32_t n_i
         // the item count is read on the device: launched even with none
         const hipError_t e = launch_fill_u32(a.queue, 1u, 0u, s);
         if (e != hipSuccess) return e;
-        const bool c = a.near_compensated != 0;
         switch (a.unit) {
             case kTile / 4:
-                if (c) field_queue_expanded<true, kTile / 4><<<queue_grid, kFieldThreads, 0, s>>>(a);
-                else field_queue_expanded<false, kTile / 4><<<queue_grid, kFieldThreads, 0, s>>>(a);
+                field_queue_matrix<kTile / 4><<<queue_grid, kFieldThreads, 0, s>>>(a);
                 break;
             case kTile / 2:
-                if (c) field_queue_expanded<true, kTile / 2><<<queue_grid, kFieldThreads, 0, s>>>(a);
-                else field_queue_expanded<false, kTile / 2><<<queue_grid, kFieldThreads, 0, s>>>(a);
+                field_queue_matrix<kTile / 2><<<queue_grid, kFieldThreads, 0, s>>>(a);
                 break;
             case kTile:
-                if (c) field_queue_expanded<true, kTile><<<queue_grid, kFieldThreads, 0, s>>>(a);
-                else field_queue_expanded<false, kTile><<<queue_grid, kFieldThreads, 0, s>>>(a);
+                field_queue_matrix<kTile><<<queue_grid, kFieldThreads, 0, s>>>(a);
                 break;
             default: return hipErrorInvalidValue;
         }
@@ -1481,19 +1607,15 @@ hipError_t launch_field(const FieldArgs& a, int tpt, int precision, uint32_t n_i
     switch (precision) {
         case GCCD_PRECISION_DEFAULT:
             if (tpt == 1) {
-                const bool c = a.near_compensated != 0;
                 switch (a.unit) {
                     case kTile / 4:
-                        if (c) field_tiles_expanded<true, kTile / 4><<<n_items, kFieldThreads, 0, s>>>(a);
-                        else field_tiles_expanded<false, kTile / 4><<<n_items, kFieldThreads, 0, s>>>(a);
+                        field_tiles_matrix<kTile / 4><<<n_items, kFieldThreads, 0, s>>>(a);
                         break;
                     case kTile / 2:
-                        if (c) field_tiles_expanded<true, kTile / 2><<<n_items, kFieldThreads, 0, s>>>(a);
-                        else field_tiles_expanded<false, kTile / 2><<<n_items, kFieldThreads, 0, s>>>(a);
+                        field_tiles_matrix<kTile / 2><<<n_items, kFieldThreads, 0, s>>>(a);
                         break;
                     case kTile:
-                        if (c) field_tiles_expanded<true, kTile><<<n_items, kFieldThreads, 0, s>>>(a);
-                        else field_tiles_expanded<false, kTile><<<n_items, kFieldThreads, 0, s>>>(a);
+                        field_tiles_matrix<kTile><<<n_items, kFieldThreads, 0, s>>>(a);
                         break;
                     default: return hipErrorInvalidValue;
                 }
