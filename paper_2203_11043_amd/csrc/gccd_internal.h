@@ -220,6 +220,7 @@ constexpr int kGridNodes = kGrid * kGrid * kGrid;
 constexpr double kSigmaCells = 0.5;          // h = 0.5 x rms width per axis
 constexpr double kMaxDevCells = 14.0;        // no charge farther than 14 h from the centroid
 constexpr double kNearCells = 0.8;           // a = 0.8 h
+constexpr int kNearMatrixMin = 1 << 16;      // smallest load whose near sum takes the matrix kernel
 constexpr int kMomBlocks = 512;              // fixed partition of the placement reduction
 
 // Written on the device each time the closure field is computed.
@@ -246,7 +247,8 @@ struct ConvArgs {
     int32_t out_stride, out_off, cout;
 };
 
-hipError_t launch_near(const FieldArgs& a, const GridParams* gp, uint32_t n_items,
+// n: holes of the load (chooses the kernel)
+hipError_t launch_near(const FieldArgs& a, const GridParams* gp, uint32_t n, uint32_t n_items,
                        hipStream_t s);
 hipError_t launch_moments(const double* x, const double* y, const double* z, uint32_t n,
                           double* part, hipStream_t s);

@@ -14,6 +14,7 @@
 #include "gccd_sort_dev.h"
 
 #include <math.h>
+#include <type_traits>
 
 namespace gccd {
 
@@ -635,6 +636,15 @@ __global__ __launch_bounds__(kFieldThreads) void field_tiles(FieldArgs a) {
     }
 }
 
+// The cutoff r^2 + eps^2 < cut2 of the near sum as factors of 0 or 1 (see
+// comp_quad), on r^2 and on its reciprocal square root.
+struct CutoffTest {
+    float big_r2 = 0.0f, lim_r2 = 0.0f;    // clamp(lim_r2 - big_r2 r^2)
+    float big_inv = 0.0f, lim_inv = 0.0f;  // clamp(big_inv / r - lim_inv)
+};
+
+__device__ __forceinline__ float clamp01(float v) { return __builtin_amdgcn_fmed3f(v, 0.0f, 1.0f); }
+
 // One source quadruple of a near block in the compensated difference form:
 // sources k .. k + 3 of the staged tile (sources src .. src + 3 of the event)
 // at the lane's target, number tgt of the block.  The four reciprocal square
@@ -647,10 +657,16 @@ __global__ __launch_bounds__(kFieldThreads) void field_tiles(FieldArgs a) {
 // which are recorded for exact summation.  e2 is the softening and rx the
 // exact-sum limit (0 for a lane without a target) in vector registers (an
 // instruction with a scalar operand does not pair either).
+// CUT: the term counts only while r^2 < cut2, as a factor clamp(big (cut2 -
+// r^2)) of 0 or 1 (big: a power of two that makes one unit in the last place
+// exceed 1); no pair is recorded.  Two full-rate instructions where compare and
+// select are two half-rate ones.
+template <bool CUT>
 __device__ __forceinline__ void comp_quad(WaveList& xl, uint32_t& nx, uint32_t tgt, uint32_t src,
                                           const float (&hl)[6][kTile], uint32_t k, float thx,
                                           float thy, float thz, float tlx, float tly, float tlz,
-                                          float e2, float rx, float& bx, float& by, float& bz) {
+                                          float e2, float rx, const CutoffTest& ct, float& bx, float& by,
+                                          float& bz) {
     const f32x4 x4 = *reinterpret_cast<const f32x4*>(&hl[0][k]);
     const f32x4 y4 = *reinterpret_cast<const f32x4*>(&hl[1][k]);
     const f32x4 z4 = *reinterpret_cast<const f32x4*>(&hl[2][k]);
@@ -668,22 +684,24 @@ __device__ __forceinline__ void comp_quad(WaveList& xl, uint32_t& nx, uint32_t t
         r2[u] = __builtin_fmaf(dy[u], dy[u], r2[u]);
         r2[u] = __builtin_fmaf(dz[u], dz[u], r2[u]);
     }
-    const float m = fminf(fminf(r2[0], r2[1]), fminf(r2[2], r2[3]));
-    if (__builtin_expect(__ballot(m < rx) != 0ull, 0)) {
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const bool rec = r2[u] < rx && r2[u] > e2;
-            const uint64_t who = __ballot(rec);
-            if (who) {
-                const uint32_t i =
-                    nx + __builtin_amdgcn_mbcnt_hi((uint32_t)(who >> 32),
-                                                   __builtin_amdgcn_mbcnt_lo((uint32_t)who, 0u));
-                if (rec && i < (uint32_t)kWaveCap) {
-                    xl.src[i] = src + (uint32_t)u;
-                    xl.tgt[i] = (uint8_t)tgt;
-                    dx[u] = dy[u] = dz[u] = 0.0f;
+    if constexpr (!CUT) {
+        const float m = fminf(fminf(r2[0], r2[1]), fminf(r2[2], r2[3]));
+        if (__builtin_expect(__ballot(m < rx) != 0ull, 0)) {
+    #pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const bool rec = r2[u] < rx && r2[u] > e2;
+                const uint64_t who = __ballot(rec);
+                if (who) {
+                    const uint32_t i =
+                        nx + __builtin_amdgcn_mbcnt_hi((uint32_t)(who >> 32),
+                                                       __builtin_amdgcn_mbcnt_lo((uint32_t)who, 0u));
+                    if (rec && i < (uint32_t)kWaveCap) {
+                        xl.src[i] = src + (uint32_t)u;
+                        xl.tgt[i] = (uint8_t)tgt;
+                        dx[u] = dy[u] = dz[u] = 0.0f;
+                    }
+                    nx = min(nx + (uint32_t)__popcll(who), (uint32_t)kWaveCap);
                 }
-                nx = min(nx + (uint32_t)__popcll(who), (uint32_t)kWaveCap);
             }
         }
     }
@@ -693,7 +711,8 @@ __device__ __forceinline__ void comp_quad(WaveList& xl, uint32_t& nx, uint32_t t
     transcendental_end();
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
-        const float w = inv[u] * inv[u] * inv[u];
+        float w = inv[u] * inv[u] * inv[u];
+        if constexpr (CUT) w *= clamp01(__builtin_fmaf(r2[u], -ct.big_r2, ct.lim_r2));
         bx = __builtin_fmaf(dx[u], w, bx);
         by = __builtin_fmaf(dy[u], w, by);
         bz = __builtin_fmaf(dz[u], w, bz);
@@ -766,7 +785,10 @@ struct MatrixLds {
         float gbox[6][16];            // boxes of the 16-source groups, relative to the origin
     } tile[2];
     double box[6][kFieldThreads / 16];
-    WaveList xl[kFieldThreads / 64];  // close pairs of the item
+    union {
+        WaveList xl[kFieldThreads / 64];  // close pairs of the item
+        uint32_t list[1024];              // CUT: groups (tile * 16 + group) to be staged
+    };
 };
 
 // The sum of v over the lanes of one column (lane % 16), in each of them.
@@ -779,9 +801,17 @@ __device__ __forceinline__ float add_quarters(float v) {
     return __uint_as_float(s[0]) + __uint_as_float(s[1]);
 }
 
-template <int UNIT>
+// CUT: the near part of the closure's split, the sum over the sources closer
+// than a only (r^2 + eps^2 < a^2 + eps^2, gp).  Of the item's tiles, 64 tested at
+// a time, the 16-source groups within a of the workgroup's targets are listed,
+// and sixteen of them at a time are staged as one tile: the boundary of the
+// a-ball cuts through most tiles, and staging whole ones left the waves waiting
+// for whichever had most of a tile within reach.  Of the staged tile's blocks those whose boxes
+// come within a are summed; far source groups that lie within a as a whole for
+// all four target groups skip the cutoff.  No pair is summed exactly.
+template <int UNIT, bool CUT>
 __device__ __forceinline__ void matrix_item(const FieldArgs& a, const FieldItem it, MatrixLds& L,
-                                            uint32_t na0) {
+                                            uint32_t na0, const GridParams* gp = nullptr) {
     const bool one = a.one_event_n != 0u;
     const uint32_t off = one ? 0u : a.ev_off[it.event];
     const uint32_t ne = one ? a.one_event_n : a.ev_off[it.event + 1] - off;
@@ -886,30 +916,45 @@ __device__ __forceinline__ void matrix_item(const FieldArgs& a, const FieldItem 
     double qx = 0.0, qy = 0.0, qz = 0.0;  // this lane's source of the next tile
     double qb = 0.0;                      // lanes 0-95: one bound of one of its groups
     const double ob = (tid >> 4) % 3 == 0 ? ox : (tid >> 4) % 3 == 1 ? oy : oz;  // its origin
-    auto fetch = [&](uint32_t t) {
-        const uint32_t i = t * UNIT + (uint32_t)tid;
+    bool qv = false;                      // that source exists
+    uint32_t n_list = 0;                  // CUT: groups listed, in L.list
+    // tile number i of the batch: the item's tile t_first + i S, or (CUT) sixteen
+    // listed groups
+    auto fetch = [&](uint32_t i) {
+        uint32_t j, row, tile;  // source slot; lanes 0-95: box row and tile of their group
+        if constexpr (CUT) {
+            const uint32_t g = i * 16u + (uint32_t)(tid >> 4), gb = i * 16u + (uint32_t)col;
+            const uint32_t G = L.list[min(g, n_list - 1u)], Gb = L.list[min(gb, n_list - 1u)];
+            j = G * 16u + (uint32_t)col;
+            qv = g < n_list && j < ns;
+            row = 30u + (uint32_t)(tid & ~15) + (Gb & 15u);
+            tile = Gb >> 4;
+        } else {
+            const uint32_t s0 = (t_first + i * step_t) * UNIT;
+            j = s0 + (uint32_t)tid;
+            qv = tid < UNIT && j < ns;
+            // rows 30 + 16 k + g of the 256-source tile that holds the tile
+            row = 30u + (uint32_t)(tid & ~15) +
+                  min((uint32_t)col + ((s0 & (kTile - 1)) >> 4), 15u);
+            tile = s0 / kTile;
+        }
         qx = ox;
         qy = oy;
         qz = oz;
-        if (tid < UNIT && i < ns) {
-            qx = a.px[off + i];
-            qy = a.py[off + i];
-            qz = a.pz[off + i];
+        if (qv) {
+            qx = a.px[off + j];
+            qy = a.py[off + j];
+            qz = a.pz[off + j];
         }
-        if (tid < 96) {  // rows 30 + 16 k + g of the 256-source tile that holds tile t
-            const uint32_t s0 = t * UNIT;
-            const int g = min((tid & 15) + (int)((s0 & (kTile - 1)) >> 4), 15);
-            qb = a.tile_box[(size_t)(30 + (tid & ~15) + g) * a.tile_stride + tile0 + s0 / kTile];
-        }
+        if (tid < 96) qb = a.tile_box[(size_t)row * a.tile_stride + tile0 + tile];
     };
-    auto stage = [&](uint32_t t, int b) {
+    auto stage = [&](int b) {
         MatrixLds::Tile& S = L.tile[b];
         if (tid < 96) S.gbox[tid >> 4][tid & 15] = (float)(qb - ob);
         const double rx = qx - ox, ry = qy - oy, rz = qz - oz;
         const float fx = (float)rx, fy = (float)ry, fz = (float)rz;
         const float mx = -2.0f * fx, my = -2.0f * fy, mz = -2.0f * fz;
-        const bool valid = tid < UNIT && t * UNIT + (uint32_t)tid < ns;
-        S.hl[0][tid] = valid ? mx : kPadX;
+        S.hl[0][tid] = qv ? mx : kPadX;
         S.hl[1][tid] = my;
         S.hl[2][tid] = mz;
         S.hl[3][tid] = (float)(rx - (double)fx);
@@ -917,7 +962,7 @@ __device__ __forceinline__ void matrix_item(const FieldArgs& a, const FieldItem 
         S.hl[5][tid] = (float)(rz - (double)fz);
         float s2 = (float)fma((double)fx, (double)fx,
                              fma((double)fy, (double)fy, fma((double)fz, (double)fz, eps2d)));
-        s2 = valid ? fminf(s2, kPadS) : kPadS;
+        s2 = qv ? fminf(s2, kPadS) : kPadS;
         const float v[4] = {mx, my, mz, s2};
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
@@ -925,7 +970,52 @@ __device__ __forceinline__ void matrix_item(const FieldArgs& a, const FieldItem 
             S.pk[tid >> 4][k][tid & 15] = u32x2{p.hm, p.ml};
         }
     };
-    if (t_first < t_end) fetch(t_first);
+    // CUT: lists the groups within a of the targets in the next tiles that have
+    // any.  Every wave does the same work, the first one writes.
+    uint32_t t_test = t_first;  // the next tile to test
+    const double a2 = CUT ? uniform(gp->a2) : 0.0;
+    auto gap2 = [&](const double* tb, size_t st) {  // of the targets' box and one at tb
+        const double gx = fmax(0.0, fmax(tb[0] - hi_x, lo_x - tb[3 * st]));
+        const double gy = fmax(0.0, fmax(tb[st] - hi_y, lo_y - tb[4 * st]));
+        const double gz = fmax(0.0, fmax(tb[2 * st] - hi_z, lo_z - tb[5 * st]));
+        return gx * gx + gy * gy + gz * gz;
+    };
+    auto list_groups = [&]() {
+        n_list = 0;
+        while (n_list == 0 && t_test < t_end) {
+            const uint32_t t0 = t_test, m = t0 + (uint32_t)lane * step_t;
+            t_test += 64u * step_t;
+            uint64_t cand =
+                __ballot(m < t_end && gap2(a.tile_box + tile0 + m, a.tile_stride) < a2);
+            while (cand) {  // four tiles at a time, sixteen lanes each
+                uint32_t t = t_end;
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    const uint32_t b = cand ? t0 + (uint32_t)__builtin_ctzll(cand) * step_t : t_end;
+                    cand &= cand - 1ull;
+                    if (q == k) t = b;
+                }
+                const bool keep =
+                    t < t_end && t * kTile + (uint32_t)col * 16u < ns &&
+                    gap2(a.tile_box + (size_t)(30 + col) * a.tile_stride + tile0 + t,
+                         16 * (size_t)a.tile_stride) < a2;
+                const uint64_t who = __ballot(keep);
+                const uint32_t i =
+                    n_list + __builtin_amdgcn_mbcnt_hi((uint32_t)(who >> 32),
+                                                       __builtin_amdgcn_mbcnt_lo((uint32_t)who, 0u));
+                if (keep && wave == 0) L.list[i] = t * 16u + (uint32_t)col;
+                n_list += (uint32_t)__popcll(who);
+            }
+        }
+    };
+    // the batch: all of the item's tiles, or (CUT) the groups listed at a time
+    uint32_t n_batch = t_first < t_end ? (t_end - t_first + step_t - 1) / step_t : 0u;
+    if constexpr (CUT) {
+        list_groups();
+        __syncthreads();
+        n_batch = (n_list + 15u) / 16u;
+    }
+    if (n_batch) fetch(0u);
 
     // this lane's target (lanes past the last target sit at the origin, their
     // sums unused), and its parts of the B operands of the wave's four groups
@@ -966,33 +1056,52 @@ __device__ __forceinline__ void matrix_item(const FieldArgs& a, const FieldItem 
     float e2 = a.eps2;
     float rx = ts < nt ? a.acc2 : 0.0f;  // lanes past the last target record nothing
     asm volatile("" : "+v"(e2), "+v"(rx));  // vector registers (see comp_quad)
+    CutoffTest ct;
+    float in2 = 0.0f, near_a2 = 0.0f;
+    if constexpr (CUT) {
+        const double cut2 = gp->cut2;
+        const float c2 = (float)cut2, ic = (float)(1.0 / sqrt(cut2));
+        ct.big_r2 = ldexpf(1.0f, 26 - ilogbf(c2));
+        ct.lim_r2 = c2 * ct.big_r2;
+        ct.big_inv = ldexpf(1.0f, 26 - ilogbf(ic));
+        ct.lim_inv = ic * ct.big_inv;
+        asm volatile("" : "+v"(ct.big_r2), "+v"(ct.lim_r2), "+v"(ct.big_inv), "+v"(ct.lim_inv));
+        near_a2 = uniform((float)(1.0001 * a2));
+        in2 = uniform((float)(0.9999 * a2));
+    }
     float ex = 0.0f, ey = 0.0f, ez = 0.0f;
     uint32_t nx = 0;  // pairs in this wave's list
 
     int buf = 0;
-    if (t_first < t_end) stage(t_first, 0);
+    if (n_batch) stage(0);
     __syncthreads();
-    for (uint32_t t = t_first; t < t_end; t += step_t) {
-        const uint32_t next = t + step_t;
-        if (next < t_end) fetch(next);
+    for (uint32_t i = 0; i < n_batch;) {
+        const bool more = i + 1 < n_batch;
+        if (more) fetch(i + 1);
+        const uint32_t src0 = (t_first + i * step_t) * UNIT;  // not CUT: the tile's first source
         const MatrixLds::Tile& S = L.tile[buf];
-        const uint32_t cnt = min((uint32_t)UNIT, ns - t * UNIT);
+        const uint32_t cnt = CUT ? min(16u, n_list - i * 16u) * 16u : min((uint32_t)UNIT, ns - src0);
         // lane 16 g + c: target group g of the wave against source group c
-        uint64_t far_b;
-        uint32_t groups;
+        uint64_t far_b, near_b, in_b = 0;
         {
             const float gx = fmaxf(0.0f, fmaxf(S.gbox[0][col] - ghx, glx - S.gbox[3][col]));
             const float gy = fmaxf(0.0f, fmaxf(S.gbox[1][col] - ghy, gly - S.gbox[4][col]));
             const float gz = fmaxf(0.0f, fmaxf(S.gbox[2][col] - ghz, glz - S.gbox[5][col]));
             const float g2 = gx * gx + gy * gy + gz * gz;
-            const bool valid = (uint32_t)col * 16u < cnt;
-            groups = (uint32_t)__ballot(valid) & 0xFFFFu;
+            bool valid = (uint32_t)col * 16u < cnt;
+            if constexpr (CUT) {
+                valid = valid && g2 < near_a2;
+                const float mx = fmaxf(S.gbox[3][col] - glx, ghx - S.gbox[0][col]);
+                const float my = fmaxf(S.gbox[4][col] - gly, ghy - S.gbox[1][col]);
+                const float mz = fmaxf(S.gbox[5][col] - glz, ghz - S.gbox[2][col]);
+                in_b = __ballot(mx * mx + my * my + mz * mz < in2);
+            }
             far_b = __ballot(valid && g2 > far2);
+            near_b = __ballot(valid) & ~far_b;
         }
         const uint32_t far_g[4] = {(uint32_t)far_b & 0xFFFFu, (uint32_t)far_b >> 16,
                                    (uint32_t)(far_b >> 32) & 0xFFFFu, (uint32_t)(far_b >> 48)};
-        uint32_t far_m = far_g[0] & far_g[1] & far_g[2] & far_g[3];  // far from all four
-        const uint32_t far_all = far_m;
+        const uint32_t far_all = far_g[0] & far_g[1] & far_g[2] & far_g[3];
         if (far_b) {
             f32x4 acc[4];  // of target group g: sums of w, -2 s_x w, -2 s_y w, -2 s_z w
 #pragma unroll
@@ -1010,14 +1119,18 @@ __device__ __forceinline__ void matrix_item(const FieldArgs& a, const FieldItem 
                 return __builtin_amdgcn_mfma_f32_16x16x32_bf16(
                     A, B[g], f32x4{0.0f, 0.0f, 0.0f, 0.0f}, 0, 0, 0);
             };
-            auto add_terms = [&](int g, const f32x4& inv, const f32x4& x4, const f32x4& y4,
-                                 const f32x4& z4) {
+            auto add_terms = [&](auto cut, int g, const f32x4& inv, const f32x4& x4,
+                                 const f32x4& y4, const f32x4& z4) {
                 // w of source u in element u ^ 1 of a register quadruple, opposite in
                 // parity to the coordinates' element u: an instruction whose three
                 // vector registers are all even or all odd takes twice as long
                 f32x4 w;
 #pragma unroll
-                for (int u = 0; u < 4; ++u) w[u ^ 1] = inv[u] * inv[u] * inv[u];
+                for (int u = 0; u < 4; ++u) {
+                    w[u ^ 1] = inv[u] * inv[u] * inv[u];
+                    if constexpr (decltype(cut)::value)
+                        w[u ^ 1] *= clamp01(__builtin_fmaf(inv[u], ct.big_inv, -ct.lim_inv));
+                }
                 asm("" : "+v"(w));
 #pragma unroll
                 for (int u = 0; u < 4; ++u) {
@@ -1027,25 +1140,34 @@ __device__ __forceinline__ void matrix_item(const FieldArgs& a, const FieldItem 
                     acc[g][3] = __builtin_fmaf(z4[u], w[u ^ 1], acc[g][3]);
                 }
             };
-            while (far_m) {
-                const int grp = __builtin_ctz(far_m);
-                far_m &= far_m - 1u;
-                bf16x8 A;
-                f32x4 x4, y4, z4, d[4];
-                source_group(grp, A, x4, y4, z4);
+            auto four_groups = [&](auto cut, uint32_t m) {
+                while (m) {
+                    const int grp = __builtin_ctz(m);
+                    m &= m - 1u;
+                    bf16x8 A;
+                    f32x4 x4, y4, z4, d[4];
+                    source_group(grp, A, x4, y4, z4);
 #pragma unroll
-                for (int g = 0; g < 4; ++g) d[g] = r2_of(A, g);
+                    for (int g = 0; g < 4; ++g) d[g] = r2_of(A, g);
 #pragma unroll
-                for (int g = 0; g < 4; g += 2) {
-                    transcendental_begin();
+                    for (int g = 0; g < 4; g += 2) {
+                        transcendental_begin();
 #pragma unroll
-                    for (int u = 0; u < 4; ++u) d[g][u] = __builtin_amdgcn_rsqf(d[g][u]);
+                        for (int u = 0; u < 4; ++u) d[g][u] = __builtin_amdgcn_rsqf(d[g][u]);
 #pragma unroll
-                    for (int u = 0; u < 4; ++u) d[g + 1][u] = __builtin_amdgcn_rsqf(d[g + 1][u]);
-                    transcendental_end();
-                    add_terms(g, d[g], x4, y4, z4);
-                    add_terms(g + 1, d[g + 1], x4, y4, z4);
+                        for (int u = 0; u < 4; ++u) d[g + 1][u] = __builtin_amdgcn_rsqf(d[g + 1][u]);
+                        transcendental_end();
+                        add_terms(cut, g, d[g], x4, y4, z4);
+                        add_terms(cut, g + 1, d[g + 1], x4, y4, z4);
+                    }
                 }
+            };
+            if constexpr (CUT) {
+                const uint32_t in_all = (uint32_t)(in_b & (in_b >> 16) & (in_b >> 32) & (in_b >> 48));
+                four_groups(std::false_type{}, far_all & in_all);
+                four_groups(std::true_type{}, far_all & ~in_all);
+            } else {
+                four_groups(std::false_type{}, far_all);
             }
 #pragma unroll
             for (int g = 0; g < 4; ++g) {
@@ -1061,7 +1183,7 @@ __device__ __forceinline__ void matrix_item(const FieldArgs& a, const FieldItem 
 #pragma unroll
                     for (int u = 0; u < 4; ++u) d[u] = __builtin_amdgcn_rsqf(d[u]);
                     transcendental_end();
-                    add_terms(g, d, x4, y4, z4);
+                    add_terms(std::bool_constant<CUT>{}, g, d, x4, y4, z4);
                 }
             }
             // add the quarters: lane 16 r + c ends with target c of group r
@@ -1087,7 +1209,7 @@ __device__ __forceinline__ void matrix_item(const FieldArgs& a, const FieldItem 
         }
         // near blocks: the lanes' targets of group g, each lane four sources of a group
         for (int g = 0; g < 4; ++g) {
-            uint32_t m = groups & ~((uint32_t)(far_b >> (16 * g)) & 0xFFFFu);
+            uint32_t m = (uint32_t)(near_b >> (16 * g)) & 0xFFFFu;
             if (m == 0u) continue;
             const int tg = g * 16 + col;
             const float hx_ = __shfl(thx, tg), hy_ = __shfl(thy, tg), hz_ = __shfl(thz, tg);
@@ -1099,17 +1221,31 @@ __device__ __forceinline__ void matrix_item(const FieldArgs& a, const FieldItem 
                 // add nothing
                 const uint32_t k = (uint32_t)__builtin_ctz(m) * 16u + (uint32_t)q * 4u;
                 m &= m - 1u;
-                comp_quad(L.xl[wave], nx, (uint32_t)(wave * 64 + tg), t * UNIT + k, S.hl, k, hx_,
-                          hy_, hz_, lx_, ly_, lz_, e2, rx_, bx, by, bz);
+                comp_quad<CUT>(L.xl[wave], nx, (uint32_t)(wave * 64 + tg), src0 + k, S.hl, k,
+                               hx_, hy_, hz_, lx_, ly_, lz_, e2, rx_, ct, bx, by, bz);
             } while (m);
             const float tx = add_quarters(bx), ty = add_quarters(by), tz = add_quarters(bz);
             ex += q == g ? tx : 0.0f;
             ey += q == g ? ty : 0.0f;
             ez += q == g ? tz : 0.0f;
         }
-        if (next < t_end) stage(next, buf ^ 1);
+        if (more) stage(buf ^ 1);
         __syncthreads();
         buf ^= 1;
+        ++i;
+        if constexpr (CUT) {
+            if (i == n_batch) {  // the next batch; every wave is past the list's last use
+                list_groups();
+                __syncthreads();
+                n_batch = (n_list + 15u) / 16u;
+                i = 0;
+                if (n_batch) {
+                    fetch(0u);
+                    stage(buf);
+                    __syncthreads();
+                }
+            }
+        }
     }
     for (uint32_t i = (uint32_t)lane; i < nx; i += 64)
         exact_add(a, off + tbase + L.xl[wave].tgt[i], off + L.xl[wave].src[i]);
@@ -1129,7 +1265,7 @@ void field_tiles_matrix(FieldArgs a) {
     const uint32_t na0 = a.ev_active[0];
     if (a.count_items && blockIdx.x >= *a.n_items) return;  // the whole workgroup
     __shared__ __align__(16) MatrixLds L;
-    matrix_item<UNIT>(a, it, L, na0);
+    matrix_item<UNIT, false>(a, it, L, na0);
 }
 
 // Persistent form: a fixed grid of workgroups takes the items in list order
@@ -1150,7 +1286,7 @@ void field_queue_matrix(FieldArgs a) {
         const uint32_t i = next;
         __syncthreads();  // every lane has read `next` before lane 0 writes it again
         if (i >= n_items) break;
-        matrix_item<UNIT>(a, a.items[i], L, na0);
+        matrix_item<UNIT, false>(a, a.items[i], L, na0);
     }
 }
 
@@ -1252,6 +1388,18 @@ __global__ __launch_bounds__(kFieldThreads) void field_tiles_f64(FieldArgs a) {
     }
 }
 
+// The near part of the closure's split of Eq. (6): matrix_item with the cutoff.
+// Bound by VALU issue: of 4.1 ms at 1e6 holes, 1.6 go to source groups far from
+// all four target groups, 1.0 to single far blocks, 0.9 to near blocks, 0.1 to
+// staging.  A kernel on difference forms that culled 16-source groups against
+// 64 targets and staged whole tiles took 6.8 ms (the closure step 7.44 against
+// 4.92 ms).
+__global__ __launch_bounds__(kFieldThreads) __attribute__((amdgpu_waves_per_eu(4)))
+void near_matrix(FieldArgs a, const GridParams* gp) {
+    __shared__ __align__(16) MatrixLds L;
+    matrix_item<kTile, true>(a, a.items[blockIdx.x], L, a.ev_active[0], gp);
+}
+
 // ---------------------------------------------------------------------------
 // Near part of the closure's split of Eq. (6): the same sum over the
 // sources closer than a only (r^2 + eps^2 < a^2 + eps^2).  Work items,
@@ -1262,7 +1410,7 @@ __global__ __launch_bounds__(kFieldThreads) void field_tiles_f64(FieldArgs a) {
 // only those are staged and summed, each wave taking only the 16-source
 // groups of a staged tile that come within a of its own 64 targets.  A
 // group entirely within a of every target of the wave skips the per-pair
-// cutoff.
+// cutoff.  For loads below kNearMatrixMin holes (see launch_near).
 // ---------------------------------------------------------------------------
 __global__ __launch_bounds__(kFieldThreads) void near_tiles(FieldArgs a, const GridParams* gp) {
     __shared__ __align__(16) float sh[2][6][kTile];
@@ -1492,10 +1640,19 @@ __global__ __launch_bounds__(kFieldThreads) void near_tiles(FieldArgs a, const G
     }
 }
 
-hipError_t launch_near(const FieldArgs& a, const GridParams* gp, uint32_t n_items,
+// The matrix kernel for loads of at least kNearMatrixMin holes.  Below, the
+// network's launches bound the closure step (0.32 of 0.6 ms at 5e4 holes, where
+// the difference-form kernel costs 0.1 ms per step more), while the FP32
+// rounding of the near sum of a close pair, which the order of summation sets,
+// grows along a run: the smaller loads, which the closure runs for many steps, keep the
+// difference form and its order.
+hipError_t launch_near(const FieldArgs& a, const GridParams* gp, uint32_t n, uint32_t n_items,
                        hipStream_t s) {
     if (n_items == 0) return hipSuccess;
-    near_tiles<<<n_items, kFieldThreads, 0, s>>>(a, gp);
+    if (n >= (uint32_t)kNearMatrixMin)
+        near_matrix<<<n_items, kFieldThreads, 0, s>>>(a, gp);
+    else
+        near_tiles<<<n_items, kFieldThreads, 0, s>>>(a, gp);
     return hipGetLastError();
 }
 
