@@ -801,10 +801,10 @@ int run_network(gccd_ctx* c) {
         a.in_off = in_off;
         a.cin = L.cin;
         a.wpk = c->wpk + c->wpk_off[layer];
-        a.nslice = (L.taps * L.cin + 31) / 32;
         a.ntile = (L.cout + 15) / 16;
         a.taps = L.taps;
         a.n = kActN[in];
+        a.log2n = __builtin_ctz((unsigned)a.n);
         a.cout = L.cout;
         if (out < 0) {
             a.outf = c->fgrid;

@@ -241,7 +241,7 @@ struct ConvArgs {
     const uint16_t* in;
     int32_t in_stride, in_off, cin;
     const uint16_t* wpk;    // weights packed per 32-deep K slice and 16-wide N tile
-    int32_t nslice, ntile, taps, n;
+    int32_t ntile, taps, n, log2n;
     uint16_t* out;          // bf16 output, or NULL
     float* outf;            // FP32 output [n^3][4], or NULL
     int32_t out_stride, out_off, cout;
