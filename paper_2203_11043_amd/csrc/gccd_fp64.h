@@ -77,6 +77,21 @@ GCCD_HD inline double sqrt_pos(double x) {
     return fma(h, fma(-g, g, x), g);
 }
 
+// q^(-3/2) for finite q > 0 with a normal result: from an estimate y of
+// 1/sqrt(q) with e = 1 - q y^2 (about 2^-21, formed with the rounding error of
+// y^2 added back), y^3 (1 - e)^(-3/2) to the second order in e.
+GCCD_HD inline double rsqrt3_pos(double q) {
+#if defined(__HIP_DEVICE_COMPILE__)
+    const double y = __builtin_amdgcn_rsq(q);
+#else
+    const double y = (double)(1.0f / sqrtf((float)q));
+#endif
+    const double t = y * y, dt = fma(y, y, -t);
+    const double e = fma(-q, dt, fma(-q, t, 1.0));
+    const double y3 = y * t;
+    return fma(y3, e * fma(1.875, e, 1.5), y3);
+}
+
 // ln 2 split for exact products k * kLn2Hi with |k| < 2^11 (kLn2Hi has 42
 // significant bits); kLn2Lo = ln 2 - kLn2Hi rounded.
 constexpr double kLn2Hi = 0x1.62e42fefa3800p-1;
