@@ -105,7 +105,9 @@ int gccd_init(const gccd_params* p, void* hip_stream, gccd_ctx** out);
  * that are already resident in device memory): x, y, z are device arrays of n FP64
  * positions in um, copied into the context.  A z beyond the back surface is
  * mirrored back; a z at or below the well is collected at step 0.  Resets the
- * step counter and every statistic.  Synchronises the stream.
+ * step counter and every statistic.  Synchronises the stream.  The context keeps
+ * its buffers for the next load (one over 64 MiB only while it is at most four
+ * times what the load needs) and gives them back in gccd_destroy.
  * GCCD_E_INVALID for n <= 0, n > 2^27 or a NULL pointer; GCCD_E_NOMEM if buffers cannot be allocated.  Non-finite
  * input positions make the next gccd_run return GCCD_E_NONFINITE. */
 int gccd_load(gccd_ctx* c, int64_t n, const double* x, const double* y, const double* z);

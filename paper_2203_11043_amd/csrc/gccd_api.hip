@@ -13,6 +13,7 @@
 #include <new>
 #include <numeric>
 #include <string>
+#include <type_traits>
 #include <vector>
 
 using namespace gccd;
@@ -82,6 +83,16 @@ struct gccd_ctx {
     int max_chunks = 1;
     int max_groups = 1;
 
+    // The load's buffers stay with the context from load to load and are freed
+    // with it: allocating some 25 of them and freeing the last load's took most of a
+    // load's time (gccd_load of 1,000 holes 180 us, now 48; of a million 3.4 ms, now
+    // 0.27; a batch of 400 events 4.1 ms, now 0.40).  reserve below bounds what stays.  `arena` holds every buffer whose
+    // size the number of holes and events fixes; the pointers below point into it.
+    unsigned char* arena = nullptr;
+    size_t arena_cap = 0, part_cap = 0, close_cap = 0, items_bytes = 0;  // allocated bytes
+    size_t host_items_bytes = 0, host_active_bytes = 0, host_tables_bytes = 0;
+    uint32_t* host_tables = nullptr;  // pinned: the event tables of a load
+    int64_t close_n = 0;              // holes the close sums stand ready (zero) for
     double* x = nullptr;
     double* y = nullptr;
     double* z = nullptr;
@@ -230,36 +241,54 @@ void drop_graph(gccd_ctx* c) {
     c->graph = nullptr;
 }
 
-void free_buffers(gccd_ctx* c) {
+// Drops what belongs to the current load; the buffers stay.
+void reset_load(gccd_ctx* c) {
     if (c->side) (void)hipStreamSynchronize(c->side);  // a list may still be sorting
     drop_graph(c);
     c->graph_refused = false;
     c->sorting = false;
-    dfree(c->x);
-    dfree(c->y);
-    dfree(c->z);
-    dfree(c->cstep);
-    dfree(c->ev_of);
-    dfree(c->keys[0]);
-    dfree(c->keys[1]);
-    dfree(c->ukeys[0]);
-    dfree(c->ukeys[1]);
-    for (auto& q : c->ps) dfree(q);
-    dfree(c->tile_box);
+    c->items_cap = 0;
+    c->part_groups = 0;
+    c->close_n = 0;
+    c->loaded = false;
+}
+
+void free_buffers(gccd_ctx* c) {
+    reset_load(c);
+    dfree(c->arena);
     dfree(c->part);
     dfree(c->close);
-    dfree(c->ev_off_d);
-    dfree(c->ev_tile_d);
-    dfree(c->tile_event_d);
-    dfree(c->ev_active_d[0]);
-    dfree(c->ev_active_d[1]);
-    dfree(c->ev_chunks_d);
     dfree(c->items_d);
     hfree(c->host_active);
     hfree(c->host_items);
-    c->items_cap = 0;
-    c->part_groups = 0;
-    c->loaded = false;
+    hfree(c->host_tables);
+    c->arena_cap = c->part_cap = c->close_cap = c->items_bytes = 0;
+    c->host_items_bytes = c->host_active_bytes = c->host_tables_bytes = 0;
+}
+
+// p with at least `need` bytes (contents lost when it moves).  A buffer that is
+// large enough is kept, unless it is over 64 MiB and over four times what is
+// needed: a large load does not hold its memory through the small ones after it.
+constexpr size_t kKeepBytes = (size_t)64 << 20;
+
+template <typename T>
+bool reserve(T*& p, size_t& cap, size_t need, bool pinned = false) {
+    need = std::max<size_t>(need, 256);
+    if (p && cap >= need && !(cap > kKeepBytes && cap / 4 > need)) return true;
+    if (pinned)
+        hfree(p);
+    else
+        dfree(p);
+    cap = 0;
+    void* q = nullptr;
+    const hipError_t e = pinned ? hipHostMalloc(&q, need) : hipMalloc(&q, need);
+    if (e != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    p = static_cast<T*>(q);
+    cap = need;
+    return true;
 }
 
 void free_closure(gccd_ctx* c) {
@@ -478,12 +507,20 @@ int build_items(gccd_ctx* c, const uint32_t* bound) {
     return GCCD_OK;
 }
 
+// The work items' buffers, on the device and pinned.
+bool reserve_items(gccd_ctx* c, size_t items) {
+    const size_t bytes = items * sizeof(FieldItem);
+    return reserve(c->items_d, c->items_bytes, bytes) &&
+           reserve(c->host_items, c->host_items_bytes, bytes, true);
+}
+
+bool reserve_part(gccd_ctx* c, int groups) {
+    return reserve(c->part, c->part_cap, (size_t)groups * 3 * (size_t)c->n * sizeof(float));
+}
+
 // Partial-sum buffer and work-item capacity for the current chunk choice.
-int size_chunk_buffers(gccd_ctx* c) {
+int reserve_chunk_buffers(gccd_ctx* c) {
     drop_graph(c);
-    dfree(c->part);
-    dfree(c->items_d);
-    hfree(c->host_items);
     size_t items = 0;
     for (uint32_t e = 0; e < c->n_events; ++e) {
         const uint64_t ne = c->off_h[e + 1] - c->off_h[e];
@@ -494,27 +531,28 @@ int size_chunk_buffers(gccd_ctx* c) {
     // the partial sums are only needed with repulsion on (a field call on a
     // load without it allocates them then: ensure_part)
     c->part_groups = c->p.coulomb ? c->max_groups : 0;
-    if ((c->p.coulomb &&
-         hipMalloc(&c->part, (size_t)c->max_groups * 3 * (size_t)c->n * sizeof(float)) !=
-             hipSuccess) ||
-        hipMalloc(&c->items_d, c->items_cap * sizeof(FieldItem)) != hipSuccess ||
-        hipHostMalloc((void**)&c->host_items, c->items_cap * sizeof(FieldItem)) != hipSuccess)
+    if ((c->p.coulomb && !reserve_part(c, c->max_groups)) || !reserve_items(c, c->items_cap))
         return fail(c, GCCD_E_NOMEM, "device allocation of the field buffers failed");
+    return GCCD_OK;
+}
+
+int size_chunk_buffers(gccd_ctx* c) {
+    if (int r = reserve_chunk_buffers(c); r != GCCD_OK) return r;
     GCCD_HIP(c, hipMemcpyAsync(c->ev_chunks_d, c->groups_h.data(), c->n_events * sizeof(int32_t),
                                hipMemcpyHostToDevice, c->stream));
     GCCD_HIP(c, hipStreamSynchronize(c->stream));
     return GCCD_OK;
 }
 
-// The close-pair sums of the default precision: allocated with the partial
-// sums, zero between launches (every consumer of a field launch clears the
-// slots it reads).
+// The close-pair sums of the default precision: zero between launches (every
+// consumer of a field launch clears the slots it reads).
 int ensure_close(gccd_ctx* c) {
-    if (c->close) return GCCD_OK;
+    if (c->close_n == c->n) return GCCD_OK;
     const size_t words = 3 * (size_t)c->n;
-    if (hipMalloc(&c->close, words * sizeof(unsigned long long)) != hipSuccess)
+    if (!reserve(c->close, c->close_cap, words * sizeof(unsigned long long)))
         return fail(c, GCCD_E_NOMEM, "close-pair sum allocation failed");
     GCCD_HIP(c, launch_fill_u32(reinterpret_cast<uint32_t*>(c->close), 2 * words, 0u, c->stream));
+    c->close_n = c->n;
     return GCCD_OK;
 }
 
@@ -522,9 +560,7 @@ int ensure_part(gccd_ctx* c) {
     if (int r = ensure_close(c); r != GCCD_OK) return r;
     if (c->part_groups >= c->max_groups) return GCCD_OK;
     drop_graph(c);
-    dfree(c->part);
-    if (hipMalloc(&c->part, (size_t)c->max_groups * 3 * (size_t)c->n * sizeof(float)) !=
-        hipSuccess)
+    if (!reserve_part(c, c->max_groups))
         return fail(c, GCCD_E_NOMEM, "partial-sum allocation failed");
     c->part_groups = c->max_groups;
     return GCCD_OK;
@@ -737,18 +773,14 @@ int ensure_closure_capacity(gccd_ctx* c) {
     const int groups = c->near_chunks + 1;
     if (groups > c->part_groups) {
         drop_graph(c);  // the captured steps name the old buffers
-        dfree(c->part);
-        if (hipMalloc(&c->part, (size_t)groups * 3 * (size_t)c->n * sizeof(float)) != hipSuccess)
+        if (!reserve_part(c, groups))
             return fail(c, GCCD_E_NOMEM, "closure partial-sum allocation failed");
         c->part_groups = groups;
     }
     const size_t items = (((size_t)c->n + kFieldThreads - 1) / kFieldThreads) * c->near_chunks;
     if (items > c->items_cap) {
         drop_graph(c);
-        dfree(c->items_d);
-        hfree(c->host_items);
-        if (hipMalloc(&c->items_d, items * sizeof(FieldItem)) != hipSuccess ||
-            hipHostMalloc((void**)&c->host_items, items * sizeof(FieldItem)) != hipSuccess)
+        if (!reserve_items(c, items))
             return fail(c, GCCD_E_NOMEM, "closure work-item allocation failed");
         c->items_cap = items;
     }
@@ -866,6 +898,79 @@ int closure_field(gccd_ctx* c, bool targets_all, uint32_t nt, bool with_net) {
 }  // namespace
 
 namespace {
+
+// Whether a kernel of this device may read the count doubles at p: aligned device
+// memory of this device, all inside its allocation.  Other memory that a copy
+// reaches (a peer's, the host's) is copied first, and a range past the end
+// is refused by that copy.
+bool kernel_readable(const double* p, size_t count) {
+    if ((uintptr_t)p % sizeof(double) != 0) return false;
+    int dev = -1;
+    hipPointerAttribute_t at{};
+    hipDeviceptr_t base = nullptr;
+    size_t size = 0;
+    if (hipGetDevice(&dev) != hipSuccess || hipPointerGetAttributes(&at, p) != hipSuccess ||
+        at.type != hipMemoryTypeDevice || at.device != dev ||
+        hipMemGetAddressRange(&base, &size, (hipDeviceptr_t)p) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    const size_t at_byte = (size_t)((const char*)p - (const char*)base);
+    return at_byte <= size && count * sizeof(double) <= size - at_byte;
+}
+
+// Where launch_load reads coordinate p: p itself or, copied there on stream s, `own`.
+hipError_t load_source(const double* p, double* own, size_t count, const double** from,
+                       hipStream_t s) {
+    *from = p;
+    if (kernel_readable(p, count)) return hipSuccess;
+    *from = own;
+    return hipMemcpyAsync(own, p, count * sizeof(double), hipMemcpyDeviceToDevice, s);
+}
+
+// The buffers of the load described by c->n, n_events, n_tiles and the chunk
+// choice; *words: 32-bit words of the event tables, which start at ev_off_d
+// (event offsets, tile offsets, chunk groups, tile events).
+int load_buffers(gccd_ctx* c, size_t* words) {
+    const size_t n = (size_t)c->n, E = c->n_events, T = std::max<uint32_t>(c->n_tiles, 1);
+    *words = 2 * (E + 1) + E + T;
+    unsigned char* base = nullptr;
+    size_t used = 0;
+    auto take = [&](auto*& p, size_t count) {
+        p = reinterpret_cast<std::remove_reference_t<decltype(p)>>(base + used);
+        used += (count * sizeof(*p) + 255) & ~(size_t)255;
+    };
+    for (int pass = 0; pass < 2; ++pass) {  // sizes, then addresses
+        used = 0;
+        take(c->x, n);
+        take(c->y, n);
+        take(c->z, n);
+        take(c->cstep, n);
+        take(c->ev_of, n);
+        take(c->keys[0], n);
+        take(c->keys[1], n);
+        take(c->ukeys[0], n);
+        take(c->ukeys[1], n);
+        for (auto& q : c->ps) take(q, n);
+        take(c->tile_box, kBoxRows * T);
+        take(c->ev_off_d, *words);
+        c->ev_tile_d = c->ev_off_d + (E + 1);
+        c->ev_chunks_d = reinterpret_cast<int32_t*>(c->ev_tile_d + (E + 1));
+        c->tile_event_d = reinterpret_cast<uint32_t*>(c->ev_chunks_d + E);
+        take(c->ev_active_d[0], E);
+        take(c->ev_active_d[1], E);
+        if (pass == 0) {
+            if (!reserve(c->arena, c->arena_cap, used) ||
+                !reserve(c->host_active, c->host_active_bytes, E * sizeof(uint32_t), true) ||
+                !reserve(c->host_tables, c->host_tables_bytes, *words * sizeof(uint32_t), true) ||
+                (c->p.coulomb &&
+                 !reserve(c->close, c->close_cap, 3 * n * sizeof(unsigned long long))))
+                return fail(c, GCCD_E_NOMEM, "gccd_load_events: device allocation failed");
+            base = c->arena;
+        }
+    }
+    return reserve_chunk_buffers(c);
+}
 
 // Captures kPoll steps issued by `issue` (step offsets 0 .. kPoll-1) as a
 // graph, recorded on a stream of the context's own and replayed later on the
@@ -1033,7 +1138,7 @@ int gccd_load_events(gccd_ctx* c, int32_t n_events, const int64_t* offsets, cons
                     "gccd_load_events: events x largest event exceed 2^27 key space");
 
     GCCD_HIP(c, hipStreamSynchronize(c->stream));
-    free_buffers(c);
+    reset_load(c);
     c->n = n;
     c->n_events = (uint32_t)n_events;
     c->kl = kl;
@@ -1045,9 +1150,6 @@ int gccd_load_events(gccd_ctx* c, int32_t n_events, const int64_t* offsets, cons
     for (int32_t e = 0; e < n_events; ++e)
         c->tile_h[e + 1] = c->tile_h[e] + (c->off_h[e + 1] - c->off_h[e] + kTile - 1) / kTile;
     c->n_tiles = c->tile_h[n_events];
-    std::vector<uint32_t> tile_event(std::max<uint32_t>(c->n_tiles, 1), 0);
-    for (int32_t e = 0; e < n_events; ++e)
-        for (uint32_t t = c->tile_h[e]; t < c->tile_h[e + 1]; ++t) tile_event[t] = (uint32_t)e;
     c->order_h.resize(n_events);
     std::iota(c->order_h.begin(), c->order_h.end(), 0u);
     std::stable_sort(c->order_h.begin(), c->order_h.end(), [&](uint32_t a, uint32_t b) {
@@ -1055,67 +1157,62 @@ int gccd_load_events(gccd_ctx* c, int32_t n_events, const int64_t* offsets, cons
     });
     choose_chunks(c);
 
-    const size_t d = (size_t)n * sizeof(double);
-    const size_t E = (size_t)n_events;
-    bool ok = hipMalloc(&c->x, d) == hipSuccess && hipMalloc(&c->y, d) == hipSuccess &&
-              hipMalloc(&c->z, d) == hipSuccess &&
-              hipMalloc(&c->cstep, (size_t)n * sizeof(int32_t)) == hipSuccess &&
-              hipMalloc(&c->ev_of, (size_t)n * sizeof(uint32_t)) == hipSuccess &&
-              hipMalloc(&c->keys[0], (size_t)n * sizeof(uint64_t)) == hipSuccess &&
-              hipMalloc(&c->keys[1], (size_t)n * sizeof(uint64_t)) == hipSuccess &&
-              hipMalloc(&c->ukeys[0], (size_t)n * sizeof(uint64_t)) == hipSuccess &&
-              hipMalloc(&c->ukeys[1], (size_t)n * sizeof(uint64_t)) == hipSuccess &&
-              hipMalloc(&c->ps[0], d) == hipSuccess && hipMalloc(&c->ps[1], d) == hipSuccess &&
-              hipMalloc(&c->ps[2], d) == hipSuccess &&
-              hipMalloc(&c->tile_box, kBoxRows * sizeof(double) * tile_event.size()) ==
-                  hipSuccess &&
-              hipMalloc(&c->ev_off_d, (E + 1) * sizeof(uint32_t)) == hipSuccess &&
-              hipMalloc(&c->ev_tile_d, (E + 1) * sizeof(uint32_t)) == hipSuccess &&
-              hipMalloc(&c->tile_event_d, tile_event.size() * sizeof(uint32_t)) == hipSuccess &&
-              hipMalloc(&c->ev_active_d[0], E * sizeof(uint32_t)) == hipSuccess &&
-              hipMalloc(&c->ev_active_d[1], E * sizeof(uint32_t)) == hipSuccess &&
-              hipMalloc(&c->ev_chunks_d, E * sizeof(int32_t)) == hipSuccess &&
-              hipHostMalloc((void**)&c->host_active, E * sizeof(uint32_t)) == hipSuccess;
-    if (!ok) {
+    // Buffers.  A first try keeps what earlier loads left; if memory runs out
+    // all of it is given back and only what this load needs is asked for.
+    size_t words = 0;
+    int r = load_buffers(c, &words);
+    if (r == GCCD_E_NOMEM) {
         free_buffers(c);
-        return fail(c, GCCD_E_NOMEM, "gccd_load_events: device allocation failed");
+        r = load_buffers(c, &words);
     }
-    GCCD_HIP(c, hipMemcpyAsync(c->ev_off_d, c->off_h.data(), (E + 1) * sizeof(uint32_t),
-                               hipMemcpyHostToDevice, c->stream));
-    GCCD_HIP(c, hipMemcpyAsync(c->ev_tile_d, c->tile_h.data(), (E + 1) * sizeof(uint32_t),
-                               hipMemcpyHostToDevice, c->stream));
-    GCCD_HIP(c, hipMemcpyAsync(c->tile_event_d, tile_event.data(),
-                               tile_event.size() * sizeof(uint32_t), hipMemcpyHostToDevice,
-                               c->stream));
-    {
-        int r = c->p.coulomb ? ensure_close(c) : GCCD_OK;
-        if (r == GCCD_OK) r = size_chunk_buffers(c);  // synchronises: tile_event may go out of scope
-        if (r != GCCD_OK) {
-            free_buffers(c);
-            return r;
-        }
+    if (r != GCCD_OK) {
+        free_buffers(c);
+        return r;
     }
 
-    GCCD_HIP(c, hipMemcpyAsync(c->x, x, d, hipMemcpyDeviceToDevice, c->stream));
-    GCCD_HIP(c, hipMemcpyAsync(c->y, y, d, hipMemcpyDeviceToDevice, c->stream));
-    GCCD_HIP(c, hipMemcpyAsync(c->z, z, d, hipMemcpyDeviceToDevice, c->stream));
-    GCCD_HIP(c, launch_fill_u32(c->meta, kMetaWords, 0u, c->stream));
-    GCCD_HIP(c, launch_load(c->z, c->cstep, c->ev_off_d, c->ev_of, c->n_events, (uint32_t)n,
-                            c->p.thickness_um, c->p.well_z_um, c->meta + kMetaCount, c->stream));
+    // the event tables, in the order load_buffers lays them out
+    const size_t E = (size_t)n_events;
+    uint32_t* t = c->host_tables;
+    t = std::copy(c->off_h.begin(), c->off_h.end(), t);
+    t = std::copy(c->tile_h.begin(), c->tile_h.end(), t);
+    t = std::copy(c->groups_h.begin(), c->groups_h.end(), t);
+    for (size_t e = 0; e < E; ++e)
+        t = std::fill_n(t, c->tile_h[e + 1] - c->tile_h[e], (uint32_t)e);
+    GCCD_HIP(c, hipMemcpyAsync(c->ev_off_d, c->host_tables, words * sizeof(uint32_t),
+                               hipMemcpyHostToDevice, c->stream));
     c->list_mode = c->p.coulomb != 0;
     c->cur = 0;
     c->u = 0;
     c->pipe_mode = -1;
+    GCCD_HIP(c, launch_fill_u32(c->meta, kMetaWords, 0u, c->stream));
+    LoadArgs la{};
+    GCCD_HIP(c, load_source(x, c->x, (size_t)n, &la.sx, c->stream));
+    GCCD_HIP(c, load_source(y, c->y, (size_t)n, &la.sy, c->stream));
+    GCCD_HIP(c, load_source(z, c->z, (size_t)n, &la.sz, c->stream));
+    la.x = c->x;
+    la.y = c->y;
+    la.z = c->z;
+    la.cstep = c->cstep;
+    la.ev_off = c->ev_off_d;
+    la.ev_of = c->ev_of;
+    la.n_events = c->n_events;
+    la.n = (uint32_t)n;
+    la.thickness = c->p.thickness_um;
+    la.z_well = c->p.well_z_um;
+    la.cnt = c->meta + kMetaCount;
+    la.kl = c->kl;
     if (c->list_mode) {
-        GCCD_HIP(c, launch_make_keys(c->x, c->y, c->z, c->cstep, c->ev_of, c->ev_off_d,
-                                     (uint32_t)n, c->kl, c->ukeys[0], c->stream));
-        int r = finish_list(c, c->ukeys[0]);
+        la.keys = c->ukeys[0];
+        la.close = c->close;
+        c->close_n = n;
+    }
+    GCCD_HIP(c, launch_load(la, c->stream));
+    if (c->list_mode) {
+        r = finish_list(c, c->ukeys[0]);
         if (r != GCCD_OK) return r;
     }
-    {
-        int r = read_counts(c);
-        if (r != GCCD_OK) return r;
-    }
+    r = read_counts(c);
+    if (r != GCCD_OK) return r;
     c->n_active = c->host_meta[kMetaCount];
     c->step = 0;
     c->loaded = true;
@@ -1898,7 +1995,6 @@ int gccd_field_noalloc(const gccd_params* p, int64_t n, const double* x, const d
     uint32_t* tile_event = sched + kSchedWords;  // [tiles]
 
     const KeyLayout kl{std::max<uint32_t>(1, bits_for((uint64_t)nn)), 0u};
-    const size_t dbytes = (size_t)nn * sizeof(double);
 #define NA_HIP(call)                                   \
     do {                                               \
         if ((call) != hipSuccess) {                    \
@@ -1909,17 +2005,35 @@ int gccd_field_noalloc(const gccd_params* p, int64_t n, const double* x, const d
     // meta and sched are contiguous: both zeroed
     NA_HIP(launch_noalloc_setup(nn, (uint32_t)tiles, g, tail, split, (uint32_t)blocks, ev_off,
                                 ev_tile, ev_chunks, tile_event, meta, kMetaWords + kSchedWords,
-                                items, close, st));
-    NA_HIP(hipMemcpyAsync(cx, x, dbytes, hipMemcpyDeviceToDevice, st));
-    NA_HIP(hipMemcpyAsync(cy, y, dbytes, hipMemcpyDeviceToDevice, st));
-    NA_HIP(hipMemcpyAsync(cz, z, dbytes, hipMemcpyDeviceToDevice, st));
-    NA_HIP(launch_load(cz, cstep, ev_off, ev_of, 1u, nn, p->thickness_um, p->well_z_um,
-                       meta + kMetaCount, st));
-    NA_HIP(launch_make_keys(cx, cy, cz, cstep, ev_of, ev_off, nn, kl, keys1, st));
+                                items, st));
+    LoadArgs la{};
+    NA_HIP(load_source(x, cx, nn, &la.sx, st));
+    NA_HIP(load_source(y, cy, nn, &la.sy, st));
+    NA_HIP(load_source(z, cz, nn, &la.sz, st));
+    la.x = cx;
+    la.y = cy;
+    la.z = cz;
+    la.cstep = cstep;
+    la.ev_off = ev_off;
+    la.ev_of = ev_of;
+    la.n_events = 1u;
+    la.n = nn;
+    la.thickness = p->thickness_um;
+    la.z_well = p->well_z_um;
+    la.cnt = meta + kMetaCount;
+    la.kl = kl;
+    la.keys = keys1;
+    la.close = close;
+    NA_HIP(launch_load(la, st));
     NA_HIP(sort_keys(keys1, keys0, nn, st));
-    NA_HIP(launch_count(keys0, ev_off, 1u, kl, ev_active, st));
-    NA_HIP(launch_gather(keys0, ev_off, ev_tile, tile_event, ev_active, p->collected_are_sources,
-                         (uint32_t)tiles, kl, cx, cy, cz, px, py, pz, box, (uint32_t)tiles, st));
+    if (p->collected_are_sources) {  // the gather needs no count: one launch
+        NA_HIP(launch_gather_count(keys0, ev_off, ev_tile, tile_event, 1u, (uint32_t)tiles, kl, cx,
+                                   cy, cz, px, py, pz, box, (uint32_t)tiles, ev_active, st));
+    } else {
+        NA_HIP(launch_count(keys0, ev_off, 1u, kl, ev_active, st));
+        NA_HIP(launch_gather(keys0, ev_off, ev_tile, tile_event, ev_active, 0, (uint32_t)tiles, kl,
+                             cx, cy, cz, px, py, pz, box, (uint32_t)tiles, st));
+    }
     FieldArgs fa{};
     fa.items = items;
     fa.ev_off = ev_off;

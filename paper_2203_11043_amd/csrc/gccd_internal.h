@@ -158,6 +158,28 @@ struct StepArgs {
     uint32_t box_stride;
 };
 
+// What taking in a load does per carrier, in one pass: the caller's positions
+// copied with the back-surface mirror, collection at step 0, the event, and (where
+// not NULL) the unsorted list key and zeroed close sums.
+struct LoadArgs {
+    const double* sx;  // the caller's positions
+    const double* sy;
+    const double* sz;
+    double* x;
+    double* y;
+    double* z;
+    int32_t* cstep;
+    const uint32_t* ev_off;  // [E+1]
+    uint32_t* ev_of;
+    uint32_t n_events;
+    uint32_t n;
+    double thickness, z_well;
+    uint32_t* cnt;  // travelling holes, added to
+    KeyLayout kl;
+    uint64_t* keys;
+    unsigned long long* close;  // [3][n]
+};
+
 // precision: a GCCD_PRECISION_* mode
 int field_slots_per_cu(int tpt, int precision);
 int field_queue_slots_per_cu();
@@ -169,9 +191,7 @@ int field_queue_slots_per_cu();
 hipError_t launch_field(const FieldArgs& a, int tpt, int precision, uint32_t n_items,
                         uint32_t queue_grid, hipStream_t s, uint32_t grid_cap = 0);
 hipError_t launch_step(const StepArgs& a, uint32_t n_slots, hipStream_t s);
-hipError_t launch_load(double* z, int32_t* cstep, const uint32_t* ev_off, uint32_t* ev_of,
-                       uint32_t n_events, uint32_t n, double thickness, double z_well,
-                       uint32_t* cnt, hipStream_t s);
+hipError_t launch_load(const LoadArgs& a, hipStream_t s);
 hipError_t launch_make_keys(const double* x, const double* y, const double* z,
                             const int32_t* cstep, const uint32_t* ev_of, const uint32_t* ev_off,
                             uint32_t n, KeyLayout kl, uint64_t* keys, hipStream_t s);
@@ -199,12 +219,12 @@ hipError_t launch_field_finish(const float* part, uint32_t pstride, const int32_
                                KeyLayout kl, uint32_t n, double K, unsigned long long* close,
                                double close_unit, double* ex, double* ey, double* ez,
                                hipStream_t s);
-// gccd_field_noalloc: event tables, zeroed words and close sums, work items.
+// gccd_field_noalloc: event tables, zeroed words, work items.
 hipError_t launch_noalloc_setup(uint32_t n, uint32_t tiles, int32_t g, int32_t tail,
                                 uint32_t split, uint32_t blocks, uint32_t* ev_off,
                                 uint32_t* ev_tile, int32_t* ev_chunks, uint32_t* tile_event,
                                 uint32_t* words, uint32_t n_words, FieldItem* items,
-                                unsigned long long* close, hipStream_t s);
+                                hipStream_t s);
 hipError_t launch_image(const double* x, const double* y, const int32_t* cstep,
                         const uint32_t* ev_of, uint32_t n, int per_event, double x0, double y0,
                         double pitch, int32_t nx, int32_t ny, uint32_t* counts,

@@ -3,7 +3,7 @@
 //   field_tiles_matrix, field_tiles -- Eq. (6), softened all-pairs Coulomb field
 //                    (the O(N^2) part)
 //   step_update   -- Eqs. (1)-(4) and the z check of Sec. III.B, fused per carrier
-//   load_prepare  -- load-time boundary handling
+//   load_prepare  -- a load's positions taken in, with its boundary handling
 //   make_keys, count_active, gather_tiles -- the spatially sorted carrier list
 //   image_bin     -- 2D histogram of collected holes (Sec. V.A)
 // Several independent events (clouds) can share one launch; every kernel
@@ -2517,28 +2517,41 @@ hipError_t launch_step(const StepArgs& a, uint32_t n_slots, hipStream_t s) {
 }
 
 // ---------------------------------------------------------------------------
-// Load-time boundary handling: mirror z beyond the back surface, collect
-// holes at or below the well (collection step 0), record each carrier's
-// event, count the travelling ones.
+// Taking in a load: the caller's positions copied with z mirrored at the back
+// surface, holes at or below the well collected (collection step 0), each
+// carrier's event recorded and the travelling ones counted; with repulsion
+// also the unsorted list key and the zeroed close sums (LoadArgs).  One pass
+// at HBM rate in place of three copies, the boundary pass, the key pass and a
+// fill: per carrier 24 B read and 32 B written, 64 B with repulsion (before:
+// 128 and 176 B in all).  gccd_load of 8 million holes without repulsion takes
+// 141 us in all, most of it this kernel (before, with the allocations: 4.1 ms).
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(kStepThreads) void load_prepare(double* z, int32_t* cstep,
-                                                             const uint32_t* ev_off,
-                                                             uint32_t* ev_of, uint32_t n_events,
-                                                             uint32_t n, double thickness,
-                                                             double z_well, uint32_t* cnt) {
+template <bool LIST>
+__global__ __launch_bounds__(kStepThreads) void load_prepare(LoadArgs a) {
     const int lane = threadIdx.x & 63;
     uint32_t kept = 0;  // this wave's travelling holes (wave-uniform)
-    for (uint32_t base = blockIdx.x * kStepThreads; base < n; base += gridDim.x * kStepThreads) {
+    for (uint32_t base = blockIdx.x * kStepThreads; base < a.n;
+         base += gridDim.x * kStepThreads) {
         const uint32_t j = base + threadIdx.x;
         bool keep = false;
-        if (j < n) {
-            double zz = z[j];
-            if (zz > thickness) zz = 2.0 * thickness - zz;
-            z[j] = zz;
-            const bool collected = zz <= z_well;
-            cstep[j] = collected ? 0 : -1;
+        if (j < a.n) {
+            const double xx = a.sx[j], yy = a.sy[j];
+            double zz = a.sz[j];
+            if (zz > a.thickness) zz = 2.0 * a.thickness - zz;
+            a.x[j] = xx;
+            a.y[j] = yy;
+            a.z[j] = zz;
+            const bool collected = zz <= a.z_well;
+            a.cstep[j] = collected ? 0 : -1;
             keep = !collected;
-            ev_of[j] = event_of(ev_off, n_events, j);
+            const uint32_t e = event_of(a.ev_off, a.n_events, j);
+            a.ev_of[j] = e;
+            if constexpr (LIST) {
+                a.keys[j] = make_key(e, collected, xx, yy, zz, j - a.ev_off[e], a.kl);
+                a.close[j] = 0ull;
+                a.close[(size_t)a.n + j] = 0ull;
+                a.close[2 * (size_t)a.n + j] = 0ull;
+            }
         }
         kept += (uint32_t)__popcll(__ballot(keep));
     }
@@ -2549,15 +2562,16 @@ __global__ __launch_bounds__(kStepThreads) void load_prepare(double* z, int32_t*
     if (threadIdx.x == 0) {
         uint32_t t = 0;
         for (int w = 0; w < kStepThreads / 64; ++w) t += wave_kept[w];
-        if (t) atomicAdd(cnt, t);
+        if (t) atomicAdd(a.cnt, t);
     }
 }
 
-hipError_t launch_load(double* z, int32_t* cstep, const uint32_t* ev_off, uint32_t* ev_of,
-                       uint32_t n_events, uint32_t n, double thickness, double z_well,
-                       uint32_t* cnt, hipStream_t s) {
-    load_prepare<<<grid_for(n, kStepThreads, 8192), kStepThreads, 0, s>>>(
-        z, cstep, ev_off, ev_of, n_events, n, thickness, z_well, cnt);
+hipError_t launch_load(const LoadArgs& a, hipStream_t s) {
+    const auto grid = grid_for(a.n, kStepThreads, 8192);
+    if (a.keys)
+        load_prepare<true><<<grid, kStepThreads, 0, s>>>(a);
+    else
+        load_prepare<false><<<grid, kStepThreads, 0, s>>>(a);
     return hipGetLastError();
 }
 
@@ -2626,12 +2640,12 @@ hipError_t launch_field_finish(const float* part, uint32_t pstride, const int32_
 // The per-call state of gccd_field_noalloc (one event of n holes, t tiles,
 // `blocks` target blocks, g chunks of which the last `tail` form the tail
 // layer from tile `split`), written in its scratch memory: event tables,
-// zeroed counters and close-pair sums, and the work items in the order the
-// context's item builder lists them for one event.
+// zeroed counters, and the work items in the order the context's item builder
+// lists them for one event.
 __global__ void noalloc_setup(uint32_t n, uint32_t tiles, int32_t g, int32_t tail, uint32_t split,
                               uint32_t blocks, uint32_t* ev_off, uint32_t* ev_tile,
                               int32_t* ev_chunks, uint32_t* tile_event, uint32_t* words,
-                              uint32_t n_words, FieldItem* items, unsigned long long* close) {
+                              uint32_t n_words, FieldItem* items) {
     const uint64_t i0 = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
     const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
     if (i0 == 0) {
@@ -2643,7 +2657,6 @@ __global__ void noalloc_setup(uint32_t n, uint32_t tiles, int32_t g, int32_t tai
     }
     for (uint64_t i = i0; i < n_words; i += stride) words[i] = 0u;
     for (uint64_t i = i0; i < tiles; i += stride) tile_event[i] = 0u;
-    for (uint64_t i = i0; i < 3ull * n; i += stride) close[i] = 0ull;
     const uint32_t s1 = (uint32_t)(g - tail), s2 = (uint32_t)tail;
     const uint64_t first = (uint64_t)blocks * s1, total = first + (uint64_t)blocks * s2;
     for (uint64_t k = i0; k < total; k += stride) {
@@ -2675,10 +2688,10 @@ hipError_t launch_noalloc_setup(uint32_t n, uint32_t tiles, int32_t g, int32_t t
                                 uint32_t split, uint32_t blocks, uint32_t* ev_off,
                                 uint32_t* ev_tile, int32_t* ev_chunks, uint32_t* tile_event,
                                 uint32_t* words, uint32_t n_words, FieldItem* items,
-                                unsigned long long* close, hipStream_t s) {
-    noalloc_setup<<<grid_for(3ull * n, 256, 1024), 256, 0, s>>>(
+                                hipStream_t s) {
+    noalloc_setup<<<grid_for((uint64_t)blocks * g, 256, 1024), 256, 0, s>>>(
         n, tiles, g, tail, split, blocks, ev_off, ev_tile, ev_chunks, tile_event, words, n_words,
-        items, close);
+        items);
     return hipGetLastError();
 }
 
