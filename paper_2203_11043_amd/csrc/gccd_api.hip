@@ -27,6 +27,21 @@ constexpr double kEps0 = 8.8541878128e-12;
 constexpr double kPi = 3.14159265358979323846;
 
 constexpr int kPoll = 32;                       // steps between host reads of the counts
+// Steps that one order of a serial list serves (every hole a source).  The order
+// sets only which holes share blocks and boxes, never which are summed; keeping
+// it saves the sort (24 us with the step of a load of 1,000 holes, 31 us of
+// launches after it at 10,000) and costs the Eq. (6) kernel some of its far
+// blocks as holes move apart.  us per step, order kept 1, 4, 8, 16, 32 steps:
+//   1,000 holes  37.3 23.9 21.8 19.2 20.4     30,000  274 245 248 267 308
+//   10,007       94.9 67.9 64.7 64.6 69.9     70,000  1054 1041 1071 1152 1146
+// With longer steps holes part sooner.  Steps of 160 and 1000 ps, order kept 1, 4
+// and 16 steps: 30,000 holes 287 254 291 and 316 265 332, 70,000 holes 996 1022
+// 1286 and 738 833 1273; so such loads keep no order above 40 ps.
+constexpr int kKeepSmall = 16, kKeepLarge = 4;
+constexpr double kKeepPairs = 4e8;              // pairs of the load's events: the line
+constexpr double kKeepLongPairs = 2e9, kKeepLongPs = 40.0;
+static_assert(kPoll % kKeepSmall == 0 && kPoll % kKeepLarge == 0,
+              "stretches start with a fresh list");
 // Pair interactions per step from which the exact path pipelines its list
 // (sorts the next step's keys on a second stream while the field runs).
 // Below it the field launch is too short to hide the sort, and the sort's
@@ -110,6 +125,10 @@ struct gccd_ctx {
     uint64_t* ukeys[2] = {nullptr, nullptr};
     int cur = 0;
     int u = 0;
+    // A serial list keeps its order for some steps (kKeepSmall): kept, the current
+    // list is that of an earlier step's positions; gathered, ps and tile_box hold
+    // the current positions in its order.
+    bool kept = false, gathered = false;
     bool sorting = false;            // the side stream sorts into keys[cur ^ 1]
     hipStream_t side = nullptr;      // default priority, like every stream here
     hipEvent_t ev_keys = nullptr;    // the step kernel has written ukeys
@@ -247,6 +266,7 @@ void reset_load(gccd_ctx* c) {
     drop_graph(c);
     c->graph_refused = false;
     c->sorting = false;
+    c->kept = false;
     c->items_cap = 0;
     c->part_groups = 0;
     c->close_n = 0;
@@ -690,6 +710,30 @@ int settle(gccd_ctx* c) {
     c->sorting = false;
     return gather(c);
 }
+
+// The list of the current positions, for a call between runs.  Without repulsion
+// none is kept, so it is built; a pipelined list is taken as it stands.  A kept
+// one is sorted into the buffers of the other list, which is the current one
+// until the view ends, so that the run goes on with its own.
+struct ListView {
+    gccd_ctx* c;
+    bool other = false;
+    explicit ListView(gccd_ctx* ctx) : c(ctx) {}
+    ~ListView() {
+        if (other) c->cur ^= 1;
+    }
+    int make() {
+        if (c->list_mode && !c->kept) return gather(c);
+        GCCD_HIP(c, launch_make_keys(c->x, c->y, c->z, c->cstep, c->ev_of, c->ev_off_d,
+                                     (uint32_t)c->n, c->kl, c->ukeys[c->u], c->stream));
+        if (c->list_mode) {
+            other = true;
+            c->cur ^= 1;
+            c->gathered = false;
+        }
+        return finish_list(c, c->ukeys[c->u]);
+    }
+};
 
 int read_counts(gccd_ctx* c) {
     GCCD_HIP(c, hipMemcpyAsync(c->host_meta, c->meta, kMetaWords * sizeof(uint32_t),
@@ -1358,13 +1402,8 @@ int gccd_closure_parts(gccd_ctx* c, double* near_x, double* near_y, double* near
     GCCD_HIP(c, hipStreamSynchronize(c->stream));
     int r = ensure_closure_buffers(c);
     if (r != GCCD_OK) return r;
-    if (!c->list_mode) {
-        GCCD_HIP(c, launch_make_keys(c->x, c->y, c->z, c->cstep, c->ev_of, c->ev_off_d, n, c->kl,
-                                     c->ukeys[0], c->stream));
-        r = finish_list(c, c->ukeys[0]);
-    } else {
-        r = gather(c);  // the current positions in the order of the current list
-    }
+    ListView list(c);
+    r = list.make();
     if (r != GCCD_OK) return r;
     choose_near_chunks(c);
     r = ensure_closure_capacity(c);
@@ -1541,8 +1580,8 @@ int gccd_run(gccd_ctx* c, double dt_ps, int64_t max_steps, int64_t* steps_done,
     sa.stats = reinterpret_cast<unsigned long long*>(c->meta + kMetaStats);
     sa.misc = reinterpret_cast<int32_t*>(c->meta + kMetaFlag);
 
-    // A small load's step kernel rebuilds the list itself (its last
-    // workgroup sorts, counts and gathers: two launches per step).  Other
+    // A small load's step kernel rebuilds the list itself where the step sorts
+    // (its last workgroup sorts, counts and gathers: two launches per step).  Other
     // exact steps with every hole a source are pipelined (see gccd_ctx::keys)
     // while their pair work hides the sort (kPipeMinPairs); the others need
     // the list of the positions they run over.  The choice is made at load
@@ -1566,17 +1605,36 @@ int gccd_run(gccd_ctx* c, double dt_ps, int64_t max_steps, int64_t* steps_done,
     else if (c->pipe_mode < 0 || step0 % kPoll == 0)
         c->pipe_mode = decide_pipe();
     bool pipelined = c->pipe_mode == 1;
-    if (fused) {
-        sa.arrive = c->sched + kSchedArrive;
-        sa.n_events = c->n_events;
-        sa.ev_tile = c->ev_tile_d;
-        sa.tile_event = c->tile_event_d;
-        sa.n_tiles = c->n_tiles;
-        sa.px = c->ps[0];
-        sa.py = c->ps[1];
-        sa.pz = c->ps[2];
-        sa.tile_box = c->tile_box;
-        sa.box_stride = std::max<uint32_t>(c->n_tiles, 1);
+    // A serial list with every hole a source is sorted only every few steps, at
+    // multiples of that number, so that a split of a run changes nothing.
+    const bool keep_ok = c->list_mode && !use_closure && c->p.collected_are_sources;
+    double load_pairs = 0.0;
+    for (uint32_t e = 0; e < c->n_events; ++e) {
+        const double ne = (double)(c->off_h[e + 1] - c->off_h[e]);
+        load_pairs += ne * ne;
+    }
+    const int64_t keep_steps = load_pairs <= kKeepPairs                             ? kKeepSmall
+                               : load_pairs <= kKeepLongPairs || dt_ps <= kKeepLongPs ? kKeepLarge
+                                                                                      : 1;
+    sa.n_events = c->n_events;
+    sa.ev_tile = c->ev_tile_d;
+    sa.tile_event = c->tile_event_d;
+    sa.n_tiles = c->n_tiles;
+    sa.px = c->ps[0];
+    sa.py = c->ps[1];
+    sa.pz = c->ps[2];
+    sa.tile_box = c->tile_box;
+    sa.box_stride = std::max<uint32_t>(c->n_tiles, 1);
+    if (c->kept && use_closure) {  // whose steps run over the list of their positions
+        GCCD_HIP(c, launch_make_keys(c->x, c->y, c->z, c->cstep, c->ev_of, c->ev_off_d, n, c->kl,
+                                     c->ukeys[c->u], c->stream));
+        int r = finish_list(c, c->ukeys[c->u]);
+        if (r != GCCD_OK) return r;
+        c->kept = false;
+    } else if (c->kept && !c->gathered) {
+        int r = gather(c);
+        if (r != GCCD_OK) return r;
+        c->gathered = true;
     }
     // Puts the list state in line with `pipelined`.
     auto enter_mode = [&]() -> int {
@@ -1610,6 +1668,7 @@ int gccd_run(gccd_ctx* c, double dt_ps, int64_t max_steps, int64_t* steps_done,
         if (r != GCCD_OK) return r;
     }
     int64_t stretch = 0;  // steps of the stretch being issued
+    int64_t first = 0;    // and its first step
 
     // One time step: in list mode step i of the current stretch (its index is
     // the base in sched[kSchedStep] plus i), else absolute step s.
@@ -1640,6 +1699,14 @@ int gccd_run(gccd_ctx* c, double dt_ps, int64_t max_steps, int64_t* steps_done,
             // sort of a pipelined list overlaps the field and gains nothing)
             sa.sort_runs = (!fused && !pipelined) ? 1 : 0;
             sa.ev_active = c->ev_active_d[c->cur];
+            sa.keep = keep_ok && !pipelined && (first + i + 1) % keep_steps != 0 ? 1 : 0;
+            c->kept = sa.keep != 0;
+            c->gathered = true;
+            sa.arrive = fused ? c->sched + kSchedArrive : nullptr;
+            if (c->kept) {
+                GCCD_HIP(c, launch_step(sa, n, c->stream));
+                return GCCD_OK;
+            }
             if (fused) {  // the kernel leaves the next step's list in place of this one's
                 sa.keys_sorted = c->keys[c->cur];
                 sa.ev_active_out = c->ev_active_d[c->cur];
@@ -1690,6 +1757,7 @@ int gccd_run(gccd_ctx* c, double dt_ps, int64_t max_steps, int64_t* steps_done,
                                        sizeof(uint32_t), hipMemcpyHostToDevice, c->stream));
         }
         stretch = chunk_steps;
+        first = step0 + k;
         bool replayed = false;
         // a pipelined stretch is replayed from the list buffers it was
         // captured from (an even stretch leaves them as it found them)
@@ -1762,18 +1830,8 @@ int gccd_field(gccd_ctx* c, double* ex, double* ey, double* ez) {
     if (!ex || !ey || !ez) return fail(c, GCCD_E_INVALID, "gccd_field: NULL pointer");
     const uint32_t n = (uint32_t)c->n;
     GCCD_HIP(c, hipStreamSynchronize(c->stream));  // the item staging buffer is free
-    {
-        int r;
-        if (!c->list_mode) {
-            // no list is kept without Coulomb repulsion: build one for this call
-            GCCD_HIP(c, launch_make_keys(c->x, c->y, c->z, c->cstep, c->ev_of, c->ev_off_d, n,
-                                         c->kl, c->ukeys[0], c->stream));
-            r = finish_list(c, c->ukeys[0]);
-        } else {
-            r = gather(c);  // the current positions in the order of the current list
-        }
-        if (r != GCCD_OK) return r;
-    }
+    ListView list(c);
+    if (int r = list.make(); r != GCCD_OK) return r;
     if (closure_applies(c)) {
         choose_near_chunks(c);
         int r = ensure_closure_capacity(c);

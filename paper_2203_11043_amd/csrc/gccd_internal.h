@@ -138,6 +138,9 @@ struct StepArgs {
     double close_unit;          // um^-2 per fixed-point unit of close
     unsigned long long* stats;  // [0] carrier-steps, [1] pair interactions
     int32_t* misc;              // [0] non-finite flag, [1] step after the last busy one
+    int32_t keep;               // list mode, every hole a source: the list's order stays,
+                                // and the step writes the new positions to px, py, pz
+                                // and the boxes of its tiles itself
     // A load of at most kFusedList carriers in at most kFusedTiles source
     // tiles (list mode): with arrive set, the
     // last workgroup of the step sorts keys_out into keys_sorted, writes each

@@ -1867,43 +1867,18 @@ hipError_t launch_count(const uint64_t* keys, const uint32_t* ev_off, uint32_t n
     return hipGetLastError();
 }
 
-// Source tile g of event e = tile_event[g] (local tile t = g - ev_tile[e]),
-// by one workgroup of kTile threads: positions of every slot of the tile
-// (key_at(slot) gives the slot's key; ns_or_active is the event's travelling
-// holes, the sources unless sources_all), bounding box of
-// the slots that are sources (rows 0-5 of box: low x, y, z, high x, y, z),
-// and the same for each 64-slot quarter of the tile (row 6 + 4 k + q for
-// bound k of quarter q) and each 16-slot group (row 30 + 16 k + g), which
-// the near-field kernel culls by.  The group boxes are the first four steps
-// of the lane reduction that gives the quarter boxes.
-template <class KeyAt>
-__device__ __forceinline__ void gather_tile(uint32_t g, KeyAt key_at, const uint32_t* ev_off,
-                                            const uint32_t* ev_tile, const uint32_t* tile_event,
-                                            uint32_t ns_or_active, int sources_all, KeyLayout kl,
-                                            const double* x, const double* y, const double* z,
-                                            double* px, double* py, double* pz, double* box,
-                                            uint32_t stride, double (*red)[kTile / 64]) {
-    const uint32_t e = tile_event[g];
-    const uint32_t t = g - ev_tile[e];
-    const uint32_t off = ev_off[e], ne = ev_off[e + 1] - off;
-    const uint32_t ns = sources_all ? ne : ns_or_active;
-    const uint32_t i = t * kTile + threadIdx.x;
-    double lx = INFINITY, ly = INFINITY, lz = INFINITY;
-    double hx = -INFINITY, hy = -INFINITY, hz = -INFINITY;
-    if (i < ne) {
-        // a slot of event e holds a key of event e; the clamp keeps every
-        // load inside the event regardless
-        const uint32_t c = off + min(key_local(key_at(off + i), kl), ne - 1u);
-        const double vx = x[c], vy = y[c], vz = z[c];
-        px[off + i] = vx;
-        py[off + i] = vy;
-        pz[off + i] = vz;
-        if (i < ns) {
-            lx = hx = vx;
-            ly = hy = vy;
-            lz = hz = vz;
-        }
-    }
+// The boxes of source tile g, by one workgroup of kTile threads, one slot
+// each (source: whether the slot is one): bounding box of the tile (rows
+// 0-5 of box: low x, y, z, high x, y, z), and the same for each 64-slot
+// quarter of the tile (row 6 + 4 k + q for bound k of quarter q) and each
+// 16-slot group (row 30 + 16 k + g), which the near-field kernel culls by.
+// The group boxes are the first four steps of the lane reduction that gives
+// the quarter boxes.
+__device__ __forceinline__ void tile_boxes(uint32_t g, bool source, double vx, double vy,
+                                           double vz, double* box, uint32_t stride,
+                                           double (*red)[kTile / 64]) {
+    double lx = source ? vx : INFINITY, ly = source ? vy : INFINITY, lz = source ? vz : INFINITY;
+    double hx = source ? vx : -INFINITY, hy = source ? vy : -INFINITY, hz = source ? vz : -INFINITY;
     // butterfly over lanes: after the strides 1..8 every lane holds its
     // 16-slot group's box, after 16 and 32 its quarter's
 #pragma unroll
@@ -1949,6 +1924,37 @@ __device__ __forceinline__ void gather_tile(uint32_t g, KeyAt key_at, const uint
         for (int w = 1; w < kTile / 64; ++w) v = (k < 3) ? fmin(v, red[k][w]) : fmax(v, red[k][w]);
         box[(size_t)k * stride + g] = v;
     }
+}
+
+// Source tile g of event e = tile_event[g] (local tile t = g - ev_tile[e]),
+// by one workgroup of kTile threads: positions of every slot of the tile
+// (key_at(slot) gives the slot's key) and its boxes; ns_or_active is the
+// event's travelling holes, the sources unless sources_all.
+template <class KeyAt>
+__device__ __forceinline__ void gather_tile(uint32_t g, KeyAt key_at, const uint32_t* ev_off,
+                                            const uint32_t* ev_tile, const uint32_t* tile_event,
+                                            uint32_t ns_or_active, int sources_all, KeyLayout kl,
+                                            const double* x, const double* y, const double* z,
+                                            double* px, double* py, double* pz, double* box,
+                                            uint32_t stride, double (*red)[kTile / 64]) {
+    const uint32_t e = tile_event[g];
+    const uint32_t t = g - ev_tile[e];
+    const uint32_t off = ev_off[e], ne = ev_off[e + 1] - off;
+    const uint32_t ns = sources_all ? ne : ns_or_active;
+    const uint32_t i = t * kTile + threadIdx.x;
+    double vx = 0.0, vy = 0.0, vz = 0.0;
+    if (i < ne) {
+        // a slot of event e holds a key of event e; the clamp keeps every
+        // load inside the event regardless
+        const uint32_t c = off + min(key_local(key_at(off + i), kl), ne - 1u);
+        vx = x[c];
+        vy = y[c];
+        vz = z[c];
+        px[off + i] = vx;
+        py[off + i] = vy;
+        pz[off + i] = vz;
+    }
+    tile_boxes(g, i < ne && i < ns, vx, vy, vz, box, stride, red);
 }
 
 __global__ __launch_bounds__(kTile) void gather_tiles(
@@ -2070,6 +2076,10 @@ __device__ __forceinline__ double unit_open(uint32_t w) {
 //   list mode (Coulomb on): one thread per slot of the sorted list; every
 //     carrier keeps its slot in the next (unsorted) list with its new key,
 //     collected holes copying theirs through; the next sort restores order.
+//   kept list (a.keep): one workgroup per source tile, one thread per slot.  The
+//     order stays, so no key is made or sorted: the step writes the slots' new
+//     positions and its tile's boxes.  1,000 holes, latency-bound: 7.1 us, with
+//     the rebuilt list 24.4.
 //   carrier mode: one thread per carrier; travelling holes are counted, one
 //     atomic per wave.
 // ---------------------------------------------------------------------------
@@ -2232,11 +2242,15 @@ __device__ __forceinline__ void sincospi_s(double x, double* s, double* c) {
     fp64::sincospi<!LIST>(x, s, c);
 }
 
-// LIST: list mode (a.list_mode, Coulomb on); carrier mode is a kernel of
-// its own (drift_update), without the list code, for the step without
-// repulsion.
-template <bool FUSE, bool LIST>
+// The step's modes: list mode (a.list_mode, Coulomb on) leaving the new keys for
+// a sort of their own, rebuilding the list itself (a.arrive) or keeping the
+// list's order (a.keep); carrier mode is a kernel of its own (drift_update),
+// without the list code, for the step without repulsion.
+constexpr int kStepList = 0, kStepFused = 1, kStepKept = 2, kStepDrift = 3;
+
+template <int MODE>
 __device__ __forceinline__ void step_body(const StepArgs& a) {
+    constexpr bool FUSE = MODE == kStepFused, KEEP = MODE == kStepKept, LIST = MODE != kStepDrift;
     const uint32_t step = a.step + (a.step_base ? *a.step_base : 0u);
     // travelling holes at the start of this step, of the next one, and the
     // counter of the step after next (cleared now; nobody reads it)
@@ -2256,24 +2270,43 @@ __device__ __forceinline__ void step_body(const StepArgs& a) {
     // FUSE, or a.sort_runs: each turn's kStepThreads slots leave their new
     // keys as one sorted run (sort_block_keys), which the next sort only
     // merges; else every slot leaves its key in place
-    const bool runs = FUSE || (LIST && a.sort_runs != 0);
+    const bool runs = FUSE || (MODE == kStepList && a.sort_runs != 0);
     __shared__ uint64_t sk[kStepThreads];
-    for (uint32_t base = blockIdx.x * kStepThreads; base < a.n_all;
+    // KEEP: workgroup g owns source tile g, one slot per thread (one turn)
+    uint32_t te = 0u, toff = 0u, tne = a.n_all, ti = blockIdx.x * kTile + threadIdx.x;
+    if (KEEP && !a.one_event) {
+        te = a.tile_event[blockIdx.x];
+        toff = a.ev_off[te];
+        tne = a.ev_off[te + 1] - toff;
+        ti = (blockIdx.x - a.ev_tile[te]) * kTile + threadIdx.x;
+    }
+    double px = 0.0, py = 0.0, pz = 0.0;  // KEEP: the slot's position
+    const uint32_t end = KEEP ? gridDim.x * kStepThreads : a.n_all;
+    for (uint32_t base = blockIdx.x * kStepThreads; base < end;
          base += gridDim.x * kStepThreads) {
-        const uint32_t slot = base + threadIdx.x;
+        const uint32_t slot = KEEP ? toff + ti : base + threadIdx.x;
         uint64_t run_key = ~0ull;  // this slot's new key, when the keys form runs
         bool keep = false;
-        if (slot < a.n_all) {
+        if (KEEP ? ti < tne : slot < a.n_all) {
             uint32_t e, j, local, src = 0u;
             bool active;
             uint64_t key = 0;
+            if (KEEP) {
+                px = a.px[slot];
+                py = a.py[slot];
+                pz = a.pz[slot];
+            }
             if (LIST) {
-                // the list may be one step old (its travelling segment then
-                // still holds the holes collected in the last step): the
+                // the list may be some steps old (its travelling segment then
+                // still holds the holes collected since): the
                 // carrier's own collection step decides
                 key = a.keys_in[slot];
                 uint32_t off, ne;
-                if (a.one_event) {
+                if (KEEP) {
+                    e = te;
+                    off = toff;
+                    ne = tne;
+                } else if (a.one_event) {
                     e = 0u;
                     off = 0u;
                     ne = a.n_all;
@@ -2287,8 +2320,13 @@ __device__ __forceinline__ void step_body(const StepArgs& a) {
                 active = a.cstep[j] < 0;
                 if (active) {
                     src = a.sources_all ? ne : a.ev_active[e];
-                } else if (a.close && slot - off < a.ev_active[e]) {
-                    // a target of the field launch collected in the last step:
+                } else {
+                    // collected in a step that kept the list
+                    if (runs && !key_collected(key, a.kl))
+                        key = make_key(e, true, a.x[j], a.y[j], a.z[j], local, a.kl);
+                }
+                if (!active && a.close && slot - off < a.ev_active[e]) {
+                    // a target of the field launch collected since the list was sorted:
                     // its close-pair sums are not consumed, so cleared here
                     const size_t ps = a.pstride;
                     a.close[slot] = 0ull;
@@ -2318,7 +2356,7 @@ __device__ __forceinline__ void step_body(const StepArgs& a) {
                     // eight (a small load, latency-bound: sixteen), then four
                     // groups' loads in flight ahead of their adds (the adds in
                     // group order)
-                    constexpr int kW = FUSE ? 16 : 8;
+                    constexpr int kW = FUSE || KEEP ? 16 : 8;
                     for (; c + kW <= nchunk; c += kW) {
                         float v[kW][3];
 #pragma unroll
@@ -2332,7 +2370,7 @@ __device__ __forceinline__ void step_body(const StepArgs& a) {
                             sz += (double)v[u][2];
                         }
                     }
-                    if (FUSE && c + 8 <= nchunk) {
+                    if ((FUSE || KEEP) && c + 8 <= nchunk) {
                         float v[8][3];
 #pragma unroll
                         for (int u = 0; u < 8; ++u)
@@ -2382,7 +2420,8 @@ __device__ __forceinline__ void step_body(const StepArgs& a) {
                     ecy = a.K * sy;
                     ecz = a.K * sz;
                 }
-                const double x0 = a.x[j], y0 = a.y[j], z0 = a.z[j];
+                const double x0 = KEEP ? px : a.x[j], y0 = KEEP ? py : a.y[j],
+                             z0 = KEEP ? pz : a.z[j];
                 const double es = a.a1 * z0 - a.a2;
                 const double ex = ecx, ey = ecy, ez = LIST ? ecz + es : es;
                 double mu = a.mu0;
@@ -2438,11 +2477,17 @@ __device__ __forceinline__ void step_body(const StepArgs& a) {
                 const bool collected = zn <= a.z_well;
                 if (collected) a.cstep[j] = (int32_t)(step + 1u);
                 keep = !collected;
-                if (LIST) key = make_key(e, collected, xn, yn, zn, local, a.kl);
+                if (KEEP) {
+                    a.px[slot] = px = xn;
+                    a.py[slot] = py = yn;
+                    a.pz[slot] = pz = zn;
+                } else if (LIST) {
+                    key = make_key(e, collected, xn, yn, zn, local, a.kl);
+                }
             }
             if (runs)
                 run_key = key;
-            else if (LIST)
+            else if (LIST && !KEEP)
                 a.keys_out[slot] = key;
         }
         kept += (uint32_t)__popcll(__ballot(keep));
@@ -2451,6 +2496,10 @@ __device__ __forceinline__ void step_body(const StepArgs& a) {
             const uint64_t sorted = sort_block_keys(run_key, m, sk);
             if (threadIdx.x < m) a.keys_out[base + threadIdx.x] = sorted;
         }
+    }
+    if constexpr (KEEP) {
+        __shared__ double red[6][kTile / 64];
+        tile_boxes(blockIdx.x, ti < tne, px, py, pz, a.tile_box, a.box_stride, red);
     }
     // one atomic per workgroup for each count: a counter taking one per wave
     // and grid-stride turn (2.6e5 at 2^24 holes) serialised the whole step
@@ -2491,25 +2540,31 @@ __device__ __forceinline__ void step_body(const StepArgs& a) {
     }
 }
 
-template <bool FUSE>
+template <int MODE>
 __global__ __launch_bounds__(kStepThreads) void step_update(StepArgs a) {
-    step_body<FUSE, true>(a);
+    step_body<MODE>(a);
 }
 
 __global__ __launch_bounds__(kStepThreads) void drift_update(StepArgs a) {
-    step_body<false, false>(a);
+    step_body<kStepDrift>(a);
 }
 
 hipError_t launch_step(const StepArgs& a, uint32_t n_slots, hipStream_t s) {
-    if (a.arrive) {
+    static_assert(kTile == kStepThreads, "a workgroup of the kept step owns one source tile");
+    if (a.keep) {
+        if (!a.list_mode || !a.sources_all || a.n_tiles == 0) return hipErrorInvalidValue;
+        step_update<kStepKept><<<a.n_tiles, kStepThreads, 0, s>>>(a);
+    } else if (a.arrive) {
         // the rebuilt list needs every slot and tile in one workgroup's LDS
         if (!a.list_mode || n_slots != a.n_all || n_slots > (uint32_t)kFusedList ||
             a.n_tiles > (uint32_t)kFusedTiles)
             return hipErrorInvalidValue;
         // one slot per thread: workgroup b's keys are slots [b, b + 1) kStepThreads
-        step_update<true><<<(n_slots + kStepThreads - 1) / kStepThreads, kStepThreads, 0, s>>>(a);
+        step_update<kStepFused>
+            <<<(n_slots + kStepThreads - 1) / kStepThreads, kStepThreads, 0, s>>>(a);
     } else if (a.list_mode) {
-        step_update<false><<<grid_for(n_slots, kStepThreads, 16384), kStepThreads, 0, s>>>(a);
+        step_update<kStepList>
+            <<<grid_for(n_slots, kStepThreads, 16384), kStepThreads, 0, s>>>(a);
     } else {
         drift_update<<<grid_for(n_slots, kStepThreads, 16384), kStepThreads, 0, s>>>(a);
     }
