@@ -190,6 +190,7 @@ struct gccd_ctx {
     bool graph_refused = false;      // a capture for this load failed or held a memset node
     int graph_cur = -1, graph_u = -1;  // the list buffers the captured steps start from
     int graph_pipe = -1;               // ... and whether they pipeline the list
+    double graph_dt_ps = 0.0;          // ... and their time step
     int64_t graph_replays = 0;
 
     bool timing = false;
@@ -1763,7 +1764,8 @@ int gccd_run(gccd_ctx* c, double dt_ps, int64_t max_steps, int64_t* steps_done,
         // captured from (an even stretch leaves them as it found them)
         if (graphable && chunk_steps == kPoll && !c->graph_refused) {
             if (c->graph_exec && (c->graph_cur != c->cur || c->graph_u != c->u ||
-                                  c->graph_pipe != (pipelined ? 1 : 0)))
+                                  c->graph_pipe != (pipelined ? 1 : 0) ||
+                                  c->graph_dt_ps != dt_ps))
                 drop_graph(c);
             if (!c->graph_exec) {
                 int r = capture_steps(c, issue);
@@ -1771,6 +1773,7 @@ int gccd_run(gccd_ctx* c, double dt_ps, int64_t max_steps, int64_t* steps_done,
                 c->graph_cur = c->cur;
                 c->graph_u = c->u;
                 c->graph_pipe = pipelined ? 1 : 0;
+                c->graph_dt_ps = dt_ps;
             }
             if (c->graph_exec) {
                 GCCD_HIP(c, hipGraphLaunch(c->graph_exec, c->stream));

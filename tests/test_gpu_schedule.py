@@ -207,3 +207,21 @@ def test_full_batch_schedules_agree(g, W):
     print(f"[schedule] batch of 4096 ({len(x)} holes): graph replays {st['graph_replays']}, "
           f"usable {st['graph_usable']}", flush=True)
     assert st["graph_usable"] == 1 and st["graph_replays"] == 2
+
+
+def test_graph_follows_the_time_step(g, W):
+    """A stretch with another time step is not a replay of the captured one."""
+    w = W.single_cloud(500, seed=9, depth_um=400.0)
+    d = dict(W.DEVICE, event=9)
+    out = {}
+    for s in ("grid", "graph"):
+        ctx = g.gccd_init(g.Params.from_device(d))
+        try:
+            g.gccd_set_schedule(ctx, s)
+            g.gccd_load(ctx, *gpu(w.x, w.y, w.z))
+            for dt in (10.0, 5.0, 5.0, 20.0):
+                g.gccd_run(ctx, dt, 32)
+            out[s] = g.gccd_positions(ctx, 500)[0].cpu().numpy()
+        finally:
+            g.gccd_destroy(ctx)
+    assert np.array_equal(out["grid"], out["graph"])
