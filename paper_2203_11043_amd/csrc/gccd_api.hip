@@ -72,6 +72,22 @@ enum : int {
 
 }  // namespace
 
+namespace {
+
+// Everything that the launches of a captured stretch take their arguments, grids
+// and number from.  A graph is replayed while this stays the same bytes; the
+// next load of the same shape on a context then replays the graph of the last one
+// (its buffers stay in place) instead of capturing 64 launches again (150 us).
+struct GraphKey {
+    FieldArgs field;
+    StepArgs step;
+    size_t items_cap;
+    int64_t keep_steps;
+    int tpt, precision, cur, u, pipelined, sorting, keep_ok, fused;
+};
+
+}  // namespace
+
 struct gccd_ctx {
     gccd_params p{};
     hipStream_t stream = nullptr;
@@ -188,9 +204,7 @@ struct gccd_ctx {
     hipStream_t cap_stream = nullptr; // captures are recorded here (the context's stream
                                       // may be the null stream, which cannot capture)
     bool graph_refused = false;      // a capture for this load failed or held a memset node
-    int graph_cur = -1, graph_u = -1;  // the list buffers the captured steps start from
-    int graph_pipe = -1;               // ... and whether they pipeline the list
-    double graph_dt_ps = 0.0;          // ... and their time step
+    GraphKey graph_key;              // what the captured steps were issued from
     int64_t graph_replays = 0;
 
     bool timing = false;
@@ -252,8 +266,9 @@ void hfree(T*& ptr) {
     ptr = nullptr;
 }
 
-// The captured steps refer to the load's buffers and launch shape: any change
-// of those drops the graph (the next gccd_run captures again).
+// The captured steps refer to the load's buffers and launch shape: a buffer that
+// moves under them or a setting that changes them drops the graph (the next
+// gccd_run captures again), and so does a GraphKey that differs.
 void drop_graph(gccd_ctx* c) {
     if (c->graph_exec) (void)hipGraphExecDestroy(c->graph_exec);
     if (c->graph) (void)hipGraphDestroy(c->graph);
@@ -264,7 +279,6 @@ void drop_graph(gccd_ctx* c) {
 // Drops what belongs to the current load; the buffers stay.
 void reset_load(gccd_ctx* c) {
     if (c->side) (void)hipStreamSynchronize(c->side);  // a list may still be sorting
-    drop_graph(c);
     c->graph_refused = false;
     c->sorting = false;
     c->kept = false;
@@ -276,6 +290,7 @@ void reset_load(gccd_ctx* c) {
 
 void free_buffers(gccd_ctx* c) {
     reset_load(c);
+    drop_graph(c);
     dfree(c->arena);
     dfree(c->part);
     dfree(c->close);
@@ -541,7 +556,6 @@ bool reserve_part(gccd_ctx* c, int groups) {
 
 // Partial-sum buffer and work-item capacity for the current chunk choice.
 int reserve_chunk_buffers(gccd_ctx* c) {
-    drop_graph(c);
     size_t items = 0;
     for (uint32_t e = 0; e < c->n_events; ++e) {
         const uint64_t ne = c->off_h[e + 1] - c->off_h[e];
@@ -558,6 +572,7 @@ int reserve_chunk_buffers(gccd_ctx* c) {
 }
 
 int size_chunk_buffers(gccd_ctx* c) {
+    drop_graph(c);
     if (int r = reserve_chunk_buffers(c); r != GCCD_OK) return r;
     GCCD_HIP(c, hipMemcpyAsync(c->ev_chunks_d, c->groups_h.data(), c->n_events * sizeof(int32_t),
                                hipMemcpyHostToDevice, c->stream));
@@ -1745,6 +1760,7 @@ int gccd_run(gccd_ctx* c, double dt_ps, int64_t max_steps, int64_t* steps_done,
     const bool graphable = c->list_mode && !use_closure && !c->timing &&
                            graph_cap(c) > 0;
 
+    const StepArgs sa0 = sa;  // before a step's own fields
     int64_t k = 0;
     while (k < max_steps && bound > 0) {
         // stretches end at multiples of kPoll (a call that starts between
@@ -1763,17 +1779,25 @@ int gccd_run(gccd_ctx* c, double dt_ps, int64_t max_steps, int64_t* steps_done,
         // a pipelined stretch is replayed from the list buffers it was
         // captured from (an even stretch leaves them as it found them)
         if (graphable && chunk_steps == kPoll && !c->graph_refused) {
-            if (c->graph_exec && (c->graph_cur != c->cur || c->graph_u != c->u ||
-                                  c->graph_pipe != (pipelined ? 1 : 0) ||
-                                  c->graph_dt_ps != dt_ps))
-                drop_graph(c);
+            GraphKey key;
+            memset(&key, 0, sizeof key);
+            key.field = field_args(c, false);
+            key.step = sa0;
+            key.items_cap = c->items_cap;
+            key.keep_steps = keep_steps;
+            key.tpt = c->tpt;
+            key.precision = c->precision;
+            key.cur = c->cur;
+            key.u = c->u;
+            key.pipelined = pipelined ? 1 : 0;
+            key.sorting = c->sorting ? 1 : 0;
+            key.keep_ok = keep_ok ? 1 : 0;
+            key.fused = fused ? 1 : 0;
+            if (c->graph_exec && memcmp(&key, &c->graph_key, sizeof key) != 0) drop_graph(c);
             if (!c->graph_exec) {
                 int r = capture_steps(c, issue);
                 if (r != GCCD_OK) return r;
-                c->graph_cur = c->cur;
-                c->graph_u = c->u;
-                c->graph_pipe = pipelined ? 1 : 0;
-                c->graph_dt_ps = dt_ps;
+                memcpy(&c->graph_key, &key, sizeof key);
             }
             if (c->graph_exec) {
                 GCCD_HIP(c, hipGraphLaunch(c->graph_exec, c->stream));

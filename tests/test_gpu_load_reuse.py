@@ -85,3 +85,34 @@ def test_copied_source(source):
         np.testing.assert_array_equal(u, v)
     g.gccd_destroy(a)
     g.gccd_destroy(b)
+
+
+@pytest.mark.parametrize("n", [700, 3000])
+def test_replays_of_a_later_load(n):
+    """Loads of the same shape replay the steps captured for an earlier one: other
+    positions, other events of the same total and number of tiles, another
+    launch shape and another time step in between, each as on a fresh context."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2203_11043_amd import gccd as g
+
+    params = g.Params()
+    kept = g.gccd_init(params)
+    a, b = n // 2 - 20, n - n // 2 + 20
+    for k, (sizes, dt, chunks) in enumerate([([n], 10.0, 0), ([n], 10.0, 0), ([a, b], 10.0, 0),
+                                             ([b, a], 10.0, 0), ([n], 10.0, 3), ([n], 5.0, 3),
+                                             ([n - 1], 5.0, 3), ([n], 10.0, 0)]):
+        p = cloud(sizes, 80 + k)
+        off = [0] + np.cumsum(sizes).tolist()
+        fresh = g.gccd_init(params)
+        out = []
+        for ctx in (kept, fresh):
+            g.gccd_set_launch(ctx, 0, chunks)
+            g.gccd_load_events(ctx, off, *p)
+            g.gccd_run(ctx, dt, 70)
+            assert g.gccd_stats(ctx)["graph_usable"] == 1
+            out.append(g.gccd_positions(ctx, off[-1]))
+        for u, v in zip(*out):
+            assert torch.equal(u, v)
+        g.gccd_destroy(fresh)
+    g.gccd_destroy(kept)
