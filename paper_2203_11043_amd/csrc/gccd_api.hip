@@ -1751,7 +1751,8 @@ int gccd_run(gccd_ctx* c, double dt_ps, int64_t max_steps, int64_t* steps_done,
                 GCCD_HIP(c, hipStreamWaitEvent(c->stream, c->ev_list, 0));
             return GCCD_OK;
         }
-        sa.step = s;
+        sa.step = s;  // the whole stretch in one launch
+        sa.n_steps = (uint32_t)stretch;
         GCCD_HIP(c, launch_step(sa, n, c->stream));
         return GCCD_OK;
     };
@@ -1806,7 +1807,8 @@ int gccd_run(gccd_ctx* c, double dt_ps, int64_t max_steps, int64_t* steps_done,
             }
         }
         if (!replayed) {
-            for (int64_t i = 0; i < chunk_steps; ++i) {
+            const int64_t launches = c->list_mode ? chunk_steps : 1;
+            for (int64_t i = 0; i < launches; ++i) {
                 int r = issue((uint32_t)i, (uint32_t)(step0 + k + i));
                 if (r != GCCD_OK) return r;
             }
@@ -1818,7 +1820,7 @@ int gccd_run(gccd_ctx* c, double dt_ps, int64_t max_steps, int64_t* steps_done,
             r = collect_timing(c);
             if (r != GCCD_OK) return r;
         }
-        bound = c->host_meta[kMetaCount + (uint32_t)(step0 + k) % 3u];
+        bound = c->host_meta[kMetaCount + (c->list_mode ? (uint32_t)(step0 + k) % 3u : 0u)];
         if (c->host_meta[kMetaFlag] != 0) {
             c->step = (int64_t)(uint32_t)c->host_meta[kMetaLast];
             c->n_active = bound;

@@ -130,9 +130,11 @@ struct StepArgs {
     uint32_t step;             // the step index, or its offset from *step_base
     const uint32_t* step_base; // list mode: device word added to step (a graph replays
                                // the same arguments at a new base)
+    uint32_t n_steps;          // carrier mode: steps of the launch
     uint32_t event0;          // Philox event word of event 0
     uint32_t key0, key1;
     uint32_t* cnt_ring;       // [3] travelling holes at the start of step s in [s % 3]
+                              // (carrier mode: in [0], after the steps issued so far)
     unsigned long long* close;  // list mode: the exactly summed close terms by slot
                                 // ([3][pstride]); read and cleared
     double close_unit;          // um^-2 per fixed-point unit of close

@@ -2080,8 +2080,7 @@ __device__ __forceinline__ double unit_open(uint32_t w) {
 //     order stays, so no key is made or sorted: the step writes the slots' new
 //     positions and its tile's boxes.  1,000 holes, latency-bound: 7.1 us, with
 //     the rebuilt list 24.4.
-//   carrier mode: one thread per carrier; travelling holes are counted, one
-//     atomic per wave.
+//   carrier mode: drift_steps.
 // ---------------------------------------------------------------------------
 // The list of a load of at most kFusedList carriers in at most kFusedTiles
 // source tiles, rebuilt by the last workgroup of its step: the new keys,
@@ -2242,15 +2241,71 @@ __device__ __forceinline__ void sincospi_s(double x, double* s, double* c) {
     fp64::sincospi<!LIST>(x, s, c);
 }
 
+// One step of one travelling hole at (x, y, z) in the Coulomb field (ecx, ecy,
+// ecz): static field, mobility, drift, diffusion and the mirror at the back surface.
+template <bool LIST>
+__device__ __forceinline__ void move_hole(const StepArgs& a, uint32_t step, uint32_t e,
+                                          uint32_t local, double ecx, double ecy, double ecz,
+                                          double& x, double& y, double& z) {
+    const double es = a.a1 * z - a.a2;
+    const double ex = ecx, ey = ecy, ez = LIST ? ecz + es : es;
+    double mu = a.mu0;
+    if (a.mobility_model == 0) {
+        // Eq. (2), mu0 / (1 + (|E|/Ec)^beta)^(1/beta), as
+        // mu0 exp(-log1p(y) / beta) with y = exp(beta (log|E|^2 / 2
+        // - log Ec)): four transcendentals instead of two general
+        // powers and a square root.  The arguments are held in the
+        // functions' finite ranges, so no special case is tested:
+        // |E|^2 at or above 2^-1000 (|E| = 0 then gives a y far
+        // below the rounding of 1 + y, so mu = mu0 exactly, as
+        // y = 0 would), the exponents within [-745, 709]
+        const double e2 = fmax(ex * ex + ey * ey + ez * ez, 0x1p-1000);
+        const double ly = a.beta * (0.5 * log_pos_s<LIST>(e2) - a.log_ec);
+        const double y = exp_fin_s<LIST>(fmin(fmax(ly, -745.0), 709.0));
+        mu = a.mu0 * exp_fin_s<LIST>(fmax(-a.inv_beta * log1p_fin_s<LIST>(y), -745.0));
+    }
+    // v = mu E in cm/s; v dt in cm; 1 cm = 1e4 um.  Without
+    // repulsion the field is the static one, along z only: no
+    // lateral drift (mu 0 dt = +0 exactly)
+    double dx = LIST ? mu * ex * a.dt_s * 1e4 : 0.0;
+    double dy = LIST ? mu * ey * a.dt_s * 1e4 : 0.0;
+    double dz = mu * ez * a.dt_s * 1e4;
+    if (a.diffusion) {
+        uint32_t w0 = local, w1 = step, w2 = a.event0 + e, w3 = 0u;
+        philox4x32_10(w0, w1, w2, w3, a.key0, a.key1);
+        // -2 ln u > 2^-33 for u on the open grid (w + 1/2) 2^-32
+        const double r01 = fp64::sqrt_pos(-2.0 * log_pos_s<LIST>(unit_open(w0)));
+        const double r23 = fp64::sqrt_pos(-2.0 * log_pos_s<LIST>(unit_open(w2)));
+        // the angles 2 pi u in half-turns: 2 u is exact, and one
+        // argument reduction serves both sine and cosine
+        double s1, c1, s3, c3;
+        sincospi_s<LIST>(2.0 * unit_open(w1), &s1, &c1);
+        sincospi_s<LIST>(2.0 * unit_open(w3), &s3, &c3);
+        (void)s3;
+        const double D = a.vt * mu;                        // Eq. (4), cm^2/s
+        // Eq. (3), um; 2 D dt > 0 (T > 0, dt > 0), held at or
+        // above 2^-1000 so that the square root's estimate stays
+        // in range even for a dt that underflows it
+        const double s2 = fmax(2.0 * D * a.dt_s, 0x1p-1000);
+        const double sigma = fp64::sqrt_pos(s2) * 1e4;
+        dx += sigma * (r01 * c1);
+        dy += sigma * (r01 * s1);
+        dz += sigma * (r23 * c3);
+    }
+    x += dx;
+    y += dy;
+    z += dz;
+    if (z > a.thickness) z = 2.0 * a.thickness - z;
+}
+
 // The step's modes: list mode (a.list_mode, Coulomb on) leaving the new keys for
 // a sort of their own, rebuilding the list itself (a.arrive) or keeping the
-// list's order (a.keep); carrier mode is a kernel of its own (drift_update),
-// without the list code, for the step without repulsion.
-constexpr int kStepList = 0, kStepFused = 1, kStepKept = 2, kStepDrift = 3;
+// list's order (a.keep).  Carrier mode is a kernel of its own (drift_steps).
+constexpr int kStepList = 0, kStepFused = 1, kStepKept = 2;
 
 template <int MODE>
 __device__ __forceinline__ void step_body(const StepArgs& a) {
-    constexpr bool FUSE = MODE == kStepFused, KEEP = MODE == kStepKept, LIST = MODE != kStepDrift;
+    constexpr bool FUSE = MODE == kStepFused, KEEP = MODE == kStepKept;
     const uint32_t step = a.step + (a.step_base ? *a.step_base : 0u);
     // travelling holes at the start of this step, of the next one, and the
     // counter of the step after next (cleared now; nobody reads it)
@@ -2296,7 +2351,7 @@ __device__ __forceinline__ void step_body(const StepArgs& a) {
                 py = a.py[slot];
                 pz = a.pz[slot];
             }
-            if (LIST) {
+            {
                 // the list may be some steps old (its travelling segment then
                 // still holds the holes collected since): the
                 // carrier's own collection step decides
@@ -2333,21 +2388,11 @@ __device__ __forceinline__ void step_body(const StepArgs& a) {
                     a.close[slot + ps] = 0ull;
                     a.close[slot + 2 * ps] = 0ull;
                 }
-            } else {
-                j = slot;
-                if (a.one_event) {
-                    e = 0u;
-                    local = j;
-                } else {
-                    e = a.ev_of[j];
-                    local = j - a.ev_off[e];
-                }
-                active = a.cstep[j] < 0;
             }
             if (active) {
                 pairs += src;  // sources of the Eq. (6) sum at this target
                 double ecx = 0.0, ecy = 0.0, ecz = 0.0;
-                if (LIST && a.coulomb) {
+                if (a.coulomb) {
                     double sx = 0.0, sy = 0.0, sz = 0.0;
                     const int nchunk = a.ev_chunks[e];
                     const float* pp = a.part + slot;
@@ -2420,56 +2465,9 @@ __device__ __forceinline__ void step_body(const StepArgs& a) {
                     ecy = a.K * sy;
                     ecz = a.K * sz;
                 }
-                const double x0 = KEEP ? px : a.x[j], y0 = KEEP ? py : a.y[j],
-                             z0 = KEEP ? pz : a.z[j];
-                const double es = a.a1 * z0 - a.a2;
-                const double ex = ecx, ey = ecy, ez = LIST ? ecz + es : es;
-                double mu = a.mu0;
-                if (a.mobility_model == 0) {
-                    // Eq. (2), mu0 / (1 + (|E|/Ec)^beta)^(1/beta), as
-                    // mu0 exp(-log1p(y) / beta) with y = exp(beta (log|E|^2 / 2
-                    // - log Ec)): four transcendentals instead of two general
-                    // powers and a square root.  The arguments are held in the
-                    // functions' finite ranges, so no special case is tested:
-                    // |E|^2 at or above 2^-1000 (|E| = 0 then gives a y far
-                    // below the rounding of 1 + y, so mu = mu0 exactly, as
-                    // y = 0 would), the exponents within [-745, 709]
-                    const double e2 = fmax(ex * ex + ey * ey + ez * ez, 0x1p-1000);
-                    const double ly = a.beta * (0.5 * log_pos_s<LIST>(e2) - a.log_ec);
-                    const double y = exp_fin_s<LIST>(fmin(fmax(ly, -745.0), 709.0));
-                    mu = a.mu0 * exp_fin_s<LIST>(fmax(-a.inv_beta * log1p_fin_s<LIST>(y), -745.0));
-                }
-                // v = mu E in cm/s; v dt in cm; 1 cm = 1e4 um.  Without
-                // repulsion the field is the static one, along z only: no
-                // lateral drift (mu 0 dt = +0 exactly)
-                double dx = LIST ? mu * ex * a.dt_s * 1e4 : 0.0;
-                double dy = LIST ? mu * ey * a.dt_s * 1e4 : 0.0;
-                double dz = mu * ez * a.dt_s * 1e4;
-                if (a.diffusion) {
-                    uint32_t w0 = local, w1 = step, w2 = a.event0 + e, w3 = 0u;
-                    philox4x32_10(w0, w1, w2, w3, a.key0, a.key1);
-                    // -2 ln u > 2^-33 for u on the open grid (w + 1/2) 2^-32
-                    const double r01 = fp64::sqrt_pos(-2.0 * log_pos_s<LIST>(unit_open(w0)));
-                    const double r23 = fp64::sqrt_pos(-2.0 * log_pos_s<LIST>(unit_open(w2)));
-                    // the angles 2 pi u in half-turns: 2 u is exact, and one
-                    // argument reduction serves both sine and cosine
-                    double s1, c1, s3, c3;
-                    sincospi_s<LIST>(2.0 * unit_open(w1), &s1, &c1);
-                    sincospi_s<LIST>(2.0 * unit_open(w3), &s3, &c3);
-                    (void)s3;
-                    const double D = a.vt * mu;                        // Eq. (4), cm^2/s
-                    // Eq. (3), um; 2 D dt > 0 (T > 0, dt > 0), held at or
-                    // above 2^-1000 so that the square root's estimate stays
-                    // in range even for a dt that underflows it
-                    const double s2 = fmax(2.0 * D * a.dt_s, 0x1p-1000);
-                    const double sigma = fp64::sqrt_pos(s2) * 1e4;
-                    dx += sigma * (r01 * c1);
-                    dy += sigma * (r01 * s1);
-                    dz += sigma * (r23 * c3);
-                }
-                const double xn = x0 + dx, yn = y0 + dy;
-                double zn = z0 + dz;
-                if (zn > a.thickness) zn = 2.0 * a.thickness - zn;
+                double xn = KEEP ? px : a.x[j], yn = KEEP ? py : a.y[j],
+                       zn = KEEP ? pz : a.z[j];
+                move_hole<true>(a, step, e, local, ecx, ecy, ecz, xn, yn, zn);
                 a.x[j] = xn;
                 a.y[j] = yn;
                 a.z[j] = zn;
@@ -2481,13 +2479,13 @@ __device__ __forceinline__ void step_body(const StepArgs& a) {
                     a.px[slot] = px = xn;
                     a.py[slot] = py = yn;
                     a.pz[slot] = pz = zn;
-                } else if (LIST) {
+                } else {
                     key = make_key(e, collected, xn, yn, zn, local, a.kl);
                 }
             }
             if (runs)
                 run_key = key;
-            else if (LIST && !KEEP)
+            else if (!KEEP)
                 a.keys_out[slot] = key;
         }
         kept += (uint32_t)__popcll(__ballot(keep));
@@ -2545,8 +2543,79 @@ __global__ __launch_bounds__(kStepThreads) void step_update(StepArgs a) {
     step_body<MODE>(a);
 }
 
-__global__ __launch_bounds__(kStepThreads) void drift_update(StepArgs a) {
-    step_body<kStepDrift>(a);
+// a.n_steps steps without repulsion: holes do not see each other, so each
+// stays in its thread's registers over all of them.  Bound by VALU issue: about
+// 300 FP64 instructions per hole and step.  One launch per step read and wrote
+// 52 B per hole each time and stopped at the launch's end: 8 million holes
+// 207 us per step, now 105; 1,000 holes 4.4 us, now 1.5.
+__global__ __launch_bounds__(kStepThreads) void drift_steps(StepArgs a) {
+    const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x >> 6;
+    unsigned long long moved = 0;   // carrier-steps of this lane
+    uint32_t last = 0, gone = 0;    // steps until its last hole stopped; holes collected (wave)
+    for (uint32_t base = blockIdx.x * kStepThreads; base < a.n_all;
+         base += gridDim.x * kStepThreads) {
+        const uint32_t j = base + threadIdx.x;
+        const bool was = j < a.n_all && a.cstep[j] < 0;
+        if (!__any(was)) continue;
+        uint32_t e = 0u, local = j;
+        double x = 0.0, y = 0.0, z = 0.0;
+        if (was) {
+            if (!a.one_event) {
+                e = a.ev_of[j];
+                local = j - a.ev_off[e];
+            }
+            x = a.x[j];
+            y = a.y[j];
+            z = a.z[j];
+        }
+        bool active = was;
+        uint32_t done = 0;  // steps in which this hole travelled
+        for (uint32_t i = 0; i < a.n_steps && __any(active); ++i) {
+            if (active) {
+                move_hole<false>(a, a.step + i, e, local, 0.0, 0.0, 0.0, x, y, z);
+                ++done;
+                active = !(z <= a.z_well);
+            }
+        }
+        if (was) {
+            a.x[j] = x;
+            a.y[j] = y;
+            a.z[j] = z;
+            // a coordinate once infinite or NaN never becomes finite again
+            if (!isfinite(x) || !isfinite(y) || !isfinite(z)) atomicOr(&a.misc[0], 1);
+            if (!active) a.cstep[j] = (int32_t)(a.step + done);
+            moved += done;
+            last = max(last, done);
+        }
+        gone += (uint32_t)__popcll(__ballot(was && !active));
+    }
+    // one atomic per workgroup for each count: a counter taking one per wave
+    // and grid-stride turn (2.6e5 at 2^24 holes) serialised the whole step
+#pragma unroll
+    for (int m = 32; m >= 1; m >>= 1) {
+        moved += __shfl_xor(moved, m);
+        last = max(last, (uint32_t)__shfl_xor((int)last, m));
+    }
+    __shared__ unsigned long long wave_moved[kStepThreads / 64];
+    __shared__ uint32_t wave_last[kStepThreads / 64], wave_gone[kStepThreads / 64];
+    if (lane == 0) {
+        wave_moved[wave] = moved;
+        wave_last[wave] = last;
+        wave_gone[wave] = gone;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        for (int w = 1; w < kStepThreads / 64; ++w) {
+            moved += wave_moved[w];
+            last = max(last, wave_last[w]);
+            gone += wave_gone[w];
+        }
+        if (moved) {
+            atomicAdd(&a.stats[0], moved);
+            atomicMax(reinterpret_cast<uint32_t*>(&a.misc[1]), a.step + last);
+        }
+        if (gone) atomicSub(a.cnt_ring, gone);
+    }
 }
 
 hipError_t launch_step(const StepArgs& a, uint32_t n_slots, hipStream_t s) {
@@ -2566,7 +2635,7 @@ hipError_t launch_step(const StepArgs& a, uint32_t n_slots, hipStream_t s) {
         step_update<kStepList>
             <<<grid_for(n_slots, kStepThreads, 16384), kStepThreads, 0, s>>>(a);
     } else {
-        drift_update<<<grid_for(n_slots, kStepThreads, 16384), kStepThreads, 0, s>>>(a);
+        drift_steps<<<grid_for(n_slots, kStepThreads, 1 << 16), kStepThreads, 0, s>>>(a);
     }
     return hipGetLastError();
 }

@@ -1,0 +1,48 @@
+"""Without repulsion the steps of a stretch run in one launch, each hole in its
+thread's registers.  Whatever the split of a run, positions, collection steps and
+the counts of the statistics are the same; with holes collected on the way, on
+both sides of a workgroup's and a 32-step stretch's edge, for one event and
+several; and the travelling count and the last busy step are those that the
+collection steps say."""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("sizes", [[1], [63], [257], [5000], [1, 300, 700]],
+                         ids=lambda s: "-".join(map(str, s)))
+def test_split_runs(sizes):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2203_11043_amd import gccd as g
+    from paper_2203_11043_amd import workloads as W
+
+    r = np.random.default_rng(17)
+    off = [0] + np.cumsum(sizes).tolist()
+    n = off[-1]
+    p = r.normal(0.0, 3.0, size=(3, n)) + np.array([480.0, 480.0, 25.0])[:, None]
+    p[2, ::50] = 0.0  # collected at the load
+    p = [torch.as_tensor(v).cuda() for v in p]
+    params = g.Params.from_device(dict(W.DEVICE, coulomb=0))
+    out = []
+    for split in ([33, 600], [1] * 40 + [593], [31, 1, 32, 33, 536]):
+        ctx = g.gccd_init(params)
+        g.gccd_load_events(ctx, off, *p)
+        done = [g.gccd_run(ctx, 10.0, k) for k in split]
+        pos, cstep = (v.cpu().numpy() for v in g.gccd_positions(ctx, n))
+        st = g.gccd_stats(ctx)
+        out.append((pos, cstep, st["carrier_steps"], st["step"], sum(d for d, _ in done)))
+        assert np.all(cstep >= 0) and done[-1][1] == 0
+        # every hole travelled until its collection step, the last until the end
+        assert st["carrier_steps"] == cstep.sum() and st["step"] == cstep.max()
+        assert out[-1][4] == cstep.max()
+        # and after the first call those collected later were travelling
+        assert done[0][1] == np.sum(cstep > split[0])
+        g.gccd_destroy(ctx)
+    for o in out[1:]:
+        np.testing.assert_array_equal(o[0], out[0][0])
+        np.testing.assert_array_equal(o[1], out[0][1])
+        assert o[2:] == out[0][2:]
