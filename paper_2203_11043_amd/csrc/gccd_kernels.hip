@@ -2052,8 +2052,9 @@ __device__ __forceinline__ void philox4x32_10(uint32_t& c0, uint32_t& c1, uint32
     for (int r = 0; r < 10; ++r) {
         // one 32 x 32 -> 64-bit multiply-add instruction gives both halves
         const uint64_t pA = (uint64_t)kMulA * c0, pB = (uint64_t)kMulB * c2;
-        const uint32_t n0 = (uint32_t)(pB >> 32) ^ c1 ^ k0;
-        const uint32_t n2 = (uint32_t)(pA >> 32) ^ c3 ^ k1;
+        // (0x96: the three-way XOR)
+        const uint32_t n0 = __builtin_amdgcn_bitop3_b32((uint32_t)(pB >> 32), c1, k0, 0x96);
+        const uint32_t n2 = __builtin_amdgcn_bitop3_b32((uint32_t)(pA >> 32), c3, k1, 0x96);
         c0 = n0;
         c1 = (uint32_t)pB;
         c2 = n2;
@@ -2238,7 +2239,7 @@ __device__ __forceinline__ double log1p_fin_s(double x) {
 }
 template <bool LIST>
 __device__ __forceinline__ void sincospi_s(double x, double* s, double* c) {
-    fp64::sincospi<!LIST>(x, s, c);
+    fp64::sincospi<!LIST, true>(x, s, c);  // x in (0, 2)
 }
 
 // One step of one travelling hole at (x, y, z) in the Coulomb field (ecx, ecy,
@@ -2547,7 +2548,7 @@ __global__ __launch_bounds__(kStepThreads) void step_update(StepArgs a) {
 // stays in its thread's registers over all of them.  Bound by VALU issue: about
 // 300 FP64 instructions per hole and step.  One launch per step read and wrote
 // 52 B per hole each time and stopped at the launch's end: 8 million holes
-// 207 us per step, now 105; 1,000 holes 4.4 us, now 1.5.
+// 207 us per step, now 104; 1,000 holes 4.4 us, now 1.5.
 __global__ __launch_bounds__(kStepThreads) void drift_steps(StepArgs a) {
     const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x >> 6;
     unsigned long long moved = 0;   // carrier-steps of this lane
