@@ -945,7 +945,7 @@ int closure_field(gccd_ctx* c, bool targets_all, uint32_t nt, bool with_net) {
         if (r != GCCD_OK) return r;
     }
     FieldArgs fa = field_args(c, targets_all);
-    GCCD_HIP(c, launch_near(fa, c->gp, n, c->n_items, st));
+    GCCD_HIP(c, launch_near(fa, c->gp, n, c->n_items, (uint32_t)c->near_chunks, st));
     float* far = c->part + (size_t)c->near_chunks * 3 * n;
     if (with_net)
         GCCD_HIP(c, launch_far(c->fgrid, c->gp, c->ps[0], c->ps[1], c->ps[2], nt, far, far + n,

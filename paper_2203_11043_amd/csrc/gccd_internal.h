@@ -237,7 +237,7 @@ hipError_t launch_image(const double* x, const double* y, const int32_t* cstep,
 
 // ---------------------------------------------------------------------------
 // Far-field closure: the Eq. (6) sum split at a distance a into an exact
-// near part (near_tiles) and a far part read from a 32^3 grid through a
+// near part (near_waves, near_matrix) and a far part read from a 32^3 grid through a
 // linear U-Net (bf16 MFMA convolutions) and Catmull-Rom interpolation.
 // ---------------------------------------------------------------------------
 constexpr int kGrid = 32;                    // nodes per axis
@@ -274,7 +274,7 @@ struct ConvArgs {
 
 // n: holes of the load (chooses the kernel)
 hipError_t launch_near(const FieldArgs& a, const GridParams* gp, uint32_t n, uint32_t n_items,
-                       hipStream_t s);
+                       uint32_t n_chunks, hipStream_t s);
 hipError_t launch_moments(const double* x, const double* y, const double* z, uint32_t n,
                           double* part, hipStream_t s);
 hipError_t launch_grid_params(const double* part, const double* x, const double* y,

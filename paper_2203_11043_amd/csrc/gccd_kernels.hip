@@ -1409,93 +1409,143 @@ void near_matrix(FieldArgs a, const GridParams* gp) {
 }
 
 // ---------------------------------------------------------------------------
-// Near part of the closure's split of Eq. (6): the same sum over the
-// sources closer than a only (r^2 + eps^2 < a^2 + eps^2).  Work items,
-// origins, hi/lo staging and the close-pair recomputation are those of
-// field_tiles; the difference is which tiles are visited.  The item's
-// candidate tiles (first, first + S, ...) are tested 256 at a time against
-// the targets' box, the ones within a are compacted into an LDS list, and
-// only those are staged and summed, each wave taking only the 16-source
-// groups of a staged tile that come within a of its own 64 targets.  A
-// group entirely within a of every target of the wave skips the per-pair
-// cutoff.  For loads below kNearMatrixMin holes (see launch_near).
+// Near part of the closure's split of Eq. (6) for loads below kNearMatrixMin
+// holes (see launch_near): the same sum over the sources closer than a only
+// (r^2 + eps^2 < a^2 + eps^2), in the difference form of field_tiles with its
+// origins, hi and lo parts and close-pair recomputation.  Chunk c of the sum holds
+// the source tiles c, c + S, c + 2 S, ..., at most kNearTiles of them.
+//
+// One wave per workgroup: 64 targets and one chunk, whose tiles are tested by
+// one lane each.  The 16-source groups of the tiles that come within a of the
+// wave's targets are listed (a group within a of them as a whole skips the
+// per-pair cutoff), and the wave stages four at a time, the next four's
+// positions in flight, and sums those that come within a of any of its targets.
+// The last test matters most for the holes at the cloud's edge, whose boxes are
+// large: without it their waves, the longest, set the time.  The sums of a tile
+// are taken before they meet those of other tiles.
+//
+// Four waves that shared whole staged tiles spent over half of their time at
+// barriers and in set-up: 5e4 holes 204 us, this kernel 93.  Two chunks per
+// wave 111 us, four 145 (fewer set-ups, longer waves); workgroups of four such
+// waves 97.
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(kFieldThreads) void near_tiles(FieldArgs a, const GridParams* gp) {
-    __shared__ __align__(16) float sh[2][6][kTile];
-    __shared__ double box[6][kFieldThreads / 64];
-    __shared__ double tbox[2][kBoxRows];  // the staged tile's boxes (tile, quarters, groups)
-    __shared__ uint32_t list[kFieldThreads];
-    __shared__ uint32_t wcount[kFieldThreads / 64];
+constexpr int kNearTiles = 8;
 
-    const FieldItem it = a.items[blockIdx.x];
-    const uint32_t off = a.ev_off[it.event];
-    const uint32_t ne = a.ev_off[it.event + 1] - off;
-    const uint32_t na = a.ev_active[it.event];
+__global__ __launch_bounds__(64) void near_waves(FieldArgs a, const GridParams* gp,
+                                                 uint32_t n_chunks) {
+    __shared__ __align__(16) float sh[2][6][64];
+    __shared__ __align__(16) float gbox[2][4][8];  // boxes of the staged groups
+    __shared__ uint16_t list[kNearTiles * 16];  // tile | group << 3 | inside << 7 | far << 8
+
+    const uint32_t nwaves = gridDim.x / n_chunks;
+    const uint32_t wave = blockIdx.x % nwaves;  // of the event's targets
+    const uint32_t chunk = blockIdx.x / nwaves;
+    const uint32_t ne = a.pstride, na = a.ev_active[0];
     const uint32_t nt = a.targets_all ? ne : na;
     const uint32_t ns = a.sources_all ? ne : na;
-    const uint32_t tbase = it.blk * (uint32_t)kFieldThreads;
-    if (tbase >= nt) return;
+    const uint32_t ts0 = wave * 64u, tbase = ts0 & ~(uint32_t)(kFieldThreads - 1);
+    if (ts0 >= nt) return;
     const uint32_t ntiles = (ns + kTile - 1) / kTile;
-    const uint32_t tile0 = a.ev_tile[it.event];
-    const uint32_t chunk = it.group;  // partial-sum group written
-    const uint32_t step_t = it.step;
-    const uint32_t t_first = it.first;
-    const uint32_t t_end = min(it.end, ntiles);
-    const int tid = threadIdx.x;
-    const int wave = tid >> 6, lane = tid & 63;
+    const int lane = threadIdx.x;
+    const uint32_t ts = ts0 + (uint32_t)lane;
+    const size_t st = a.tile_stride;
 
-    const uint32_t ts = tbase + (uint32_t)tid;
     double px = 0.0, py = 0.0, pz = 0.0;
-    double lo_x = INFINITY, lo_y = INFINITY, lo_z = INFINITY;
-    double hi_x = -INFINITY, hi_y = -INFINITY, hi_z = -INFINITY;
     if (ts < nt) {
-        px = a.px[off + ts];
-        py = a.py[off + ts];
-        pz = a.pz[off + ts];
-        lo_x = hi_x = px;
-        lo_y = hi_y = py;
-        lo_z = hi_z = pz;
+        px = a.px[ts];
+        py = a.py[ts];
+        pz = a.pz[ts];
     }
-    lo_x = wave_min(lo_x);
-    lo_y = wave_min(lo_y);
-    lo_z = wave_min(lo_z);
-    hi_x = wave_max(hi_x);
-    hi_y = wave_max(hi_y);
-    hi_z = wave_max(hi_z);
-    // this wave's own 64 targets, for culling source quarters
-    const double wl_x = uniform(lo_x), wl_y = uniform(lo_y), wl_z = uniform(lo_z);
-    const double wh_x = uniform(hi_x), wh_y = uniform(hi_y), wh_z = uniform(hi_z);
-    if (lane == 0) {
-        box[0][wave] = lo_x;
-        box[1][wave] = lo_y;
-        box[2][wave] = lo_z;
-        box[3][wave] = hi_x;
-        box[4][wave] = hi_y;
-        box[5][wave] = hi_z;
-    }
-    __syncthreads();
+    // The boxes of the 256-target block (its centre is the origin) and of this wave's
+    // targets, by which groups are culled: those of a source tile and its quarter
+    // where all 256 targets are sources.
+    double lo[3], hi[3], wl[3], wh[3];
+    if (tbase + (uint32_t)kFieldThreads <= min(nt, ns)) {
+        const double* tb = a.tile_box + tbase / kTile;
+        const uint32_t qr = (ts0 - tbase) / 64u;
 #pragma unroll
-    for (int w = 0; w < kFieldThreads / 64; ++w) {
-        lo_x = fmin(lo_x, box[0][w]);
-        lo_y = fmin(lo_y, box[1][w]);
-        lo_z = fmin(lo_z, box[2][w]);
-        hi_x = fmax(hi_x, box[3][w]);
-        hi_y = fmax(hi_y, box[4][w]);
-        hi_z = fmax(hi_z, box[5][w]);
+        for (int k = 0; k < 3; ++k) {
+            lo[k] = tb[k * st];
+            hi[k] = tb[(3 + k) * st];
+            wl[k] = tb[(6 + 4 * k + qr) * st];
+            wh[k] = tb[(6 + 4 * (3 + k) + qr) * st];
+        }
+    } else {
+        for (int k = 0; k < 3; ++k) {
+            const double* p = k == 0 ? a.px : k == 1 ? a.py : a.pz;
+            lo[k] = wl[k] = INFINITY;
+            hi[k] = wh[k] = -INFINITY;
+            for (uint32_t w = 0; w < kFieldThreads / 64; ++w) {
+                const uint32_t i = tbase + w * 64u + (uint32_t)lane;
+                if (i < nt) {
+                    const double v = p[i];
+                    lo[k] = fmin(lo[k], v);
+                    hi[k] = fmax(hi[k], v);
+                    if (i == ts) wl[k] = wh[k] = v;
+                }
+            }
+            lo[k] = wave_min(lo[k]);
+            hi[k] = wave_max(hi[k]);
+            wl[k] = wave_min(wl[k]);
+            wh[k] = wave_max(wh[k]);
+        }
     }
-    lo_x = uniform(lo_x);
-    lo_y = uniform(lo_y);
-    lo_z = uniform(lo_z);
-    hi_x = uniform(hi_x);
-    hi_y = uniform(hi_y);
-    hi_z = uniform(hi_z);
-    const double ox = 0.5 * (lo_x + hi_x), oy = 0.5 * (lo_y + hi_y), oz = 0.5 * (lo_z + hi_z);
-    const double hx = 0.5 * (hi_x - lo_x), hy = 0.5 * (hi_y - lo_y), hz = 0.5 * (hi_z - lo_z);
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        lo[k] = uniform(lo[k]);
+        hi[k] = uniform(hi[k]);
+        wl[k] = uniform(wl[k]);
+        wh[k] = uniform(wh[k]);
+    }
+    const double ox = 0.5 * (lo[0] + hi[0]), oy = 0.5 * (lo[1] + hi[1]), oz = 0.5 * (lo[2] + hi[2]);
+    const double hx = 0.5 * (hi[0] - lo[0]), hy = 0.5 * (hi[1] - lo[1]), hz = 0.5 * (hi[2] - lo[2]);
     const double rc2d = 0.0625 * (hx * hx + hy * hy + hz * hz);
     const double a2 = uniform(gp->a2);
     const float cut2 = uniform((float)gp->cut2);
 
-    float thx[1], thy[1], thz[1], tlx[1], tly[1], tlz[1], ax[1], ay[1], az[1], rc2[1];
+    const auto tile_of = [&](uint32_t l) { return chunk + l * n_chunks; };
+    const auto gap2_of = [&](const double* b, size_t s) {  // b: low x at b[0], ..., stride s
+        const double gx = fmax(0.0, fmax(b[0] - wh[0], wl[0] - b[3 * s]));
+        const double gy = fmax(0.0, fmax(b[s] - wh[1], wl[1] - b[4 * s]));
+        const double gz = fmax(0.0, fmax(b[2 * s] - wh[2], wl[2] - b[5 * s]));
+        return gx * gx + gy * gy + gz * gz;
+    };
+    uint64_t cand;  // tiles within a of the targets
+    {
+        const uint32_t t = tile_of((uint32_t)lane);
+        const bool have = lane < kNearTiles && t < ntiles;
+        cand = __ballot(have && gap2_of(a.tile_box + (have ? t : 0u), st) < a2);
+    }
+    // the groups of those tiles, four tiles at a time, sixteen lanes each
+    uint32_t n_list = 0;
+    while (cand) {
+        uint32_t l = 64u;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const uint32_t bit = cand ? (uint32_t)__builtin_ctzll(cand) : 64u;
+            cand &= cand - 1ull;
+            if ((lane >> 4) == k) l = bit;
+        }
+        const uint32_t grp = (uint32_t)lane & 15u, t = l < 64u ? tile_of(l) : 0u;
+        const double* gb = a.tile_box + (size_t)(30 + grp) * st + t;  // bound k at gb[16 k st]
+        const double gap2 = gap2_of(gb, 16 * st);
+        // largest distance between the boxes: every pair well inside a (a margin
+        // far above the FP32 error of r^2) needs no per-pair test
+        const double mx = fmax(gb[48 * st] - wl[0], wh[0] - gb[0]);
+        const double my = fmax(gb[64 * st] - wl[1], wh[1] - gb[16 * st]);
+        const double mz = fmax(gb[80 * st] - wl[2], wh[2] - gb[32 * st]);
+        const bool inside = mx * mx + my * my + mz * mz < 0.9999 * a2;
+        const bool keep = l < 64u && t * kTile + grp * 16u < ns && gap2 < a2;
+        const uint64_t who = __ballot(keep);
+        if (keep)
+            list[n_list + (uint32_t)__popcll(who & ((1ull << lane) - 1ull))] =
+                (uint16_t)(l | grp << 3 | (inside ? 1u << 7 : 0u) |
+                           (gap2 >= rc2d ? 1u << 8 : 0u));
+        n_list += (uint32_t)__popcll(who);
+    }
+    __syncthreads();
+
+    float thx[1], thy[1], thz[1], tlx[1], tly[1], tlz[1], rc2[1];
     {
         const double rx = px - ox, ry = py - oy, rz = pz - oz;
         thx[0] = (float)rx;
@@ -1504,163 +1554,132 @@ __global__ __launch_bounds__(kFieldThreads) void near_tiles(FieldArgs a, const G
         tlx[0] = (float)(rx - (double)thx[0]);
         tly[0] = (float)(ry - (double)thy[0]);
         tlz[0] = (float)(rz - (double)thz[0]);
-        ax[0] = ay[0] = az[0] = 0.0f;
         // close-pair radius of this target, as in field_tiles
         rc2[0] = ts < nt ? 0.0625f * (float)((double)thx[0] * thx[0] + (double)thy[0] * thy[0] +
                                              (double)thz[0] * thz[0])
                          : 0.0f;
     }
-
-    double qx = 0.0, qy = 0.0, qz = 0.0, qb = 0.0;
-    auto fetch = [&](uint32_t t) {
-        const uint32_t i = t * kTile + (uint32_t)tid;
+    double qx = 0.0, qy = 0.0, qz = 0.0;
+    double qb = 0.0;  // lanes 0-23: bound lane % 6 of the box of group lane / 6
+    const double ob = lane % 3 == 0 ? ox : lane % 3 == 1 ? oy : oz;  // its origin
+    auto fetch = [&](uint32_t i) {  // listed groups i .. i + 3
         qx = ox;
         qy = oy;
         qz = oz;
-        if (i < ns) {
-            qx = a.px[off + i];
-            qy = a.py[off + i];
-            qz = a.pz[off + i];
+        const uint32_t e = i + (uint32_t)(lane >> 4);
+        if (e < n_list) {
+            const uint32_t v = list[e];
+            const uint32_t j =
+                tile_of(v & 7u) * kTile + ((v >> 3) & 15u) * 16u + ((uint32_t)lane & 15u);
+            if (j < ns) {
+                qx = a.px[j];
+                qy = a.py[j];
+                qz = a.pz[j];
+            }
         }
-        if (tid < kBoxRows) qb = a.tile_box[(size_t)tid * a.tile_stride + tile0 + t];
+        const uint32_t eb = i + (uint32_t)lane / 6u;
+        if (lane < 24 && eb < n_list) {
+            const uint32_t v = list[eb];
+            qb = a.tile_box[(size_t)(30u + 16u * ((uint32_t)lane % 6u) + ((v >> 3) & 15u)) * st +
+                            tile_of(v & 7u)];
+        }
     };
     auto stage = [&](int b) {
-        if (tid < kBoxRows) tbox[b][tid] = qb;
+        if (lane < 24) gbox[b][lane / 6][lane % 6] = (float)(qb - ob);
         const double rx = qx - ox, ry = qy - oy, rz = qz - oz;
         const float fx = (float)rx, fy = (float)ry, fz = (float)rz;
-        sh[b][0][tid] = fx;
-        sh[b][1][tid] = fy;
-        sh[b][2][tid] = fz;
-        sh[b][3][tid] = (float)(rx - (double)fx);
-        sh[b][4][tid] = (float)(ry - (double)fy);
-        sh[b][5][tid] = (float)(rz - (double)fz);
+        sh[b][0][lane] = fx;
+        sh[b][1][lane] = fy;
+        sh[b][2][lane] = fz;
+        sh[b][3][lane] = (float)(rx - (double)fx);
+        sh[b][4][lane] = (float)(ry - (double)fy);
+        sh[b][5][lane] = (float)(rz - (double)fz);
     };
-
-    const uint32_t ncand = t_first < t_end ? (t_end - t_first + step_t - 1) / step_t : 0u;
-    for (uint32_t base = 0; base < ncand; base += kFieldThreads) {
-        // 1. which of the next 256 candidate tiles come within a of the targets
-        const uint32_t m = base + (uint32_t)tid;
-        bool keep = false;
-        uint32_t t = 0;
-        if (m < ncand) {
-            t = t_first + m * step_t;
-            const size_t g = (size_t)tile0 + t;
-            const double* tb = a.tile_box;
-            const size_t st = a.tile_stride;
-            const double gx = fmax(0.0, fmax(tb[0 * st + g] - hi_x, lo_x - tb[3 * st + g]));
-            const double gy = fmax(0.0, fmax(tb[1 * st + g] - hi_y, lo_y - tb[4 * st + g]));
-            const double gz = fmax(0.0, fmax(tb[2 * st + g] - hi_z, lo_z - tb[5 * st + g]));
-            keep = gx * gx + gy * gy + gz * gz < a2;
-        }
-        // 2. compact them, in candidate order, into the LDS list
-        const uint64_t bal = __ballot(keep);
-        if (lane == 0) wcount[wave] = (uint32_t)__popcll(bal);
+    // of FP32 coordinates, with a margin far above their rounding
+    const float near_a2 = uniform((float)(1.001 * a2));
+    float ax = 0.0f, ay = 0.0f, az = 0.0f;
+    float bx[1] = {0.0f}, by[1] = {0.0f}, bz[1] = {0.0f};
+    uint32_t tile = 0u;  // (its number in the chunk) whose sums b holds
+    auto end_tile = [&]() {
+        ax += bx[0];
+        ay += by[0];
+        az += bz[0];
+        bx[0] = by[0] = bz[0] = 0.0f;
+    };
+    int buf = 0;
+    fetch(0u);
+    for (uint32_t i = 0; i < n_list; i += 4u) {
+        stage(buf);
         __syncthreads();
-        uint32_t before = 0, total = 0;
-#pragma unroll
-        for (int w = 0; w < kFieldThreads / 64; ++w) {
-            const uint32_t cw = wcount[w];
-            if (w < wave) before += cw;
-            total += cw;
-        }
-        if (keep) list[before + (uint32_t)__popcll(bal & ((1ull << lane) - 1ull))] = t;
-        __syncthreads();
-        // 3. the kept tiles, double buffered as in field_tiles
-        int buf = 0;
-        if (total > 0) {
-            fetch(list[0]);
-            stage(0);
-        }
-        __syncthreads();
-        for (uint32_t q = 0; q < total; ++q) {
-            const uint32_t tt = list[q];
-            const bool more = q + 1 < total;
-            if (more) fetch(list[q + 1]);
-            const uint32_t cnt = min((uint32_t)kTile, ns - tt * kTile);
-            float bx[1] = {0.0f}, by[1] = {0.0f}, bz[1] = {0.0f};
-            const double* tb = tbox[buf];
-            // each wave takes the 16-source groups of the tile within a of its
-            // own targets: lane l tests group l % 16 (three ballots collect the
-            // answers), then the wave sums the groups that pass, one by one
-            uint32_t cand, in_m, far_m;
-            {
-                const int grp = lane & 15;
-                const double* gb = tb + 30 + grp;  // bound k of the group at gb[16 k]
-                const double gx = fmax(0.0, fmax(gb[0] - wh_x, wl_x - gb[48]));
-                const double gy = fmax(0.0, fmax(gb[16] - wh_y, wl_y - gb[64]));
-                const double gz = fmax(0.0, fmax(gb[32] - wh_z, wl_z - gb[80]));
-                const double gap2 = gx * gx + gy * gy + gz * gz;
-                // largest distance between the boxes: every pair well inside a
-                // (a margin far above the FP32 error of r^2) needs no per-pair test
-                const double mx = fmax(gb[48] - wl_x, wh_x - gb[0]);
-                const double my = fmax(gb[64] - wl_y, wh_y - gb[16]);
-                const double mz = fmax(gb[80] - wl_z, wh_z - gb[32]);
-                const bool valid = (uint32_t)grp * 16u < cnt;
-                cand = (uint32_t)__ballot(valid && gap2 < a2) & 0xFFFFu;
-                in_m = (uint32_t)__ballot(mx * mx + my * my + mz * mz < 0.9999 * a2) & 0xFFFFu;
-                far_m = (uint32_t)__ballot(gap2 >= rc2d) & 0xFFFFu;
+        fetch(i + 4u);
+        const uint32_t m = min(4u, n_list - i);
+        for (uint32_t u = 0; u < m; ++u) {
+            const uint32_t v = (uint32_t)__builtin_amdgcn_readfirstlane((int)list[i + u]);
+            {  // no target of the wave within a of the group's box: no term
+                const f32x4 g0 = *reinterpret_cast<const f32x4*>(&gbox[buf][u][0]);
+                const float g4 = gbox[buf][u][4], g5 = gbox[buf][u][5];
+                const float gx = fmaxf(0.0f, fmaxf(g0[0] - thx[0], thx[0] - g0[3]));
+                const float gy = fmaxf(0.0f, fmaxf(g0[1] - thy[0], thy[0] - g4));
+                const float gz = fmaxf(0.0f, fmaxf(g0[2] - thz[0], thz[0] - g5));
+                if (!__any(ts < nt && gx * gx + gy * gy + gz * gz < near_a2)) continue;
             }
-            while (cand) {
-                const int grp = __builtin_ctz(cand);
-                cand &= cand - 1u;
-                const uint32_t k0 = (uint32_t)grp * 16u;
-                const uint32_t kn = min(16u, cnt - k0);
-                const bool inside = (in_m >> grp) & 1u;
-                const bool far_q = (far_m >> grp) & 1u;
-                const float* hxp = sh[buf][0] + k0;
-                const float* hyp = sh[buf][1] + k0;
-                const float* hzp = sh[buf][2] + k0;
-                const float* lxp = sh[buf][3] + k0;
-                const float* lyp = sh[buf][4] + k0;
-                const float* lzp = sh[buf][5] + k0;
-                if (inside) {
-                    if (far_q)
-                        tile_terms<1, kDiffHi, false>(hxp, hyp, hzp, lxp, lyp, lzp, kn, thx, thy,
-                                                      thz, tlx, tly, tlz, a.eps2, rc2, bx, by, bz);
-                    else
-                        tile_terms<1, kDiffNear, false>(hxp, hyp, hzp, lxp, lyp, lzp, kn, thx, thy,
-                                                        thz, tlx, tly, tlz, a.eps2, rc2, bx, by,
-                                                        bz);
-                } else {
-                    if (far_q)
-                        tile_terms<1, kDiffHi, true>(hxp, hyp, hzp, lxp, lyp, lzp, kn, thx, thy,
-                                                     thz, tlx, tly, tlz, a.eps2, rc2, bx, by, bz,
-                                                     cut2);
-                    else
-                        tile_terms<1, kDiffNear, true>(hxp, hyp, hzp, lxp, lyp, lzp, kn, thx, thy,
-                                                       thz, tlx, tly, tlz, a.eps2, rc2, bx, by, bz,
-                                                       cut2);
-                }
+            if ((v & 7u) != tile) {
+                end_tile();
+                tile = v & 7u;
             }
-            ax[0] += bx[0];
-            ay[0] += by[0];
-            az[0] += bz[0];
-            if (more) stage(buf ^ 1);
-            __syncthreads();
-            buf ^= 1;
+            const uint32_t j0 = tile_of(tile) * kTile + ((v >> 3) & 15u) * 16u;
+            const uint32_t kn = min(16u, ns - j0);
+            const float* hxp = sh[buf][0] + u * 16u;
+            const float* hyp = sh[buf][1] + u * 16u;
+            const float* hzp = sh[buf][2] + u * 16u;
+            const float* lxp = sh[buf][3] + u * 16u;
+            const float* lyp = sh[buf][4] + u * 16u;
+            const float* lzp = sh[buf][5] + u * 16u;
+            const bool inside = (v >> 7) & 1u, far = (v >> 8) & 1u;
+            if (inside) {
+                if (far)
+                    tile_terms<1, kDiffHi, false>(hxp, hyp, hzp, lxp, lyp, lzp, kn, thx, thy, thz,
+                                                  tlx, tly, tlz, a.eps2, rc2, bx, by, bz);
+                else
+                    tile_terms<1, kDiffNear, false>(hxp, hyp, hzp, lxp, lyp, lzp, kn, thx, thy, thz,
+                                                    tlx, tly, tlz, a.eps2, rc2, bx, by, bz);
+            } else {
+                if (far)
+                    tile_terms<1, kDiffHi, true>(hxp, hyp, hzp, lxp, lyp, lzp, kn, thx, thy, thz,
+                                                 tlx, tly, tlz, a.eps2, rc2, bx, by, bz, cut2);
+                else
+                    tile_terms<1, kDiffNear, true>(hxp, hyp, hzp, lxp, lyp, lzp, kn, thx, thy, thz,
+                                                   tlx, tly, tlz, a.eps2, rc2, bx, by, bz, cut2);
+            }
         }
+        buf ^= 1;
     }
-
+    end_tile();
     if (ts < nt) {
-        a.part[(size_t)(chunk * 3 + 0) * a.pstride + off + ts] = ax[0];
-        a.part[(size_t)(chunk * 3 + 1) * a.pstride + off + ts] = ay[0];
-        a.part[(size_t)(chunk * 3 + 2) * a.pstride + off + ts] = az[0];
+        a.part[(size_t)(chunk * 3 + 0) * a.pstride + ts] = ax;
+        a.part[(size_t)(chunk * 3 + 1) * a.pstride + ts] = ay;
+        a.part[(size_t)(chunk * 3 + 2) * a.pstride + ts] = az;
     }
 }
 
-// The matrix kernel for loads of at least kNearMatrixMin holes.  Below, the
-// network's launches bound the closure step (0.32 of 0.6 ms at 5e4 holes, where
-// the difference-form kernel costs 0.1 ms per step more), while the FP32
-// rounding of the near sum of a close pair, which the order of summation sets,
-// grows along a run: the smaller loads, which the closure runs for many steps, keep the
-// difference form and its order.
+// The matrix kernel for loads of at least kNearMatrixMin holes.  Below, near_waves
+// is faster (the closure's field at 5e4 holes 0.21 ms with it, 0.28 with the
+// matrix kernel), and the FP32 rounding of the near sum of a close pair,
+// which the order of summation sets, grows along a run: the smaller loads, which
+// the closure runs for many steps, keep the difference form and its order.
 hipError_t launch_near(const FieldArgs& a, const GridParams* gp, uint32_t n, uint32_t n_items,
-                       hipStream_t s) {
+                       uint32_t n_chunks, hipStream_t s) {
     if (n_items == 0) return hipSuccess;
-    if (n >= (uint32_t)kNearMatrixMin)
+    if (n >= (uint32_t)kNearMatrixMin) {
         near_matrix<<<n_items, kFieldThreads, 0, s>>>(a, gp);
-    else
-        near_tiles<<<n_items, kFieldThreads, 0, s>>>(a, gp);
+        return hipGetLastError();
+    }
+    // one event, and no chunk of more than kNearTiles tiles
+    const uint32_t tiles = (n + kTile - 1) / kTile;
+    if (a.pstride != n || n_chunks == 0 || tiles > n_chunks * (uint32_t)kNearTiles)
+        return hipErrorInvalidValue;
+    const uint32_t waves = n_items / n_chunks * (kFieldThreads / 64);
+    near_waves<<<waves * n_chunks, 64, 0, s>>>(a, gp, n_chunks);
     return hipGetLastError();
 }
 
