@@ -1,0 +1,39 @@
+"""The three ways of sorting a list of keys (counted places, tiles merged in one
+launch, tiles merged level by level), at the edges of their ranges and with
+part tiles.  A step moves exactly the holes that the list names, so a key lost
+or doubled by the sort of the load (unsorted keys) or by a step's (sorted runs
+of 256) shows as a hole that stands still in the next step; and the field of the
+whole load has to be the oracle's."""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("n", [1, 15, 17, 512, 513, 12288, 12289, 20480, 61441, 65536, 65537])
+def test_every_hole_listed(n):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import oracle
+    from paper_2203_11043_amd import gccd as g
+    from paper_2203_11043_amd import workloads as W
+
+    p = W.gaussian_cloud(n, W.cloud_sigma(max(n, 100)), (480.0, 480.0, 300.0), 31, stream=n)
+    ctx = g.gccd_init(g.Params.from_device(dict(W.DEVICE)))
+    try:
+        g.gccd_load(ctx, *[torch.as_tensor(np.ascontiguousarray(v)).cuda() for v in p])
+        E = g.gccd_field(ctx, n).cpu().numpy()
+        last = g.gccd_positions(ctx, n)[0].cpu().numpy()
+        # the load's list, the list after kept steps, and the lists that steps sorted
+        for steps in (1, 15, 1, 1, 15):
+            g.gccd_run(ctx, 10.0, steps)
+            pos = g.gccd_positions(ctx, n)[0].cpu().numpy()
+            assert np.all(np.any(pos != last, axis=0))
+            last = pos
+    finally:
+        g.gccd_destroy(ctx)
+    idx = np.random.default_rng(2).choice(n, min(n, 200), replace=False)
+    Eo, A = oracle.field([v[idx] for v in p], list(p), with_magnitude=True)
+    assert np.all(np.linalg.norm(E[:, idx] - Eo, axis=0) <= 1e-5 * A + 1e-9)
