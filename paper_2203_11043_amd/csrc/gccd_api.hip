@@ -1753,6 +1753,8 @@ int gccd_run(gccd_ctx* c, double dt_ps, int64_t max_steps, int64_t* steps_done,
         }
         sa.step = s;  // the whole stretch in one launch
         sa.n_steps = (uint32_t)stretch;
+        sa.holes = (unsigned long long)bound;
+        sa.counts = reinterpret_cast<DriftCounts*>(c->ukeys[0]);  // no list: free
         GCCD_HIP(c, launch_step(sa, n, c->stream));
         return GCCD_OK;
     };
@@ -1762,6 +1764,7 @@ int gccd_run(gccd_ctx* c, double dt_ps, int64_t max_steps, int64_t* steps_done,
                            graph_cap(c) > 0;
 
     const StepArgs sa0 = sa;  // before a step's own fields
+    int64_t last = step0;     // after the last busy step
     int64_t k = 0;
     while (k < max_steps && bound > 0) {
         // stretches end at multiples of kPoll (a call that starts between
@@ -1821,8 +1824,11 @@ int gccd_run(gccd_ctx* c, double dt_ps, int64_t max_steps, int64_t* steps_done,
             if (r != GCCD_OK) return r;
         }
         bound = c->host_meta[kMetaCount + (c->list_mode ? (uint32_t)(step0 + k) % 3u : 0u)];
+        // without repulsion the device knows the last busy step once no hole travels
+        last = !c->list_mode && bound > 0 ? step0 + k
+                                          : (int64_t)(uint32_t)c->host_meta[kMetaLast];
         if (c->host_meta[kMetaFlag] != 0) {
-            c->step = (int64_t)(uint32_t)c->host_meta[kMetaLast];
+            c->step = last;
             c->n_active = bound;
             c->loaded = false;
             return fail(c, GCCD_E_NONFINITE,
@@ -1844,7 +1850,6 @@ int gccd_run(gccd_ctx* c, double dt_ps, int64_t max_steps, int64_t* steps_done,
     }
     // The step after the last one that moved a hole: later steps found no hole
     // travelling and left the state unchanged.
-    const int64_t last = (k > 0) ? (int64_t)(uint32_t)c->host_meta[kMetaLast] : step0;
     c->step = (last > step0) ? last : step0;
     c->n_active = bound;
     if (use_closure) c->closure_steps += c->step - step0;

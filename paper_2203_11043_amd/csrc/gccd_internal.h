@@ -93,6 +93,13 @@ struct FieldArgs {
 constexpr double kExactRadius = 64.0;
 constexpr int kExactShift = 40;
 
+// What a workgroup of the carrier mode's launch counted of the holes it collected.
+struct DriftCounts {
+    unsigned long long missed;  // steps of the launch after their collection, in all
+    uint32_t last;              // steps until the last of them
+    uint32_t gone;              // their number
+};
+
 // Everything the per-carrier update of one step needs.
 struct StepArgs {
     double* x;
@@ -131,6 +138,8 @@ struct StepArgs {
     const uint32_t* step_base; // list mode: device word added to step (a graph replays
                                // the same arguments at a new base)
     uint32_t n_steps;          // carrier mode: steps of the launch
+    unsigned long long holes;  // carrier mode: travelling holes at its start
+    DriftCounts* counts;       // carrier mode: scratch, one per 256 carriers
     uint32_t event0;          // Philox event word of event 0
     uint32_t key0, key1;
     uint32_t* cnt_ring;       // [3] travelling holes at the start of step s in [s % 3]
@@ -140,6 +149,7 @@ struct StepArgs {
     double close_unit;          // um^-2 per fixed-point unit of close
     unsigned long long* stats;  // [0] carrier-steps, [1] pair interactions
     int32_t* misc;              // [0] non-finite flag, [1] step after the last busy one
+                                // (carrier mode: after the last collection)
     int32_t keep;               // list mode, every hole a source: the list's order stays,
                                 // and the step writes the new positions to px, py, pz
                                 // and the boxes of its tiles itself

@@ -2318,6 +2318,9 @@ __device__ __forceinline__ void move_hole(const StepArgs& a, uint32_t step, uint
     if (z > a.thickness) z = 2.0 * a.thickness - z;
 }
 
+constexpr int kDriftSum = 1024;
+constexpr uint32_t kDriftAtomics = 256;
+
 // The step's modes: list mode (a.list_mode, Coulomb on) leaving the new keys for
 // a sort of their own, rebuilding the list itself (a.arrive) or keeping the
 // list's order (a.keep).  Carrier mode is a kernel of its own (drift_steps).
@@ -2563,15 +2566,48 @@ __global__ __launch_bounds__(kStepThreads) void step_update(StepArgs a) {
     step_body<MODE>(a);
 }
 
+// The counts of a workgroup's lanes (missed, last) and waves (gone, the same in every
+// lane), left in *out or, where that is NULL, added to the load's.
+__device__ __forceinline__ void add_drift_counts(const StepArgs& a, DriftCounts c,
+                                                 DriftCounts* out) {
+    __shared__ DriftCounts wave[kDriftSum / 64];
+    if (c.gone) {  // wave-uniform
+#pragma unroll
+        for (int m = 32; m >= 1; m >>= 1) {
+            c.missed += __shfl_xor(c.missed, m);
+            c.last = max(c.last, (uint32_t)__shfl_xor((int)c.last, m));
+        }
+    }
+    if ((threadIdx.x & 63u) == 0) wave[threadIdx.x >> 6] = c;
+    __syncthreads();
+    if (threadIdx.x != 0) return;
+    for (uint32_t w = 1; w < blockDim.x / 64u; ++w) {
+        c.missed += wave[w].missed;
+        c.last = max(c.last, wave[w].last);
+        c.gone += wave[w].gone;
+    }
+    if (out) {
+        *out = c;
+        return;
+    }
+    // every hole that travelled at the start counts as moved in every step
+    if (blockIdx.x == 0) atomicAdd(&a.stats[0], a.holes * a.n_steps);
+    if (c.gone) {
+        atomicAdd(&a.stats[0], 0ull - c.missed);
+        atomicMax(reinterpret_cast<uint32_t*>(&a.misc[1]), a.step + c.last);
+        atomicSub(a.cnt_ring, c.gone);
+    }
+}
+
 // a.n_steps steps without repulsion: holes do not see each other, so each
 // stays in its thread's registers over all of them.  Bound by VALU issue: about
 // 300 FP64 instructions per hole and step.  One launch per step read and wrote
 // 52 B per hole each time and stopped at the launch's end: 8 million holes
 // 207 us per step, now 104; 1,000 holes 4.4 us, now 1.5.
 __global__ __launch_bounds__(kStepThreads) void drift_steps(StepArgs a) {
-    const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x >> 6;
-    unsigned long long moved = 0;   // carrier-steps of this lane
-    uint32_t last = 0, gone = 0;    // steps until its last hole stopped; holes collected (wave)
+    unsigned long long missed = 0;  // of this lane's collected holes: steps after that,
+    uint32_t last = 0;              // and the last one's step
+    uint32_t gone = 0;              // holes collected (wave)
     for (uint32_t base = blockIdx.x * kStepThreads; base < a.n_all;
          base += gridDim.x * kStepThreads) {
         const uint32_t j = base + threadIdx.x;
@@ -2603,39 +2639,31 @@ __global__ __launch_bounds__(kStepThreads) void drift_steps(StepArgs a) {
             a.z[j] = z;
             // a coordinate once infinite or NaN never becomes finite again
             if (!isfinite(x) || !isfinite(y) || !isfinite(z)) atomicOr(&a.misc[0], 1);
-            if (!active) a.cstep[j] = (int32_t)(a.step + done);
-            moved += done;
-            last = max(last, done);
+            if (!active) {
+                a.cstep[j] = (int32_t)(a.step + done);
+                missed += a.n_steps - done;
+                last = max(last, done);
+            }
         }
         gone += (uint32_t)__popcll(__ballot(was && !active));
     }
-    // one atomic per workgroup for each count: a counter taking one per wave
-    // and grid-stride turn (2.6e5 at 2^24 holes) serialised the whole step
+    add_drift_counts(a, DriftCounts{missed, last, gone},
+                     a.counts ? a.counts + blockIdx.x : nullptr);
+}
+
+// The sum of the workgroups' counts.
+__global__ __launch_bounds__(kDriftSum) void drift_counts(StepArgs a, uint32_t n_counts) {
+    DriftCounts c{0ull, 0u, 0u};
+#pragma unroll 4
+    for (uint32_t i = threadIdx.x; i < n_counts; i += kDriftSum) {
+        c.missed += a.counts[i].missed;
+        c.last = max(c.last, a.counts[i].last);
+        c.gone += a.counts[i].gone;
+    }
+    // add_drift_counts takes a wave's `gone` from its first lane
 #pragma unroll
-    for (int m = 32; m >= 1; m >>= 1) {
-        moved += __shfl_xor(moved, m);
-        last = max(last, (uint32_t)__shfl_xor((int)last, m));
-    }
-    __shared__ unsigned long long wave_moved[kStepThreads / 64];
-    __shared__ uint32_t wave_last[kStepThreads / 64], wave_gone[kStepThreads / 64];
-    if (lane == 0) {
-        wave_moved[wave] = moved;
-        wave_last[wave] = last;
-        wave_gone[wave] = gone;
-    }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        for (int w = 1; w < kStepThreads / 64; ++w) {
-            moved += wave_moved[w];
-            last = max(last, wave_last[w]);
-            gone += wave_gone[w];
-        }
-        if (moved) {
-            atomicAdd(&a.stats[0], moved);
-            atomicMax(reinterpret_cast<uint32_t*>(&a.misc[1]), a.step + last);
-        }
-        if (gone) atomicSub(a.cnt_ring, gone);
-    }
+    for (int m = 32; m >= 1; m >>= 1) c.gone += (uint32_t)__shfl_xor((int)c.gone, m);
+    add_drift_counts(a, c, nullptr);
 }
 
 hipError_t launch_step(const StepArgs& a, uint32_t n_slots, hipStream_t s) {
@@ -2655,7 +2683,15 @@ hipError_t launch_step(const StepArgs& a, uint32_t n_slots, hipStream_t s) {
         step_update<kStepList>
             <<<grid_for(n_slots, kStepThreads, 16384), kStepThreads, 0, s>>>(a);
     } else {
-        drift_steps<<<grid_for(n_slots, kStepThreads, 1 << 16), kStepThreads, 0, s>>>(a);
+        const uint32_t grid = grid_for(n_slots, kStepThreads, 16384);
+        StepArgs d = a;
+        // Atomics of many workgroups on the same words queue up (8 ns each): with
+        // a set per workgroup a single step of 8 million holes took 755 us.  Above
+        // kDriftAtomics workgroups each leaves its counts in memory and a second
+        // launch (3 us) adds them: 157 us.
+        if (grid <= kDriftAtomics) d.counts = nullptr;
+        drift_steps<<<grid, kStepThreads, 0, s>>>(d);
+        if (d.counts) drift_counts<<<1, kDriftSum, 0, s>>>(d, grid);
     }
     return hipGetLastError();
 }

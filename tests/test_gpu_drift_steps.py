@@ -2,7 +2,8 @@
 thread's registers.  Whatever the split of a run, positions, collection steps and
 the counts of the statistics are the same; with holes collected on the way, on
 both sides of a workgroup's and a 32-step stretch's edge, for one event and
-several; and the travelling count and the last busy step are those that the
+several, with the counts added by the workgroups or (above 65536 holes) by a
+second launch; and the travelling count and the last busy step are those that the
 collection steps say."""
 import numpy as np
 import pytest
@@ -12,7 +13,7 @@ torch = pytest.importorskip("torch")
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("sizes", [[1], [63], [257], [5000], [1, 300, 700]],
+@pytest.mark.parametrize("sizes", [[1], [63], [257], [5000], [1, 300, 700], [65536], [65537]],
                          ids=lambda s: "-".join(map(str, s)))
 def test_split_runs(sizes):
     if not torch.cuda.is_available():
