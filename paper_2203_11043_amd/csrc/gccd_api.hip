@@ -29,9 +29,9 @@ constexpr double kPi = 3.14159265358979323846;
 constexpr int kPoll = 32;                       // steps between host reads of the counts
 // Steps that one order of a serial list serves (every hole a source).  The order
 // sets only which holes share blocks and boxes, never which are summed; keeping
-// it saves the sort (24 us with the step of a load of 1,000 holes, 31 us of
-// launches after it at 10,000) and costs the Eq. (6) kernel some of its far
-// blocks as holes move apart.  us per step, order kept 1, 4, 8, 16, 32 steps:
+// it saves the sort and the gather after it and costs the Eq. (6) kernel some
+// of its far blocks as holes move apart.  us per step, order kept 1, 4, 8, 16, 32
+// steps (measured with sorts that took about twice as long):
 //   1,000 holes  37.3 23.9 21.8 19.2 20.4     30,000  274 245 248 267 308
 //   10,007       94.9 67.9 64.7 64.6 69.9     70,000  1054 1041 1071 1152 1146
 // With longer steps holes part sooner.  Steps of 160 and 1000 ps, order kept 1, 4
@@ -66,7 +66,6 @@ enum : int {
     kSchedQueue = 0,  // persistent launch: next work item
     kSchedItems = 1,  // persistent launch: work items in the list
     kSchedStep = 2,   // list mode: step index of the first step of the current stretch
-    kSchedArrive = 3, // a small load's step kernel: its workgroups arrived (zero between)
     kSchedWords = 4
 };
 
@@ -83,7 +82,7 @@ struct GraphKey {
     StepArgs step;
     size_t items_cap;
     int64_t keep_steps;
-    int tpt, precision, cur, u, pipelined, sorting, keep_ok, fused;
+    int tpt, precision, cur, u, pipelined, sorting, keep_ok;
 };
 
 }  // namespace
@@ -1596,17 +1595,13 @@ int gccd_run(gccd_ctx* c, double dt_ps, int64_t max_steps, int64_t* steps_done,
     sa.stats = reinterpret_cast<unsigned long long*>(c->meta + kMetaStats);
     sa.misc = reinterpret_cast<int32_t*>(c->meta + kMetaFlag);
 
-    // A small load's step kernel rebuilds the list itself where the step sorts
-    // (its last workgroup sorts, counts and gathers: two launches per step).  Other
-    // exact steps with every hole a source are pipelined (see gccd_ctx::keys)
+    // Exact steps with every hole a source are pipelined (see gccd_ctx::keys)
     // while their pair work hides the sort (kPipeMinPairs); the others need
     // the list of the positions they run over.  The choice is made at load
     // and at every step that is a multiple of kPoll (the polls are aligned to
     // those steps), from the counts there, so a run gives the same bits however
     // it is split into calls.
-    const bool fused = c->list_mode && !use_closure && n <= (uint32_t)kFusedList &&
-                       c->n_tiles <= (uint32_t)kFusedTiles;
-    const bool pipe_ok = !fused && c->list_mode && !use_closure && c->p.collected_are_sources;
+    const bool pipe_ok = c->list_mode && !use_closure && c->p.collected_are_sources;
     auto decide_pipe = [&]() -> int {
         if (!pipe_ok) return 0;
         double pairs = 0.0;
@@ -1713,22 +1708,16 @@ int gccd_run(gccd_ctx* c, double dt_ps, int64_t max_steps, int64_t* steps_done,
             // a serial list: the step kernel's workgroups sort their slots'
             // keys into runs, so the sort only merges them (the side stream's
             // sort of a pipelined list overlaps the field and gains nothing)
-            sa.sort_runs = (!fused && !pipelined) ? 1 : 0;
+            sa.sort_runs = !pipelined ? 1 : 0;
             sa.ev_active = c->ev_active_d[c->cur];
             sa.keep = keep_ok && !pipelined && (first + i + 1) % keep_steps != 0 ? 1 : 0;
             c->kept = sa.keep != 0;
             c->gathered = true;
-            sa.arrive = fused ? c->sched + kSchedArrive : nullptr;
             if (c->kept) {
                 GCCD_HIP(c, launch_step(sa, n, c->stream));
                 return GCCD_OK;
             }
-            if (fused) {  // the kernel leaves the next step's list in place of this one's
-                sa.keys_sorted = c->keys[c->cur];
-                sa.ev_active_out = c->ev_active_d[c->cur];
-            }
             GCCD_HIP(c, launch_step(sa, n, c->stream));
-            if (fused) return GCCD_OK;
             if (!pipelined)  // the next step's list, from the runs the step kernel sorted
                 return finish_list(c, c->ukeys[c->u], kStepThreads);
             // The list of the new positions is sorted on the side stream while
@@ -1796,7 +1785,6 @@ int gccd_run(gccd_ctx* c, double dt_ps, int64_t max_steps, int64_t* steps_done,
             key.pipelined = pipelined ? 1 : 0;
             key.sorting = c->sorting ? 1 : 0;
             key.keep_ok = keep_ok ? 1 : 0;
-            key.fused = fused ? 1 : 0;
             if (c->graph_exec && memcmp(&key, &c->graph_key, sizeof key) != 0) drop_graph(c);
             if (!c->graph_exec) {
                 int r = capture_steps(c, issue);

@@ -2098,147 +2098,9 @@ __device__ __forceinline__ double unit_open(uint32_t w) {
 //     collected holes copying theirs through; the next sort restores order.
 //   kept list (a.keep): one workgroup per source tile, one thread per slot.  The
 //     order stays, so no key is made or sorted: the step writes the slots' new
-//     positions and its tile's boxes.  1,000 holes, latency-bound: 7.1 us, with
-//     the rebuilt list 24.4.
+//     positions and its tile's boxes.  1,000 holes, latency-bound: 7.1 us.
 //   carrier mode: drift_steps.
 // ---------------------------------------------------------------------------
-// The list of a load of at most kFusedList carriers in at most kFusedTiles
-// source tiles, rebuilt by the last workgroup of its step: the new keys,
-// which each workgroup of the step left as a sorted run of its slots
-// (sort_block_keys), merged in LDS (merge_sorted_runs), each event's
-// travelling holes (its first collected key, by binary search in LDS), and
-// the positions and boxes of every source tile in slot order -- the same
-// list, counts, slots and boxes as sort_keys, count_active and
-// gather_tiles.  The positions are gathered four slots per thread with all
-// their loads in flight and kept in LDS; the boxes are then reduced by one
-// thread per 16-slot group, per 64-slot quarter and per tile.
-__device__ __forceinline__ void build_small_list(const StepArgs& a) {
-    __shared__ uint64_t s[kFusedList + kFusedList / kSortItems];
-    __shared__ uint32_t act[kFusedList];
-    const uint32_t n = a.n_all;
-    // the step's workgroups left sorted runs of kStepThreads keys
-    if (n <= (uint32_t)kFusedList / 2)
-        merge_sorted_runs<kFusedList / 2 / kSortItems>(a.keys_out, n, s, kStepThreads);
-    else
-        merge_sorted_runs<kFusedList / kSortItems>(a.keys_out, n, s, kStepThreads);
-    for (uint32_t i = threadIdx.x; i < n; i += kStepThreads) a.keys_sorted[i] = s[lds_slot(i)];
-    for (uint32_t e = threadIdx.x; e < a.n_events; e += kStepThreads) {
-        const uint32_t off = a.one_event ? 0u : a.ev_off[e];
-        const uint32_t ne = a.one_event ? n : a.ev_off[e + 1] - off;
-        uint32_t lo = 0, hi = ne;  // first collected key of the segment in [lo, hi]
-        while (lo < hi) {
-            const uint32_t mid = (lo + hi) >> 1;
-            if (key_collected(s[lds_slot(off + mid)], a.kl))
-                hi = mid;
-            else
-                lo = mid + 1;
-        }
-        act[e] = lo;
-        a.ev_active_out[e] = lo;
-    }
-    __syncthreads();
-    // positions of every tile slot (tile g, slot w at g kTile + w), gathered
-    // four per thread with all loads in flight, kept in LDS with a flag for
-    // the slots that are sources
-    __shared__ double gp[3][kFusedTiles * kTile];
-    __shared__ uint8_t gsrc[kFusedTiles * kTile];
-    __shared__ double gbox[kFusedTiles * (kTile / 16)][6];
-    const uint32_t nq = a.n_tiles * (uint32_t)kTile;
-    constexpr uint32_t kBatch = 4;
-    for (uint32_t q0 = threadIdx.x; q0 < nq; q0 += kBatch * kStepThreads) {
-        double v[kBatch][3];
-        bool src[kBatch], in[kBatch];
-        uint32_t dst[kBatch];
-#pragma unroll
-        for (uint32_t b = 0; b < kBatch; ++b) {
-            const uint32_t q = q0 + b * kStepThreads;
-            v[b][0] = v[b][1] = v[b][2] = 0.0;
-            src[b] = in[b] = false;
-            dst[b] = 0;
-            if (q < nq) {
-                const uint32_t g = q / kTile, w = q % kTile;
-                // a single event's tiles start at slot 0 (no lookups)
-                const uint32_t e = a.one_event ? 0u : a.tile_event[g];
-                const uint32_t off = a.one_event ? 0u : a.ev_off[e];
-                const uint32_t ne = a.one_event ? n : a.ev_off[e + 1] - off;
-                const uint32_t ns = a.sources_all ? ne : act[e];
-                const uint32_t i = (a.one_event ? g : g - a.ev_tile[e]) * kTile + w;
-                if (i < ne) {
-                    const uint32_t c = off + min(key_local(s[lds_slot(off + i)], a.kl), ne - 1u);
-                    v[b][0] = a.x[c];
-                    v[b][1] = a.y[c];
-                    v[b][2] = a.z[c];
-                    in[b] = true;
-                    src[b] = i < ns;
-                    dst[b] = off + i;
-                }
-            }
-        }
-#pragma unroll
-        for (uint32_t b = 0; b < kBatch; ++b) {
-            const uint32_t q = q0 + b * kStepThreads;
-            if (q >= nq) break;
-            if (in[b]) {
-                a.px[dst[b]] = v[b][0];
-                a.py[dst[b]] = v[b][1];
-                a.pz[dst[b]] = v[b][2];
-            }
-            gp[0][q] = v[b][0];
-            gp[1][q] = v[b][1];
-            gp[2][q] = v[b][2];
-            gsrc[q] = src[b] ? 1 : 0;
-        }
-    }
-    __syncthreads();
-    // the boxes of the sources: one thread per 16-slot group, then one per
-    // 64-slot quarter (four groups), then one per tile (four quarters)
-    const size_t st = a.box_stride;
-    const uint32_t ng = a.n_tiles * (uint32_t)(kTile / 16);
-    for (uint32_t t = threadIdx.x; t < ng; t += kStepThreads) {
-        double b[6] = {INFINITY, INFINITY, INFINITY, -INFINITY, -INFINITY, -INFINITY};
-#pragma unroll 4
-        for (uint32_t w = t * 16u; w < t * 16u + 16u; ++w) {
-            if (!gsrc[w]) continue;
-#pragma unroll
-            for (int k = 0; k < 3; ++k) {
-                b[k] = fmin(b[k], gp[k][w]);
-                b[3 + k] = fmax(b[3 + k], gp[k][w]);
-            }
-        }
-        const uint32_t g = t / (kTile / 16), grp = t % (kTile / 16);
-#pragma unroll
-        for (int k = 0; k < 6; ++k) {
-            gbox[t][k] = b[k];
-            a.tile_box[(size_t)(30 + 16 * k + grp) * st + g] = b[k];
-        }
-    }
-    __syncthreads();
-    __shared__ double qbox[kFusedTiles * 4][6];
-    for (uint32_t t = threadIdx.x; t < a.n_tiles * 4u; t += kStepThreads) {
-        const uint32_t g = t / 4u, qw = t % 4u;
-#pragma unroll
-        for (int k = 0; k < 6; ++k) {
-            double m = gbox[t * 4u][k];
-#pragma unroll
-            for (uint32_t j = 1; j < 4; ++j)
-                m = k < 3 ? fmin(m, gbox[t * 4u + j][k]) : fmax(m, gbox[t * 4u + j][k]);
-            qbox[t][k] = m;
-            a.tile_box[(size_t)(6 + 4 * k + qw) * st + g] = m;
-        }
-    }
-    __syncthreads();
-    for (uint32_t t = threadIdx.x; t < a.n_tiles; t += kStepThreads) {
-#pragma unroll
-        for (int k = 0; k < 6; ++k) {
-            double m = qbox[t * 4u][k];
-#pragma unroll
-            for (uint32_t j = 1; j < 4; ++j)
-                m = k < 3 ? fmin(m, qbox[t * 4u + j][k]) : fmax(m, qbox[t * 4u + j][k]);
-            a.tile_box[(size_t)k * st + t] = m;
-        }
-    }
-}
-
 // The FP64 functions of the step (gccd_fp64.h).  Carrier mode (no
 // repulsion) is bound by VALU issue and takes the three-operand Horner steps
 // (one instruction fewer per step, at the cost of registers); list mode,
@@ -2322,13 +2184,14 @@ constexpr int kDriftSum = 1024;
 constexpr uint32_t kDriftAtomics = 256;
 
 // The step's modes: list mode (a.list_mode, Coulomb on) leaving the new keys for
-// a sort of their own, rebuilding the list itself (a.arrive) or keeping the
-// list's order (a.keep).  Carrier mode is a kernel of its own (drift_steps).
-constexpr int kStepList = 0, kStepFused = 1, kStepKept = 2;
+// a sort of their own, the same for a load whose sort counts places (kRankMax: no
+// runs; latency-bound, so more loads in flight), or keeping the list's order
+// (a.keep).  Carrier mode is a kernel of its own (drift_steps).
+constexpr int kStepList = 0, kStepShort = 1, kStepKept = 2;
 
 template <int MODE>
 __device__ __forceinline__ void step_body(const StepArgs& a) {
-    constexpr bool FUSE = MODE == kStepFused, KEEP = MODE == kStepKept;
+    constexpr bool KEEP = MODE == kStepKept;
     const uint32_t step = a.step + (a.step_base ? *a.step_base : 0u);
     // travelling holes at the start of this step, of the next one, and the
     // counter of the step after next (cleared now; nobody reads it)
@@ -2345,10 +2208,10 @@ __device__ __forceinline__ void step_body(const StepArgs& a) {
     const int lane = threadIdx.x & 63;
     uint32_t kept = 0;  // this wave's holes still travelling (wave-uniform)
     unsigned long long pairs = 0;  // this lane's pair interactions of Eq. (6)
-    // FUSE, or a.sort_runs: each turn's kStepThreads slots leave their new
+    // a.sort_runs: each turn's kStepThreads slots leave their new
     // keys as one sorted run (sort_block_keys), which the next sort only
     // merges; else every slot leaves its key in place
-    const bool runs = FUSE || (MODE == kStepList && a.sort_runs != 0);
+    const bool runs = MODE == kStepList && a.sort_runs != 0;
     __shared__ uint64_t sk[kStepThreads];
     // KEEP: workgroup g owns source tile g, one slot per thread (one turn)
     uint32_t te = 0u, toff = 0u, tne = a.n_all, ti = blockIdx.x * kTile + threadIdx.x;
@@ -2400,7 +2263,7 @@ __device__ __forceinline__ void step_body(const StepArgs& a) {
                     src = a.sources_all ? ne : a.ev_active[e];
                 } else {
                     // collected in a step that kept the list
-                    if (runs && !key_collected(key, a.kl))
+                    if ((runs || MODE == kStepShort) && !key_collected(key, a.kl))
                         key = make_key(e, true, a.x[j], a.y[j], a.z[j], local, a.kl);
                 }
                 if (!active && a.close && slot - off < a.ev_active[e]) {
@@ -2424,7 +2287,7 @@ __device__ __forceinline__ void step_body(const StepArgs& a) {
                     // eight (a small load, latency-bound: sixteen), then four
                     // groups' loads in flight ahead of their adds (the adds in
                     // group order)
-                    constexpr int kW = FUSE || KEEP ? 16 : 8;
+                    constexpr int kW = MODE == kStepList ? 8 : 16;
                     for (; c + kW <= nchunk; c += kW) {
                         float v[kW][3];
 #pragma unroll
@@ -2438,7 +2301,7 @@ __device__ __forceinline__ void step_body(const StepArgs& a) {
                             sz += (double)v[u][2];
                         }
                     }
-                    if ((FUSE || KEEP) && c + 8 <= nchunk) {
+                    if (kW > 8 && c + 8 <= nchunk) {
                         float v[8][3];
 #pragma unroll
                         for (int u = 0; u < 8; ++u)
@@ -2542,22 +2405,6 @@ __device__ __forceinline__ void step_body(const StepArgs& a) {
         }
         if (t) atomicAdd(cnt_out, t);
         if (pr && a.coulomb) atomicAdd(&a.stats[1], pr);
-    }
-    if constexpr (FUSE) {
-        // the last workgroup to arrive rebuilds the list (merging the runs
-        // the workgroups left): each thread's
-        // stores of the step are made visible at device scope before its
-        // workgroup arrives, and the last one sees every workgroup's
-        __shared__ uint32_t last;
-        __threadfence();
-        __syncthreads();
-        if (threadIdx.x == 0) last = atomicAdd(a.arrive, 1u) == gridDim.x - 1u ? 1u : 0u;
-        __syncthreads();
-        if (last) {
-            __threadfence();
-            if (threadIdx.x == 0) atomicExch(a.arrive, 0u);  // zero for the next launch
-            build_small_list(a);
-        }
     }
 }
 
@@ -2671,13 +2518,8 @@ hipError_t launch_step(const StepArgs& a, uint32_t n_slots, hipStream_t s) {
     if (a.keep) {
         if (!a.list_mode || !a.sources_all || a.n_tiles == 0) return hipErrorInvalidValue;
         step_update<kStepKept><<<a.n_tiles, kStepThreads, 0, s>>>(a);
-    } else if (a.arrive) {
-        // the rebuilt list needs every slot and tile in one workgroup's LDS
-        if (!a.list_mode || n_slots != a.n_all || n_slots > (uint32_t)kFusedList ||
-            a.n_tiles > (uint32_t)kFusedTiles)
-            return hipErrorInvalidValue;
-        // one slot per thread: workgroup b's keys are slots [b, b + 1) kStepThreads
-        step_update<kStepFused>
+    } else if (a.list_mode && n_slots <= kRankMax) {
+        step_update<kStepShort>
             <<<(n_slots + kStepThreads - 1) / kStepThreads, kStepThreads, 0, s>>>(a);
     } else if (a.list_mode) {
         step_update<kStepList>

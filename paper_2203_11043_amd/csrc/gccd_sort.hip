@@ -152,7 +152,6 @@ __global__ __launch_bounds__(kSortThreads) void merge_runs(const uint64_t* in, u
 // list at a time, one per lane, and count the lanes whose key is smaller.
 constexpr int kRankWaves = 8;
 constexpr uint32_t kRankKeys = 16;
-constexpr uint32_t kRankMax = 12288;
 
 __global__ __launch_bounds__(64 * kRankWaves) void rank_sort(const uint64_t* __restrict__ in,
                                                              uint64_t* __restrict__ out,

@@ -1,6 +1,5 @@
-// Device code of the one-workgroup sort of carrier keys, shared by the
-// per-step sort (gccd_sort.hip) and the step kernel that rebuilds the list of
-// a small load itself (gccd_kernels.hip).
+// Device code of the one-workgroup sorts of carrier keys: of a tile
+// (gccd_sort.hip) and of a step kernel's 256 slots (gccd_kernels.hip).
 #pragma once
 
 #include "gccd_internal.h"
