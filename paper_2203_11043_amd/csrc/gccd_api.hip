@@ -1968,7 +1968,7 @@ constexpr size_t kNaClose = align256(3 * kNaN * sizeof(unsigned long long));
 constexpr size_t kNaPart = align256((size_t)kMaxChunks * 3 * kNaN * sizeof(float));
 constexpr size_t kNaBox = align256((size_t)kBoxRows * kNaTiles * sizeof(double));
 constexpr size_t kNaItems = align256(kNaBlocks * kMaxChunks * sizeof(FieldItem));
-constexpr size_t kNaSmall = align256((8 + kNaTiles + kMetaWords + kSchedWords) * sizeof(uint32_t));
+constexpr size_t kNaSmall = align256((8 + kNaTiles + kSchedWords) * sizeof(uint32_t));
 constexpr size_t kNaBytes =
     6 * kNaPos + 2 * kNaI32 + 2 * kNaKeys + kNaClose + kNaPart + kNaBox + kNaItems + kNaSmall;
 
@@ -2070,8 +2070,7 @@ int gccd_field_noalloc(const gccd_params* p, int64_t n, const double* x, const d
     uint32_t* ev_tile = small + 2;     // [2]
     uint32_t* ev_active = small + 4;   // [1]
     int32_t* ev_chunks = reinterpret_cast<int32_t*>(small + 5);  // [1]
-    uint32_t* meta = small + 8;        // [kMetaWords]
-    uint32_t* sched = meta + kMetaWords;
+    uint32_t* sched = small + 8;       // [kSchedWords]
     uint32_t* tile_event = sched + kSchedWords;  // [tiles]
 
     const KeyLayout kl{std::max<uint32_t>(1, bits_for((uint64_t)nn)), 0u};
@@ -2082,10 +2081,6 @@ int gccd_field_noalloc(const gccd_params* p, int64_t n, const double* x, const d
             return GCCD_E_DEVICE;                      \
         }                                              \
     } while (0)
-    // meta and sched are contiguous: both zeroed
-    NA_HIP(launch_noalloc_setup(nn, (uint32_t)tiles, g, tail, split, (uint32_t)blocks, ev_off,
-                                ev_tile, ev_chunks, tile_event, meta, kMetaWords + kSchedWords,
-                                items, st));
     LoadArgs la{};
     NA_HIP(load_source(x, cx, nn, &la.sx, st));
     NA_HIP(load_source(y, cy, nn, &la.sy, st));
@@ -2094,17 +2089,16 @@ int gccd_field_noalloc(const gccd_params* p, int64_t n, const double* x, const d
     la.y = cy;
     la.z = cz;
     la.cstep = cstep;
-    la.ev_off = ev_off;
     la.ev_of = ev_of;
     la.n_events = 1u;
     la.n = nn;
     la.thickness = p->thickness_um;
     la.z_well = p->well_z_um;
-    la.cnt = meta + kMetaCount;
     la.kl = kl;
     la.keys = keys1;
     la.close = close;
-    NA_HIP(launch_load(la, st));
+    NA_HIP(launch_noalloc_setup(la, (uint32_t)tiles, g, tail, split, (uint32_t)blocks, ev_off,
+                                ev_tile, ev_chunks, tile_event, sched, kSchedWords, items, st));
     NA_HIP(sort_keys(keys1, keys0, nn, st));
     if (p->collected_are_sources) {  // the gather needs no count: one launch
         NA_HIP(launch_gather_count(keys0, ev_off, ev_tile, tile_event, 1u, (uint32_t)tiles, kl, cx,

@@ -2548,8 +2548,10 @@ hipError_t launch_step(const StepArgs& a, uint32_t n_slots, hipStream_t s) {
 // 128 and 176 B in all).  gccd_load of 8 million holes without repulsion takes
 // 141 us in all, most of it this kernel (before, with the allocations: 4.1 ms).
 // ---------------------------------------------------------------------------
-template <bool LIST>
-__global__ __launch_bounds__(kStepThreads) void load_prepare(LoadArgs a) {
+// LIST: keys and close sums too.  ONE: one event, whose tables are not read (they
+// are written by the same launch), and no count.
+template <bool LIST, bool ONE>
+__device__ __forceinline__ void load_body(const LoadArgs& a) {
     const int lane = threadIdx.x & 63;
     uint32_t kept = 0;  // this wave's travelling holes (wave-uniform)
     for (uint32_t base = blockIdx.x * kStepThreads; base < a.n;
@@ -2566,10 +2568,11 @@ __global__ __launch_bounds__(kStepThreads) void load_prepare(LoadArgs a) {
             const bool collected = zz <= a.z_well;
             a.cstep[j] = collected ? 0 : -1;
             keep = !collected;
-            const uint32_t e = event_of(a.ev_off, a.n_events, j);
+            const uint32_t e = ONE ? 0u : event_of(a.ev_off, a.n_events, j);
             a.ev_of[j] = e;
             if constexpr (LIST) {
-                a.keys[j] = make_key(e, collected, xx, yy, zz, j - a.ev_off[e], a.kl);
+                a.keys[j] =
+                    make_key(e, collected, xx, yy, zz, ONE ? j : j - a.ev_off[e], a.kl);
                 a.close[j] = 0ull;
                 a.close[(size_t)a.n + j] = 0ull;
                 a.close[2 * (size_t)a.n + j] = 0ull;
@@ -2577,15 +2580,21 @@ __global__ __launch_bounds__(kStepThreads) void load_prepare(LoadArgs a) {
         }
         kept += (uint32_t)__popcll(__ballot(keep));
     }
-    // one atomic per workgroup, as in step_update
-    __shared__ uint32_t wave_kept[kStepThreads / 64];
-    if (lane == 0) wave_kept[threadIdx.x >> 6] = kept;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        uint32_t t = 0;
-        for (int w = 0; w < kStepThreads / 64; ++w) t += wave_kept[w];
-        if (t) atomicAdd(a.cnt, t);
+    if constexpr (!ONE) {  // one atomic per workgroup, as in step_update
+        __shared__ uint32_t wave_kept[kStepThreads / 64];
+        if (lane == 0) wave_kept[threadIdx.x >> 6] = kept;
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            uint32_t t = 0;
+            for (int w = 0; w < kStepThreads / 64; ++w) t += wave_kept[w];
+            if (t) atomicAdd(a.cnt, t);
+        }
     }
+}
+
+template <bool LIST>
+__global__ __launch_bounds__(kStepThreads) void load_prepare(LoadArgs a) {
+    load_body<LIST, false>(a);
 }
 
 hipError_t launch_load(const LoadArgs& a, hipStream_t s) {
@@ -2663,16 +2672,17 @@ hipError_t launch_field_finish(const float* part, uint32_t pstride, const int32_
 // `blocks` target blocks, g chunks of which the last `tail` form the tail
 // layer from tile `split`), written in its scratch memory: event tables,
 // zeroed counters, and the work items in the order the context's item builder
-// lists them for one event.
-__global__ void noalloc_setup(uint32_t n, uint32_t tiles, int32_t g, int32_t tail, uint32_t split,
-                              uint32_t blocks, uint32_t* ev_off, uint32_t* ev_tile,
-                              int32_t* ev_chunks, uint32_t* tile_event, uint32_t* words,
-                              uint32_t n_words, FieldItem* items) {
+// lists them for one event; and, in the same launch, its holes (load_body).
+__global__ __launch_bounds__(kStepThreads) void noalloc_setup(
+    LoadArgs la, uint32_t tiles, int32_t g, int32_t tail, uint32_t split, uint32_t blocks,
+    uint32_t* ev_off, uint32_t* ev_tile, int32_t* ev_chunks, uint32_t* tile_event, uint32_t* words,
+    uint32_t n_words, FieldItem* items) {
+    load_body<true, true>(la);
     const uint64_t i0 = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
     const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
     if (i0 == 0) {
         ev_off[0] = 0u;
-        ev_off[1] = n;
+        ev_off[1] = la.n;
         ev_tile[0] = 0u;
         ev_tile[1] = tiles;
         ev_chunks[0] = g;
@@ -2706,13 +2716,13 @@ __global__ void noalloc_setup(uint32_t n, uint32_t tiles, int32_t g, int32_t tai
     }
 }
 
-hipError_t launch_noalloc_setup(uint32_t n, uint32_t tiles, int32_t g, int32_t tail,
+hipError_t launch_noalloc_setup(const LoadArgs& la, uint32_t tiles, int32_t g, int32_t tail,
                                 uint32_t split, uint32_t blocks, uint32_t* ev_off,
                                 uint32_t* ev_tile, int32_t* ev_chunks, uint32_t* tile_event,
                                 uint32_t* words, uint32_t n_words, FieldItem* items,
                                 hipStream_t s) {
-    noalloc_setup<<<grid_for((uint64_t)blocks * g, 256, 1024), 256, 0, s>>>(
-        n, tiles, g, tail, split, blocks, ev_off, ev_tile, ev_chunks, tile_event, words, n_words,
+    noalloc_setup<<<grid_for(la.n, kStepThreads, 1024), kStepThreads, 0, s>>>(
+        la, tiles, g, tail, split, blocks, ev_off, ev_tile, ev_chunks, tile_event, words, n_words,
         items);
     return hipGetLastError();
 }
