@@ -148,6 +148,8 @@ struct gccd_ctx {
     hipStream_t side = nullptr;      // default priority, like every stream here
     hipEvent_t ev_keys = nullptr;    // the step kernel has written ukeys
     hipEvent_t ev_list = nullptr;    // the side stream's list and counts are done
+    hipEvent_t ev_grid = nullptr;    // the closure's grid is placed
+    hipEvent_t ev_near = nullptr;    // the side stream's near sum is done
     double* ps[3] = {nullptr, nullptr, nullptr};
     double* tile_box = nullptr;
     float* part = nullptr;
@@ -928,29 +930,43 @@ int run_network(gccd_ctx* c) {
     return GCCD_OK;
 }
 
+// The side stream and its events.
+int ensure_side(gccd_ctx* c) {
+    if (!c->side) GCCD_HIP(c, hipStreamCreateWithFlags(&c->side, hipStreamNonBlocking));
+    for (hipEvent_t* e : {&c->ev_keys, &c->ev_list, &c->ev_grid, &c->ev_near})
+        if (!*e) GCCD_HIP(c, hipEventCreateWithFlags(e, hipEventDisableTiming));
+    return GCCD_OK;
+}
+
 // The closure's field of the current sorted list: near chunks into groups
-// [0, S), the far field of target slots [0, nt) into group S.
+// [0, S), the far field of target slots [0, nt) into group S.  Once the grid is
+// placed the two parts are independent: the near sum, one launch that fills
+// the chip, runs on the side stream beside the far part's chain of short ones.
 int closure_field(gccd_ctx* c, bool targets_all, uint32_t nt, bool with_net) {
     const uint32_t n = (uint32_t)c->n;
     const double eps2 = c->p.softening_um * c->p.softening_um;
     hipStream_t st = c->stream;
-    GCCD_HIP(c, launch_moments(c->ps[0], c->ps[1], c->ps[2], n, c->mom, st));
+    if (int r = ensure_side(c); r != GCCD_OK) return r;
+    GCCD_HIP(c, launch_moments(c->ps[0], c->ps[1], c->ps[2], n, c->mom, c->acc, st));
     GCCD_HIP(c, launch_grid_params(c->mom, c->ps[0], c->ps[1], c->ps[2], n, eps2, c->gp, st));
-    GCCD_HIP(c, launch_fill_u32(reinterpret_cast<uint32_t*>(c->acc), 2ull * kGridNodes, 0u, st));
+    GCCD_HIP(c, hipEventRecord(c->ev_grid, st));
+    GCCD_HIP(c, hipStreamWaitEvent(c->side, c->ev_grid, 0));
+    FieldArgs fa = field_args(c, targets_all);
+    GCCD_HIP(c, launch_near(fa, c->gp, n, c->n_items, (uint32_t)c->near_chunks, c->side));
+    GCCD_HIP(c, hipEventRecord(c->ev_near, c->side));
     GCCD_HIP(c, launch_deposit(c->ps[0], c->ps[1], c->ps[2], n, c->gp, c->acc, st));
     GCCD_HIP(c, launch_rho(c->acc, c->act + act_offset(kX0), c->rho_f32, st));
     if (with_net) {
         int r = run_network(c);
         if (r != GCCD_OK) return r;
     }
-    FieldArgs fa = field_args(c, targets_all);
-    GCCD_HIP(c, launch_near(fa, c->gp, n, c->n_items, (uint32_t)c->near_chunks, st));
     float* far = c->part + (size_t)c->near_chunks * 3 * n;
     if (with_net)
         GCCD_HIP(c, launch_far(c->fgrid, c->gp, c->ps[0], c->ps[1], c->ps[2], nt, far, far + n,
                                far + 2 * (size_t)n, st));
     else
         GCCD_HIP(c, launch_fill_u32(reinterpret_cast<uint32_t*>(far), 3ull * n, 0u, st));
+    GCCD_HIP(c, hipStreamWaitEvent(st, c->ev_near, 0));
     return GCCD_OK;
 }
 
@@ -1172,6 +1188,8 @@ void gccd_destroy(gccd_ctx* c) {
     if (c->side) (void)hipStreamDestroy(c->side);
     if (c->ev_keys) (void)hipEventDestroy(c->ev_keys);
     if (c->ev_list) (void)hipEventDestroy(c->ev_list);
+    if (c->ev_grid) (void)hipEventDestroy(c->ev_grid);
+    if (c->ev_near) (void)hipEventDestroy(c->ev_near);
     for (hipEvent_t e : c->ev) (void)hipEventDestroy(e);
     delete c;
 }
@@ -1653,10 +1671,9 @@ int gccd_run(gccd_ctx* c, double dt_ps, int64_t max_steps, int64_t* steps_done,
             int r = settle(c);
             if (r != GCCD_OK) return r;
         }
-        if (pipelined && !c->side) {
-            GCCD_HIP(c, hipStreamCreateWithFlags(&c->side, hipStreamNonBlocking));
-            GCCD_HIP(c, hipEventCreateWithFlags(&c->ev_keys, hipEventDisableTiming));
-            GCCD_HIP(c, hipEventCreateWithFlags(&c->ev_list, hipEventDisableTiming));
+        if (pipelined) {
+            int r = ensure_side(c);
+            if (r != GCCD_OK) return r;
         }
         if (pipelined && !c->sorting && bound > 0) {
             // Enter the steady state: the next step's list (the current one) also

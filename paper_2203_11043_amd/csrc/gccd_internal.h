@@ -277,7 +277,7 @@ struct ConvArgs {
 hipError_t launch_near(const FieldArgs& a, const GridParams* gp, uint32_t n, uint32_t n_items,
                        uint32_t n_chunks, hipStream_t s);
 hipError_t launch_moments(const double* x, const double* y, const double* z, uint32_t n,
-                          double* part, hipStream_t s);
+                          double* part, unsigned long long* acc, hipStream_t s);
 hipError_t launch_grid_params(const double* part, const double* x, const double* y,
                               const double* z, uint32_t n, double eps2, GridParams* gp,
                               hipStream_t s);
