@@ -154,12 +154,13 @@ def closure_leg(gccd, workloads, torch, n: int = 1000000, seed: int = 2000,
     return out
 
 
-DRIFT_BYTES_PER_CARRIER_STEP = 52   # x, y, z read and written (48), collection step read (4); a single event's carriers need no event read
+DRIFT_FLOP_PER_CARRIER_STEP = 377     # FP64, counted by the hardware (FMA = 2)
+PEAK_FP64_TFLOPS = 78.6               # MI355X published FP64 vector peak
 
 
 def drift_leg(gccd, workloads, torch, n: int, steps: int, warm: int, cpu: bool) -> dict:
     """The paper's O(N) case (Sec. IV, Coulomb off): n holes drift and
-    diffuse (Eqs. (1)-(4)), one step_update launch per time step.  A wide
+    diffuse (Eqs. (1)-(4)), up to 32 time steps per drift_steps launch.  A wide
     cloud 400 um deep, so that no hole is collected in the timed steps.  The
     oracle leg times whole Coulomb-off steps of the first 1e6 of the holes."""
     import numpy as np
@@ -183,10 +184,10 @@ def drift_leg(gccd, workloads, torch, n: int, steps: int, warm: int, cpu: bool) 
     rate = cs / dt
     out = {"n": n, "steps": done, "travelling": na, "ms_per_step": dt / max(done, 1) * 1e3,
            "carrier_steps_per_s": rate,
-           "roofline": {"bound": "hbm", "achieved": rate * DRIFT_BYTES_PER_CARRIER_STEP / 1e9,
-                        "peak": 8000.0, "unit": "GB/s",
-                        "frac": rate * DRIFT_BYTES_PER_CARRIER_STEP / 8e12,
-                        "bytes_per_carrier_step": DRIFT_BYTES_PER_CARRIER_STEP}}
+           "roofline": {"bound": "alu", "achieved": rate * DRIFT_FLOP_PER_CARRIER_STEP / 1e12,
+                        "peak": PEAK_FP64_TFLOPS, "unit": "TFLOP/s",
+                        "frac": rate * DRIFT_FLOP_PER_CARRIER_STEP / (PEAK_FP64_TFLOPS * 1e12),
+                        "flop_per_carrier_step": DRIFT_FLOP_PER_CARRIER_STEP}}
     if cpu:
         import oracle
         m = min(n, 1000000)
@@ -482,9 +483,10 @@ def main() -> int:
                       "one gccd_run for all timed steps (counts polled every 32 steps), "
                       "then the image"),
             "positions": "f64",
-            "pair_arithmetic": ("f32, origin per workgroup; far tiles in the expanded-square form, "
-                                "pairs closer than rho/4 with double-single differences, pairs "
-                                "within 64 softening lengths in f64"
+            "pair_arithmetic": ("f32, origin per workgroup; far 16x16 blocks of pairs with r^2 on "
+                                "the matrix cores (bf16 parts holding all 24 bits, f32 sums), "
+                                "near blocks with double-single differences, pairs within 64 "
+                                "softening lengths in f64"
                                 if s1["targets_per_thread"] == 1 else
                                 "f32, origin per workgroup; pairs closer than rho/4 with "
                                 "double-single differences, pairs within 64 softening lengths "
@@ -506,7 +508,7 @@ def main() -> int:
         "pct_fp32_peak": 100.0 * FLOP_PER_PAIR * pair_rate / (PEAK_FP32_TFLOPS * 1e12),
         "roofline": {
             "bound": "alu",
-            "kernel": ("field_tiles_expanded (Eq. (6))" if s1["targets_per_thread"] == 1
+            "kernel": ("field_tiles_matrix (Eq. (6))" if s1["targets_per_thread"] == 1
                        else "field_tiles<%d> (Eq. (6))" % s1["targets_per_thread"]),
             "achieved": kern_tflops,
             "peak": PEAK_FP32_TFLOPS,

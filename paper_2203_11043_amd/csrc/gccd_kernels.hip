@@ -2,7 +2,9 @@
 // Avalos & Sofo Haro, arXiv 2203.11043:
 //   field_tiles_matrix, field_tiles -- Eq. (6), softened all-pairs Coulomb field
 //                    (the O(N^2) part)
+//   near_matrix, near_waves -- the near part of the closure's split of Eq. (6)
 //   step_update   -- Eqs. (1)-(4) and the z check of Sec. III.B, fused per carrier
+//   drift_steps   -- the same for several steps at once, without repulsion
 //   load_prepare  -- a load's positions taken in, with its boundary handling
 //   make_keys, count_active, gather_tiles -- the spatially sorted carrier list
 //   image_bin     -- 2D histogram of collected holes (Sec. V.A)
