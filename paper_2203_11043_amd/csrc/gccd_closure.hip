@@ -279,10 +279,6 @@ hipError_t launch_deposit(const double* px, const double* py, const double* pz, 
 
 // charge per node: bf16 network input, and FP32 (for inspection) if asked
 __global__ void rho_convert(const unsigned long long* acc, uint16_t* rho, float* rho_f32) {
-    // The near sum fills the chip beside these short launches, which wait for each
-    // other (closure_field): their waves go first.  Closure step at 5e4 holes: one
-    // after the other 0.269 ms, beside each other 0.254, with this priority 0.238.
-    __builtin_amdgcn_s_setprio(3);
     const int i = blockIdx.x * 256 + threadIdx.x;
     if (i >= kGridNodes) return;
     const float v = (float)((double)acc[i] * (1.0 / 4294967296.0));
