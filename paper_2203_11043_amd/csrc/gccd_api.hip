@@ -115,9 +115,10 @@ struct gccd_ctx {
 
     // The load's buffers stay with the context from load to load and are freed
     // with it: allocating some 25 of them and freeing the last load's took most of a
-    // load's time (gccd_load of 1,000 holes 180 us, now 48; of a million 3.4 ms, now
-    // 0.27; a batch of 400 events 4.1 ms, now 0.40).  reserve below bounds what stays.  `arena` holds every buffer whose
-    // size the number of holes and events fixes; the pointers below point into it.
+    // load's time (gccd_load of 1,000 holes 180 us, now 37; of a million 3.4 ms, now
+    // 0.27; a batch of 400 events 4.1 ms, now 0.40).  reserve below bounds what
+    // stays.  `arena` holds every buffer whose size the number of holes and events
+    // fixes; the pointers below point into it.
     unsigned char* arena = nullptr;
     size_t arena_cap = 0, part_cap = 0, close_cap = 0, items_bytes = 0;  // allocated bytes
     size_t host_items_bytes = 0, host_active_bytes = 0, host_tables_bytes = 0;
@@ -974,17 +975,19 @@ int closure_field(gccd_ctx* c, bool targets_all, uint32_t nt, bool with_net) {
 
 namespace {
 
-// Whether a kernel of this device may read the count doubles at p: aligned device
-// memory of this device, all inside its allocation.  Other memory that a copy
-// reaches (a peer's, the host's) is copied first, and a range past the end
-// is refused by that copy.
-bool kernel_readable(const double* p, size_t count) {
+// Whether a kernel on stream s may read the count doubles at p: aligned device
+// memory of the stream's device, the current one, all inside its allocation.  Other
+// memory that a copy reaches (a peer's, the host's) is copied first, and a range
+// past the end is refused by that copy.
+bool kernel_readable(const double* p, size_t count, hipStream_t s) {
     if ((uintptr_t)p % sizeof(double) != 0) return false;
     int dev = -1;
+    hipDevice_t of_stream = -1;
     hipPointerAttribute_t at{};
     hipDeviceptr_t base = nullptr;
     size_t size = 0;
-    if (hipGetDevice(&dev) != hipSuccess || hipPointerGetAttributes(&at, p) != hipSuccess ||
+    if (hipGetDevice(&dev) != hipSuccess || hipStreamGetDevice(s, &of_stream) != hipSuccess ||
+        (int)of_stream != dev || hipPointerGetAttributes(&at, p) != hipSuccess ||
         at.type != hipMemoryTypeDevice || at.device != dev ||
         hipMemGetAddressRange(&base, &size, (hipDeviceptr_t)p) != hipSuccess) {
         (void)hipGetLastError();
@@ -998,7 +1001,7 @@ bool kernel_readable(const double* p, size_t count) {
 hipError_t load_source(const double* p, double* own, size_t count, const double** from,
                        hipStream_t s) {
     *from = p;
-    if (kernel_readable(p, count)) return hipSuccess;
+    if (kernel_readable(p, count, s)) return hipSuccess;
     *from = own;
     return hipMemcpyAsync(own, p, count * sizeof(double), hipMemcpyDeviceToDevice, s);
 }
