@@ -1286,10 +1286,22 @@ int gccd_load_events(gccd_ctx* c, int32_t n_events, const int64_t* offsets, cons
         la.close = c->close;
         c->close_n = n;
     }
-    GCCD_HIP(c, launch_load(la, c->stream));
-    if (c->list_mode) {
-        r = finish_list(c, c->ukeys[0]);
-        if (r != GCCD_OK) return r;
+    if (c->list_mode && n_events == 1 && n <= kSmallLoad) {
+        la.sorted = c->keys[0];
+        la.px = c->ps[0];
+        la.py = c->ps[1];
+        la.pz = c->ps[2];
+        la.box = c->tile_box;
+        la.box_stride = c->n_tiles;
+        la.ev_active = c->ev_active_d[0];
+        la.sources_all = c->p.collected_are_sources;
+        GCCD_HIP(c, launch_small_load(la, c->stream));
+    } else {
+        GCCD_HIP(c, launch_load(la, c->stream));
+        if (c->list_mode) {
+            r = finish_list(c, c->ukeys[0]);
+            if (r != GCCD_OK) return r;
+        }
     }
     r = read_counts(c);
     if (r != GCCD_OK) return r;
@@ -2117,10 +2129,22 @@ int gccd_field_noalloc(const gccd_params* p, int64_t n, const double* x, const d
     la.kl = kl;
     la.keys = keys1;
     la.close = close;
+    if (nn <= (uint32_t)kSmallLoad) {
+        la.sorted = keys0;
+        la.px = px;
+        la.py = py;
+        la.pz = pz;
+        la.box = box;
+        la.box_stride = (uint32_t)tiles;
+        la.ev_active = ev_active;
+        la.sources_all = p->collected_are_sources;
+    }
     NA_HIP(launch_noalloc_setup(la, (uint32_t)tiles, g, tail, split, (uint32_t)blocks, ev_off,
                                 ev_tile, ev_chunks, tile_event, sched, kSchedWords, items, st));
-    NA_HIP(sort_keys(keys1, keys0, nn, st));
-    if (p->collected_are_sources) {  // the gather needs no count: one launch
+    if (!la.sorted) NA_HIP(sort_keys(keys1, keys0, nn, st));
+    if (la.sorted) {
+        // the list stands
+    } else if (p->collected_are_sources) {  // the gather needs no count: one launch
         NA_HIP(launch_gather_count(keys0, ev_off, ev_tile, tile_event, 1u, (uint32_t)tiles, kl, cx,
                                    cy, cz, px, py, pz, box, (uint32_t)tiles, ev_active, st));
     } else {

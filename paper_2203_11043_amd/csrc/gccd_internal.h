@@ -183,7 +183,18 @@ struct LoadArgs {
     KeyLayout kl;
     uint64_t* keys;
     unsigned long long* close;  // [3][n]
+    // launch_small_load, one event of at most kSmallLoad holes: the sorted list, its
+    // positions and boxes (of the sources) and the travelling count, with no keys left
+    uint64_t* sorted;
+    double* px;
+    double* py;
+    double* pz;
+    double* box;
+    uint32_t box_stride;
+    uint32_t* ev_active;
+    int32_t sources_all;
 };
+constexpr int kSmallLoad = 2 * kTile;
 
 // precision: a GCCD_PRECISION_* mode
 int field_slots_per_cu(int tpt, int precision);
@@ -197,6 +208,7 @@ hipError_t launch_field(const FieldArgs& a, int tpt, int precision, uint32_t n_i
                         uint32_t queue_grid, hipStream_t s, uint32_t grid_cap = 0);
 hipError_t launch_step(const StepArgs& a, uint32_t n_slots, hipStream_t s);
 hipError_t launch_load(const LoadArgs& a, hipStream_t s);
+hipError_t launch_small_load(const LoadArgs& a, hipStream_t s);
 hipError_t launch_make_keys(const double* x, const double* y, const double* z,
                             const int32_t* cstep, const uint32_t* ev_of, const uint32_t* ev_off,
                             uint32_t n, KeyLayout kl, uint64_t* keys, hipStream_t s);
@@ -224,8 +236,8 @@ hipError_t launch_field_finish(const float* part, uint32_t pstride, const int32_
                                KeyLayout kl, uint32_t n, double K, unsigned long long* close,
                                double close_unit, double* ex, double* ey, double* ez,
                                hipStream_t s);
-// gccd_field_noalloc: event tables, zeroed words, work items, and the load (la.keys set;
-// la.ev_off and la.cnt not used).
+// gccd_field_noalloc: event tables, zeroed words, work items, and the load (la.ev_off and
+// la.cnt not used; la.keys, or la.sorted and the rest of launch_small_load, set).
 hipError_t launch_noalloc_setup(const LoadArgs& la, uint32_t tiles, int32_t g, int32_t tail,
                                 uint32_t split, uint32_t blocks, uint32_t* ev_off,
                                 uint32_t* ev_tile, int32_t* ev_chunks, uint32_t* tile_event,

@@ -1888,16 +1888,16 @@ hipError_t launch_count(const uint64_t* keys, const uint32_t* ev_off, uint32_t n
     return hipGetLastError();
 }
 
-// The boxes of source tile g, by one workgroup of kTile threads, one slot
-// each (source: whether the slot is one): bounding box of the tile (rows
+// The boxes of source tile g, by kTile threads of a workgroup (tid: index among
+// them), one slot each (source: whether the slot is one): bounding box of the tile (rows
 // 0-5 of box: low x, y, z, high x, y, z), and the same for each 64-slot
 // quarter of the tile (row 6 + 4 k + q for bound k of quarter q) and each
 // 16-slot group (row 30 + 16 k + g), which the near-field kernel culls by.
 // The group boxes are the first four steps of the lane reduction that gives
 // the quarter boxes.
-__device__ __forceinline__ void tile_boxes(uint32_t g, bool source, double vx, double vy,
-                                           double vz, double* box, uint32_t stride,
-                                           double (*red)[kTile / 64]) {
+__device__ __forceinline__ void tile_boxes(uint32_t g, uint32_t tid, bool source, double vx,
+                                           double vy, double vz, double* box, uint32_t stride,
+                                           double (*red)[kTile / 64], bool write = true) {
     double lx = source ? vx : INFINITY, ly = source ? vy : INFINITY, lz = source ? vz : INFINITY;
     double hx = source ? vx : -INFINITY, hy = source ? vy : -INFINITY, hz = source ? vz : -INFINITY;
     // butterfly over lanes: after the strides 1..8 every lane holds its
@@ -1911,8 +1911,8 @@ __device__ __forceinline__ void tile_boxes(uint32_t g, bool source, double vx, d
         hy = fmax(hy, __shfl_xor(hy, m));
         hz = fmax(hz, __shfl_xor(hz, m));
     }
-    if ((threadIdx.x & 15) == 0) {
-        const int grp = threadIdx.x >> 4;  // 0 .. 15
+    if (write && (tid & 15) == 0) {
+        const int grp = tid >> 4;  // 0 .. 15
         const double v[6] = {lx, ly, lz, hx, hy, hz};
 #pragma unroll
         for (int k = 0; k < 6; ++k) box[(size_t)(30 + 16 * k + grp) * stride + g] = v[k];
@@ -1926,8 +1926,8 @@ __device__ __forceinline__ void tile_boxes(uint32_t g, bool source, double vx, d
         hy = fmax(hy, __shfl_xor(hy, m));
         hz = fmax(hz, __shfl_xor(hz, m));
     }
-    const int wave = threadIdx.x >> 6;
-    if ((threadIdx.x & 63) == 0) {
+    const int wave = tid >> 6;
+    if ((tid & 63) == 0) {
         red[0][wave] = lx;
         red[1][wave] = ly;
         red[2][wave] = lz;
@@ -1936,11 +1936,12 @@ __device__ __forceinline__ void tile_boxes(uint32_t g, bool source, double vx, d
         red[5][wave] = hz;
         const double v[6] = {lx, ly, lz, hx, hy, hz};
 #pragma unroll
-        for (int k = 0; k < 6; ++k) box[(size_t)(6 + 4 * k + wave) * stride + g] = v[k];
+        for (int k = 0; k < 6; ++k)
+            if (write) box[(size_t)(6 + 4 * k + wave) * stride + g] = v[k];
     }
     __syncthreads();
-    if (threadIdx.x < 6) {
-        const int k = threadIdx.x;
+    if (write && tid < 6) {
+        const int k = tid;
         double v = red[k][0];
         for (int w = 1; w < kTile / 64; ++w) v = (k < 3) ? fmin(v, red[k][w]) : fmax(v, red[k][w]);
         box[(size_t)k * stride + g] = v;
@@ -1975,7 +1976,7 @@ __device__ __forceinline__ void gather_tile(uint32_t g, KeyAt key_at, const uint
         py[off + i] = vy;
         pz[off + i] = vz;
     }
-    tile_boxes(g, i < ne && i < ns, vx, vy, vz, box, stride, red);
+    tile_boxes(g, threadIdx.x, i < ne && i < ns, vx, vy, vz, box, stride, red);
 }
 
 __global__ __launch_bounds__(kTile) void gather_tiles(
@@ -2385,7 +2386,7 @@ __device__ __forceinline__ void step_body(const StepArgs& a) {
     }
     if constexpr (KEEP) {
         __shared__ double red[6][kTile / 64];
-        tile_boxes(blockIdx.x, ti < tne, px, py, pz, a.tile_box, a.box_stride, red);
+        tile_boxes(blockIdx.x, threadIdx.x, ti < tne, px, py, pz, a.tile_box, a.box_stride, red);
     }
     // one atomic per workgroup for each count: a counter taking one per wave
     // and grid-stride turn (2.6e5 at 2^24 holes) serialised the whole step
@@ -2599,6 +2600,96 @@ __global__ __launch_bounds__(kStepThreads) void load_prepare(LoadArgs a) {
     load_body<LIST, false>(a);
 }
 
+// Taking in a load of one event of at most kSmallLoad holes with its sorted list,
+// by one workgroup: what load_prepare, the counted sort and gather_count_tiles do
+// in three launches, whose latency is all that such a load costs.  Each wave sorts
+// its 64 keys by counting the smaller ones; a key's place is then the number of
+// smaller keys of every run, by binary searches side by side.  Each half of the
+// workgroup takes one source tile.  gccd_field_noalloc called without waiting, 64
+// holes 24 -> 18 us, 300 23.5 -> 20.9, 512 24 -> 23.  (Counting a key's smaller ones over
+// the whole list on the one compute unit: 512 holes 29 to 33.)
+__device__ __forceinline__ void small_load_body(const LoadArgs& a) {
+    __shared__ uint64_t keys[kSmallLoad];
+    __shared__ uint16_t from[kSmallLoad];
+    __shared__ double pos[3][kSmallLoad];
+    __shared__ double red[kSmallLoad / kTile][6][kTile / 64];
+    __shared__ uint32_t travelling;
+    const uint32_t tid = threadIdx.x, n = a.n;
+    if (tid == 0) travelling = 0u;
+    double xx = 0.0, yy = 0.0, zz = 0.0;
+    bool keep = false;
+    if (tid < n) {
+        xx = a.sx[tid];
+        yy = a.sy[tid];
+        zz = a.sz[tid];
+        if (zz > a.thickness) zz = 2.0 * a.thickness - zz;
+        a.x[tid] = pos[0][tid] = xx;
+        a.y[tid] = pos[1][tid] = yy;
+        a.z[tid] = pos[2][tid] = zz;
+        keep = !(zz <= a.z_well);
+        a.cstep[tid] = keep ? -1 : 0;
+        a.ev_of[tid] = 0u;
+        a.close[tid] = 0ull;
+        a.close[(size_t)n + tid] = 0ull;
+        a.close[2 * (size_t)n + tid] = 0ull;
+    }
+    // (past the load: distinct keys above every other)
+    const uint64_t key =
+        tid < n ? make_key(0u, !keep, xx, yy, zz, tid, a.kl) : ~0ull - (kSmallLoad - tid);
+    const uint32_t run = tid & ~63u;
+    uint32_t below = 0u;
+#pragma unroll 16
+    for (int u = 0; u < 64; ++u) {
+        const uint64_t k =
+            (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(key >> 32), u) << 32 |
+            (uint32_t)__builtin_amdgcn_readlane((int)key, u);
+        below += k < key ? 1u : 0u;
+    }
+    keys[run + below] = key;
+    __syncthreads();
+    const uint32_t kept = (uint32_t)__popcll(__ballot(keep));
+    if ((tid & 63u) == 0 && kept) atomicAdd(&travelling, kept);
+    constexpr uint32_t kRuns = kSmallLoad / 64;
+    uint32_t at[kRuns] = {};
+#pragma unroll
+    for (uint32_t step = 32u; step >= 1u; step >>= 1) {
+#pragma unroll
+        for (uint32_t q = 0; q < kRuns; ++q)
+            at[q] += keys[q * 64u + at[q] + step - 1u] < key ? step : 0u;
+    }
+    uint32_t place = 0u;
+#pragma unroll
+    for (uint32_t q = 0; q < kRuns; ++q) place += at[q] + (keys[q * 64u + at[q]] < key ? 1u : 0u);
+    if (tid < n) {
+        a.sorted[place] = key;
+        from[place] = (uint16_t)tid;
+    }
+    __syncthreads();
+    double px = 0.0, py = 0.0, pz = 0.0;
+    if (tid < n) {
+        const uint32_t i = from[tid];
+        a.px[tid] = px = pos[0][i];
+        a.py[tid] = py = pos[1][i];
+        a.pz[tid] = pz = pos[2][i];
+    }
+    const uint32_t active = travelling, g = tid / kTile, tiles = (n + kTile - 1) / kTile;
+    // (without a second tile the upper half writes no boxes)
+    tile_boxes(g, tid % kTile, tid < n && (a.sources_all || tid < active), px, py, pz, a.box,
+               a.box_stride, red[g], g < tiles);
+    if (tid == 0) {
+        a.ev_active[0] = active;
+        if (a.cnt && active) atomicAdd(a.cnt, active);
+    }
+}
+
+__global__ __launch_bounds__(kSmallLoad) void small_load(LoadArgs a) { small_load_body(a); }
+
+hipError_t launch_small_load(const LoadArgs& a, hipStream_t s) {
+    if (a.n == 0 || a.n > (uint32_t)kSmallLoad || a.n_events != 1u) return hipErrorInvalidValue;
+    small_load<<<1, kSmallLoad, 0, s>>>(a);
+    return hipGetLastError();
+}
+
 hipError_t launch_load(const LoadArgs& a, hipStream_t s) {
     const auto grid = grid_for(a.n, kStepThreads, 8192);
     if (a.keys)
@@ -2675,11 +2766,15 @@ hipError_t launch_field_finish(const float* part, uint32_t pstride, const int32_
 // layer from tile `split`), written in its scratch memory: event tables,
 // zeroed counters, and the work items in the order the context's item builder
 // lists them for one event; and, in the same launch, its holes (load_body).
-__global__ __launch_bounds__(kStepThreads) void noalloc_setup(
+template <bool SMALL>
+__global__ __launch_bounds__(SMALL ? kSmallLoad : kStepThreads) void noalloc_setup(
     LoadArgs la, uint32_t tiles, int32_t g, int32_t tail, uint32_t split, uint32_t blocks,
     uint32_t* ev_off, uint32_t* ev_tile, int32_t* ev_chunks, uint32_t* tile_event, uint32_t* words,
     uint32_t n_words, FieldItem* items) {
-    load_body<true, true>(la);
+    if (SMALL)
+        small_load_body(la);
+    else
+        load_body<true, true>(la);
     const uint64_t i0 = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
     const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
     if (i0 == 0) {
@@ -2723,9 +2818,14 @@ hipError_t launch_noalloc_setup(const LoadArgs& la, uint32_t tiles, int32_t g, i
                                 uint32_t* ev_tile, int32_t* ev_chunks, uint32_t* tile_event,
                                 uint32_t* words, uint32_t n_words, FieldItem* items,
                                 hipStream_t s) {
-    noalloc_setup<<<grid_for(la.n, kStepThreads, 1024), kStepThreads, 0, s>>>(
-        la, tiles, g, tail, split, blocks, ev_off, ev_tile, ev_chunks, tile_event, words, n_words,
-        items);
+    if (la.sorted)
+        noalloc_setup<true><<<1, kSmallLoad, 0, s>>>(la, tiles, g, tail, split, blocks, ev_off,
+                                                     ev_tile, ev_chunks, tile_event, words, n_words,
+                                                     items);
+    else
+        noalloc_setup<false><<<grid_for(la.n, kStepThreads, 1024), kStepThreads, 0, s>>>(
+            la, tiles, g, tail, split, blocks, ev_off, ev_tile, ev_chunks, tile_event, words,
+            n_words, items);
     return hipGetLastError();
 }
 
