@@ -183,7 +183,7 @@ int gccd_stats(gccd_ctx* c, gccd_stats_t* out);
  * thread, and per event a chunk count near the one that gives about 64
  * workgroups per compute unit, picked so that the event's tiles split into
  * chunks as nearly equal as possible.  With one target per thread in the
- * default precision, pairs farther than a fifth of the targets' box
+ * default precision, pairs farther than 4/7 of the targets' box
  * half-diagonal are summed in the expanded-square form (see
  * gccd_set_precision).  The
  * split changes the FP32 summation order; the targets per thread change the
@@ -230,11 +230,13 @@ int gccd_autotune(gccd_ctx* c, int32_t* targets_per_thread, int32_t* source_chun
  * rounded relative to and in how the difference of a pair is formed.
  *   DEFAULT   origin at the centre of each workgroup's targets.  With one
  *             target per thread, blocks of 16 targets and 16 sources whose
- *             boxes are farther apart than rho/5 (rho: the targets'
+ *             boxes are farther apart than 4 rho/7 (rho: the targets'
  *             half-diagonal) take r^2 + eps^2 as (|s|^2 + eps^2) + |t|^2 -
  *             2 t.s on the matrix cores (FP32 factors as three bf16 parts,
- *             FP32 sums) and the sum as t sum w - sum s w; all other pairs
- *             take the difference of coordinates and residuals.  With 2 or 4
+ *             FP32 sums) and the sum as t sum w - sum s w (at most about
+ *             5e-6 relative error per term); those farther apart than rho/4
+ *             take differences of the coordinates, all other pairs of
+ *             coordinates and residuals.  With 2 or 4
  *             targets per thread, differences of the coordinates, those of
  *             pairs closer than a quarter of the target's distance from the
  *             origin recomputed with the residuals

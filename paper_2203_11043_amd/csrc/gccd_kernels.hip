@@ -643,7 +643,7 @@ __global__ __launch_bounds__(kFieldThreads) void field_tiles(FieldArgs a) {
 }
 
 // The cutoff r^2 + eps^2 < cut2 of the near sum as factors of 0 or 1 (see
-// comp_quad), on r^2 and on its reciprocal square root.
+// diff_quad), on r^2 and on its reciprocal square root.
 struct CutoffTest {
     float big_r2 = 0.0f, lim_r2 = 0.0f;    // clamp(lim_r2 - big_r2 r^2)
     float big_inv = 0.0f, lim_inv = 0.0f;  // clamp(big_inv / r - lim_inv)
@@ -651,15 +651,15 @@ struct CutoffTest {
 
 __device__ __forceinline__ float clamp01(float v) { return __builtin_amdgcn_fmed3f(v, 0.0f, 1.0f); }
 
-// One source quadruple of a near block in the compensated difference form:
-// sources k .. k + 3 of the staged tile (sources src .. src + 3 of the event)
-// at the lane's target, number tgt of the block.  The four reciprocal square
+// One source quadruple of a near (COMP: hi and lo parts) or plain (hi parts) block
+// in the difference form: sources k .. k + 3 of the staged tile (sources src ..
+// src + 3 of the event) at the lane's target, number tgt of the block.  The four reciprocal square
 // roots stand together at raised wave priority: a compute unit issues the
 // full-rate FP32 instructions of two waves at once only while neither has a
 // transcendental next, so single ones spread through the stream cost every wave
 // that pairing (measured, far pairs: 40.3 cycles per wave and source spread,
-// 37.5 grouped by four at raised priority).  One compare with the smallest of
-// the four r^2 rules out pairs below acc2 (a compare issues at half rate),
+// 37.5 grouped by four at raised priority).  COMP: one compare with the smallest
+// of the four r^2 rules out pairs below acc2 (a compare issues at half rate),
 // which are recorded for exact summation.  e2 is the softening and rx the
 // exact-sum limit (0 for a lane without a target) in vector registers (an
 // instruction with a scalar operand does not pair either).
@@ -667,8 +667,8 @@ __device__ __forceinline__ float clamp01(float v) { return __builtin_amdgcn_fmed
 // r^2)) of 0 or 1 (big: a power of two that makes one unit in the last place
 // exceed 1); no pair is recorded.  Two full-rate instructions where compare and
 // select are two half-rate ones.
-template <bool CUT>
-__device__ __forceinline__ void comp_quad(WaveList& xl, uint32_t& nx, uint32_t tgt, uint32_t src,
+template <bool CUT, bool COMP>
+__device__ __forceinline__ void diff_quad(WaveList& xl, uint32_t& nx, uint32_t tgt, uint32_t src,
                                           const float (&hl)[6][kTile], uint32_t k, float thx,
                                           float thy, float thz, float tlx, float tly, float tlz,
                                           float e2, float rx, const CutoffTest& ct, float& bx, float& by,
@@ -676,21 +676,29 @@ __device__ __forceinline__ void comp_quad(WaveList& xl, uint32_t& nx, uint32_t t
     const f32x4 x4 = *reinterpret_cast<const f32x4*>(&hl[0][k]);
     const f32x4 y4 = *reinterpret_cast<const f32x4*>(&hl[1][k]);
     const f32x4 z4 = *reinterpret_cast<const f32x4*>(&hl[2][k]);
-    const f32x4 a4 = *reinterpret_cast<const f32x4*>(&hl[3][k]);
-    const f32x4 b4 = *reinterpret_cast<const f32x4*>(&hl[4][k]);
-    const f32x4 c4 = *reinterpret_cast<const f32x4*>(&hl[5][k]);
+    f32x4 a4, b4, c4;
+    if constexpr (COMP) {
+        a4 = *reinterpret_cast<const f32x4*>(&hl[3][k]);
+        b4 = *reinterpret_cast<const f32x4*>(&hl[4][k]);
+        c4 = *reinterpret_cast<const f32x4*>(&hl[5][k]);
+    }
     float dx[4], dy[4], dz[4], r2[4], inv[4];
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
         // thx + 0.5 (-2 s_x) rounds once, to the same value as thx - s_x
-        dx[u] = __builtin_fmaf(x4[u], 0.5f, thx) + (tlx - a4[u]);
-        dy[u] = __builtin_fmaf(y4[u], 0.5f, thy) + (tly - b4[u]);
-        dz[u] = __builtin_fmaf(z4[u], 0.5f, thz) + (tlz - c4[u]);
+        dx[u] = __builtin_fmaf(x4[u], 0.5f, thx);
+        dy[u] = __builtin_fmaf(y4[u], 0.5f, thy);
+        dz[u] = __builtin_fmaf(z4[u], 0.5f, thz);
+        if constexpr (COMP) {
+            dx[u] += tlx - a4[u];
+            dy[u] += tly - b4[u];
+            dz[u] += tlz - c4[u];
+        }
         r2[u] = __builtin_fmaf(dx[u], dx[u], e2);
         r2[u] = __builtin_fmaf(dy[u], dy[u], r2[u]);
         r2[u] = __builtin_fmaf(dz[u], dz[u], r2[u]);
     }
-    if constexpr (!CUT) {
+    if constexpr (COMP && !CUT) {
         const float m = fminf(fminf(r2[0], r2[1]), fminf(r2[2], r2[3]));
         if (__builtin_expect(__ballot(m < rx) != 0ull, 0)) {
     #pragma unroll
@@ -727,46 +735,55 @@ __device__ __forceinline__ void comp_quad(WaveList& xl, uint32_t& nx, uint32_t t
 
 // Default precision, one target per lane.  The wave's 64 targets are four groups
 // of 16 (as the matrix cores take them), a source tile up to 16 groups of 16,
-// and each of the 64 pairs of groups is summed in one of two forms, chosen by
-// the gap between the groups' bounding boxes:
+// and each of the 64 pairs of groups is summed in one of three forms, chosen by
+// the gap between the groups' bounding boxes (rho: the half-diagonal of the
+// workgroup's targets, whose centre is the origin; u = 2^-24):
 //
-// Far (gap above kFarFraction rho, rho the half-diagonal of the workgroup's
-// targets, whose centre is the origin):
+// Far (gap above kFarFraction rho = 4/7 rho):
 //     r^2 = (|s|^2 + eps^2) + |t|^2 - 2 t.s    on the matrix cores,
 //     sum d w = t sum w - sum s w,             w = (r^2)^{-3/2},
 // with s and t the hi parts.  One v_mfma_f32_16x16x32_bf16 gives r^2 of a
 // block, which leaves 6 VALU instructions and the reciprocal square root per
 // pair.  Every FP32 factor is held as three bf16 parts (exactly its 24 bits);
 // the products of parts are exact and accumulated in FP32, and those of order
-// 2^-27 (second with third part and below) are left out, so r^2 carries fewer
-// roundings than a chain of FP32 operations (a 256-source tile against 64-bit
-// sums: largest error 2.7e-7 against 7.6e-7, rms 7.6e-8 against 2.4e-7).  The
-// partial results of r^2 are at most (|s| + |t|)^2 <= ((2 + f)/f)^2 |d|^2 = 121
-// |d|^2 at f = kFarFraction = 1/5, reached only by pairs at the very edge of the
-// far region.  t sum w - sum s w is formed per tile in FP64 from the tile's FP32
-// sums, and the tiles add up in FP64 (launches level with FP32 there; rms error of
-// the field at 1e5 holes 3.2e-8 -> 2.8e-8 of its rms, at 3e5 2.6e-8 -> 2.1e-8).
+// 2^-27 (second with third part and below) are left out.  The error of r^2 is at
+// most 2.1 u (|s| + |t|)^2, the largest of 1e7 random pairs at gaps of 0.15 to 5
+// rho with |t| = rho (rms 0.34; four FP32 operations on the vector units 2.9 and
+// 0.34 to 0.63), and (|s| + |t|) / |d| is at most 2/f + 1 = 4.5 at a gap of f rho
+// = 4/7 rho: 64 u per term, with 11 u of the dropped lo parts, 4 u (1 + 1/f), and 8 u
+// of r^-3 and the products 83 u.  (At f = 1/5 the same sum is 413 u, and single
+// terms at the very edge were off by up to 1.04e-5; now 1.9e-6.)  t sum w - sum s w is
+// formed per tile in FP64 from the tile's FP32 sums, and the tiles add up in FP64
+// (launches level with FP32 there; rms error of the field at 1e5 holes 3.2e-8 ->
+// 2.8e-8 of its rms, at 3e5 2.6e-8 -> 2.1e-8).
+//
+// Plain (gap above kPlainFraction rho = rho/4): the difference of the hi parts,
+// 4 u (1 + 1/f) = 20 u from the coordinates.
 //
 // Near (all others): the compensated difference (hi and lo parts) in every
 // pair, and the exact sum for pairs within kExactRadius eps.  No pair needs a
 // test against a close-pair radius, so the loop has no branch that a dense cloud
 // takes.
 //
-// Share of near pairs: 0.01 of a 1e5-hole cloud, 0.04 of 2e4, 0.08 of 1e4, 0.6 of
-// 1000.  Error against the FP64 mode (2-norm of the field): 3.1e-8 at 1e5 holes,
-// 3.8e-8 at 2e4, 5.0e-8 on a 400-cloud batch; a VALU kernel that took r^2 as four
-// FP32 operations per pair in tiles beyond rho and checked differences within
-// measured 7.2e-8, 9.7e-8 and 1.1e-7.
+// Shares of near and plain pairs: 0.008 and 0.019 of a 1e5-hole cloud, 0.05 and
+// 0.10 of 2e4, 0.09 and 0.18 of 1e4, 0.69 and 0.29 of 1000.  us per step with the
+// far limit at rho/5, with it at 4 rho/7 and everything within near, and as it is:
+// 1e5 holes 2032, 2124, 2083; 3e5 17487, 17952, 17653; 2e4 141, 157, 148; 400 clouds
+// of 200-20000 holes 4291, 5185, 4772; the 62354-hole track 808, 814, 814.  (Far
+// where |s| + |t| of the two groups' boxes is within 4.5 gaps, at any rho: level, the
+// track 3 % slower.)  Largest error of a hole, in sums of its term magnitudes, and
+// rms error in rms fields: 5.4e-8 and 2.5e-8 at 1e5 holes, 5.9e-8 and 3.7e-8 at 2e4,
+// 1.5e-7 and 5.8e-8 on the track, 1.6e-7 and 3.4e-8 on 40 clouds; a VALU kernel that
+// took r^2 as four FP32 operations per pair in tiles beyond rho and checked
+// differences within: 8.0e-8 and 7.2e-8, 1.1e-7 and 1.1e-7, 1.5e-6 and 2.0e-7, 6.6e-7
+// and 9.5e-8.
 //
 // What bounds it: VALU issue.  The far loop runs at 24.7 cycles per wave and
 // source (2.4 GHz; its launch run twice over the same groups, minus once), of
 // which the reciprocal square root takes 8.1 and six full-rate instructions
 // 14.4; the matrix instructions run beside the transcendentals.  The VALU form
-// of the same pair took 40.  Per launch, that kernel against this one: 1000 holes 16.1
-// and 12.2 us, 1e4 60 and 46 us, 1e5 2.53 and 1.89 ms, 3e5 21.9 and 16.4 ms, the
-// 62354-hole track 1.17 and 0.87 ms, 400 clouds of 200-20000 holes 5.2 and 4.5
-// ms.  The rest of a launch is staging, classification and the barrier of each
-// tile.
+// of the same pair took 40.  The rest of a launch is staging, classification and
+// the barrier of each tile.
 //
 // The 32 products of the contraction: eight for each of the lanes' four
 // quarters q (A: source lane % 16, B: target lane % 16):
@@ -780,7 +797,8 @@ __device__ __forceinline__ void comp_quad(WaveList& xl, uint32_t& nx, uint32_t t
 // Four waves per SIMD: 128 registers hold four groups' operands, r^2 and sums.
 // Two groups at a time in 96 registers (five waves) spill and measured 8 %
 // slower at 3e5 holes.
-constexpr double kFarFraction = 0.2;
+constexpr double kFarFraction = 4.0 / 7.0;
+constexpr double kPlainFraction = 0.25;
 // A padding source: its r^-3 underflows to 0 in either form.
 constexpr float kPadS = 3.0e38f;  // |s|^2
 constexpr float kPadX = 2.0e19f;  // -2 s_x of the difference form
@@ -916,6 +934,8 @@ __device__ __forceinline__ void matrix_item(const FieldArgs& a, const FieldItem 
     const double rho2 = hx * hx + hy * hy + hz * hz;
     const float far2 =
         uniform((float)(1.0001 * fmax(kFarFraction * kFarFraction * rho2, a.acc_box2)));
+    const float plain2 =
+        uniform((float)(1.0001 * fmax(kPlainFraction * kPlainFraction * rho2, a.acc_box2)));
     const float glx = (float)(gl_x - ox), gly = (float)(gl_y - oy), glz = (float)(gl_z - oz),
                 ghx = (float)(gh_x - ox), ghy = (float)(gh_y - oy), ghz = (float)(gh_z - oz);
     const double eps2d = (double)a.eps2;
@@ -1062,7 +1082,7 @@ __device__ __forceinline__ void matrix_item(const FieldArgs& a, const FieldItem 
     }
     float e2 = a.eps2;
     float rx = ts < nt ? a.acc2 : 0.0f;  // lanes past the last target record nothing
-    asm volatile("" : "+v"(e2), "+v"(rx));  // vector registers (see comp_quad)
+    asm volatile("" : "+v"(e2), "+v"(rx));  // vector registers (see diff_quad)
     CutoffTest ct;
     float in2 = 0.0f, near_a2 = 0.0f;
     if constexpr (CUT) {
@@ -1090,7 +1110,7 @@ __device__ __forceinline__ void matrix_item(const FieldArgs& a, const FieldItem 
         const MatrixLds::Tile& S = L.tile[buf];
         const uint32_t cnt = CUT ? min(16u, n_list - i * 16u) * 16u : min((uint32_t)UNIT, ns - src0);
         // lane 16 g + c: target group g of the wave against source group c
-        uint64_t far_b, near_b, in_b = 0;
+        uint64_t far_b, plain_b, near_b, in_b = 0;
         {
             const float gx = fmaxf(0.0f, fmaxf(S.gbox[0][col] - ghx, glx - S.gbox[3][col]));
             const float gy = fmaxf(0.0f, fmaxf(S.gbox[1][col] - ghy, gly - S.gbox[4][col]));
@@ -1105,7 +1125,9 @@ __device__ __forceinline__ void matrix_item(const FieldArgs& a, const FieldItem 
                 in_b = __ballot(mx * mx + my * my + mz * mz < in2);
             }
             far_b = __ballot(valid && g2 > far2);
-            near_b = __ballot(valid) & ~far_b;
+            const uint64_t plain = __ballot(g2 > plain2), all = __ballot(valid);
+            plain_b = all & plain & ~far_b;
+            near_b = all & ~plain & ~far_b;
         }
         const uint32_t far_g[4] = {(uint32_t)far_b & 0xFFFFu, (uint32_t)far_b >> 16,
                                    (uint32_t)(far_b >> 32) & 0xFFFFu, (uint32_t)(far_b >> 48)};
@@ -1219,20 +1241,26 @@ __device__ __forceinline__ void matrix_item(const FieldArgs& a, const FieldItem 
         // near blocks: the lanes' targets of group g, each lane four sources of a group
         for (int g = 0; g < 4; ++g) {
             uint32_t m = (uint32_t)(near_b >> (16 * g)) & 0xFFFFu;
-            if (m == 0u) continue;
+            uint32_t p = (uint32_t)(plain_b >> (16 * g)) & 0xFFFFu;
+            if ((m | p) == 0u) continue;
             const int tg = g * 16 + col;
             const float hx_ = __shfl(thx, tg), hy_ = __shfl(thy, tg), hz_ = __shfl(thz, tg);
             const float lx_ = __shfl(tlx, tg), ly_ = __shfl(tly, tg), lz_ = __shfl(tlz, tg);
             const float rx_ = __shfl(rx, tg);
             float bx = 0.0f, by = 0.0f, bz = 0.0f;
-            do {
-                // sources past the last one are staged too, far enough away to
-                // add nothing
+            // sources past the last one are staged too, far enough away to add nothing
+            while (m) {
                 const uint32_t k = (uint32_t)__builtin_ctz(m) * 16u + (uint32_t)q * 4u;
                 m &= m - 1u;
-                comp_quad<CUT>(L.xl[wave], nx, (uint32_t)(wave * 64 + tg), src0 + k, S.hl, k,
-                               hx_, hy_, hz_, lx_, ly_, lz_, e2, rx_, ct, bx, by, bz);
-            } while (m);
+                diff_quad<CUT, true>(L.xl[wave], nx, (uint32_t)(wave * 64 + tg), src0 + k, S.hl, k,
+                                     hx_, hy_, hz_, lx_, ly_, lz_, e2, rx_, ct, bx, by, bz);
+            }
+            while (p) {
+                const uint32_t k = (uint32_t)__builtin_ctz(p) * 16u + (uint32_t)q * 4u;
+                p &= p - 1u;
+                diff_quad<CUT, false>(L.xl[wave], nx, (uint32_t)(wave * 64 + tg), src0 + k, S.hl, k,
+                                      hx_, hy_, hz_, lx_, ly_, lz_, e2, rx_, ct, bx, by, bz);
+            }
             const float tx = add_quarters(bx), ty = add_quarters(by), tz = add_quarters(bz);
             ex += q == g ? tx : 0.0f;
             ey += q == g ? ty : 0.0f;
