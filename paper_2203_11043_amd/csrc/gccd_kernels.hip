@@ -204,8 +204,13 @@ __device__ __forceinline__ void exact_add(const FieldArgs& a, uint32_t t, uint32
 // wave counts its entries in a scalar register and each lane finds its place
 // from the ballot.  (In the dense core of a cloud two of five turns of the
 // near loop record a pair, and the atomic's round trip through LDS stalled
-// the wave each time.)
-constexpr int kWaveCap = 512;
+// the wave each time.)  The four lists hold as many pairs as ExactList.  Lists that
+// fill (a large softening: its radius holds many pairs) cost their FP64 terms and
+// atomics: 10,007 holes at a softening of 0.1 um 136 us per step with 128 entries,
+// 177 with 256, 268 with 512 (173 with the one ExactList per workgroup that the
+// kernel before had); 1e5 holes 4.55, 4.62, 4.89 ms (4.73).  At 1 nm no list fills
+// outside clumps far denser than a fresh cloud.
+constexpr int kWaveCap = kExactCap / (kFieldThreads / 64);
 
 struct WaveList {
     uint32_t src[kWaveCap];
