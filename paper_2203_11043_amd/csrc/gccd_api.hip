@@ -40,6 +40,11 @@ constexpr int kPoll = 32;                       // steps between host reads of t
 constexpr int kKeepSmall = 16, kKeepLarge = 4;
 constexpr double kKeepPairs = 4e8;              // pairs of the load's events: the line
 constexpr double kKeepLongPairs = 2e9, kKeepLongPs = 40.0;
+// Holes per source tile from which a list is kept: a kept step takes a turn for each
+// tile, however few holes it has.  Kept 16 steps against sorted every step: 65536
+// events of 1 hole 972 and 618 us per step, 16384 of 4 237 and 169, 6553 of 10 109
+// and 97, 4096 of 16 75 and 76, 1985 of 33 51 and 68.
+constexpr int64_t kKeepFill = 16;
 static_assert(kPoll % kKeepSmall == 0 && kPoll % kKeepLarge == 0,
               "stretches start with a fresh list");
 // Pair interactions per step from which the exact path pipelines its list
@@ -1651,7 +1656,8 @@ int gccd_run(gccd_ctx* c, double dt_ps, int64_t max_steps, int64_t* steps_done,
     bool pipelined = c->pipe_mode == 1;
     // A serial list with every hole a source is sorted only every few steps, at
     // multiples of that number, so that a split of a run changes nothing.
-    const bool keep_ok = c->list_mode && !use_closure && c->p.collected_are_sources;
+    const bool keep_ok = c->list_mode && !use_closure && c->p.collected_are_sources &&
+                         c->n >= kKeepFill * (int64_t)c->n_tiles;
     double load_pairs = 0.0;
     for (uint32_t e = 0; e < c->n_events; ++e) {
         const double ne = (double)(c->off_h[e + 1] - c->off_h[e]);

@@ -16,6 +16,8 @@
 #include "gccd_sort_dev.h"
 
 #include <math.h>
+
+#include <algorithm>
 #include <type_traits>
 
 namespace gccd {
@@ -1121,7 +1123,8 @@ __device__ __forceinline__ void matrix_item(const FieldArgs& a, const FieldItem 
             const float gy = fmaxf(0.0f, fmaxf(S.gbox[1][col] - ghy, gly - S.gbox[4][col]));
             const float gz = fmaxf(0.0f, fmaxf(S.gbox[2][col] - ghz, glz - S.gbox[5][col]));
             const float g2 = gx * gx + gy * gy + gz * gz;
-            bool valid = (uint32_t)col * 16u < cnt;
+            // (a group without targets, its box empty, has no block)
+            bool valid = (uint32_t)col * 16u < cnt && glx <= ghx;
             if constexpr (CUT) {
                 valid = valid && g2 < near_a2;
                 const float mx = fmaxf(S.gbox[3][col] - glx, ghx - S.gbox[0][col]);
@@ -2135,8 +2138,8 @@ __device__ __forceinline__ double unit_open(uint32_t w) {
 //   list mode (Coulomb on): one thread per slot of the sorted list; every
 //     carrier keeps its slot in the next (unsorted) list with its new key,
 //     collected holes copying theirs through; the next sort restores order.
-//   kept list (a.keep): one workgroup per source tile, one thread per slot.  The
-//     order stays, so no key is made or sorted: the step writes the slots' new
+//   kept list (a.keep): a source tile per turn of a workgroup, one thread per slot.
+//     The order stays, so no key is made or sorted: the step writes the slots' new
 //     positions and its tile's boxes.  1,000 holes, latency-bound: 7.1 us.
 //   carrier mode: drift_steps.
 // ---------------------------------------------------------------------------
@@ -2252,18 +2255,21 @@ __device__ __forceinline__ void step_body(const StepArgs& a) {
     // merges; else every slot leaves its key in place
     const bool runs = MODE == kStepList && a.sort_runs != 0;
     __shared__ uint64_t sk[kStepThreads];
-    // KEEP: workgroup g owns source tile g, one slot per thread (one turn)
-    uint32_t te = 0u, toff = 0u, tne = a.n_all, ti = blockIdx.x * kTile + threadIdx.x;
-    if (KEEP && !a.one_event) {
-        te = a.tile_event[blockIdx.x];
-        toff = a.ev_off[te];
-        tne = a.ev_off[te + 1] - toff;
-        ti = (blockIdx.x - a.ev_tile[te]) * kTile + threadIdx.x;
-    }
+    // KEEP: each turn takes one source tile, one slot per thread
+    uint32_t te = 0u, toff = 0u, tne = a.n_all, ti = 0u;
     double px = 0.0, py = 0.0, pz = 0.0;  // KEEP: the slot's position
-    const uint32_t end = KEEP ? gridDim.x * kStepThreads : a.n_all;
-    for (uint32_t base = blockIdx.x * kStepThreads; base < end;
-         base += gridDim.x * kStepThreads) {
+    const uint32_t turns = KEEP ? a.n_tiles : (a.n_all + kStepThreads - 1) / kStepThreads;
+    for (uint32_t turn = blockIdx.x; turn < turns; turn += gridDim.x) {
+        const uint32_t base = turn * kStepThreads;  // (not KEEP)
+        if constexpr (KEEP) {
+            ti = turn * kTile + threadIdx.x;
+            if (!a.one_event) {
+                te = a.tile_event[turn];
+                toff = a.ev_off[te];
+                tne = a.ev_off[te + 1] - toff;
+                ti -= a.ev_tile[te] * kTile;
+            }
+        }
         const uint32_t slot = KEEP ? toff + ti : base + threadIdx.x;
         uint64_t run_key = ~0ull;  // this slot's new key, when the keys form runs
         bool keep = false;
@@ -2414,15 +2420,16 @@ __device__ __forceinline__ void step_body(const StepArgs& a) {
                 a.keys_out[slot] = key;
         }
         kept += (uint32_t)__popcll(__ballot(keep));
+        if constexpr (KEEP) {
+            __shared__ double red[6][kTile / 64];
+            tile_boxes(turn, threadIdx.x, ti < tne, px, py, pz, a.tile_box, a.box_stride, red);
+            if (turn + gridDim.x < turns) __syncthreads();  // red is written again
+        }
         if (runs) {  // uniform: every thread of the workgroup takes each turn
             const uint32_t m = min((uint32_t)kStepThreads, a.n_all - base);
             const uint64_t sorted = sort_block_keys(run_key, m, sk);
             if (threadIdx.x < m) a.keys_out[base + threadIdx.x] = sorted;
         }
-    }
-    if constexpr (KEEP) {
-        __shared__ double red[6][kTile / 64];
-        tile_boxes(blockIdx.x, threadIdx.x, ti < tne, px, py, pz, a.tile_box, a.box_stride, red);
     }
     // one atomic per workgroup for each count: a counter taking one per wave
     // and grid-stride turn (2.6e5 at 2^24 holes) serialised the whole step
@@ -2553,10 +2560,14 @@ __global__ __launch_bounds__(kDriftSum) void drift_counts(StepArgs a, uint32_t n
 }
 
 hipError_t launch_step(const StepArgs& a, uint32_t n_slots, hipStream_t s) {
-    static_assert(kTile == kStepThreads, "a workgroup of the kept step owns one source tile");
+    static_assert(kTile == kStepThreads, "a turn of the kept step takes one source tile");
     if (a.keep) {
         if (!a.list_mode || !a.sources_all || a.n_tiles == 0) return hipErrorInvalidValue;
-        step_update<kStepKept><<<a.n_tiles, kStepThreads, 0, s>>>(a);
+        // The workgroups' atomics on the same two words queue up (24 ns per workgroup):
+        // 6553 events of 10 holes, a tile each, take 198 us per step in as many
+        // workgroups, 109 in 512 (154 in 256, 112 in 1024); 1700 events of 1000 holes
+        // 880, 849 (889, 862).
+        step_update<kStepKept><<<std::min(a.n_tiles, 512u), kStepThreads, 0, s>>>(a);
     } else if (a.list_mode && n_slots <= kRankMax) {
         step_update<kStepShort>
             <<<(n_slots + kStepThreads - 1) / kStepThreads, kStepThreads, 0, s>>>(a);
