@@ -1,0 +1,45 @@
+"""The block mode rounds coordinates relative to the centre of each workgroup's
+targets, so its error grows with the extent of the blocks: its list is sorted
+every step.  A step deep between the sorts of the other modes has to move every
+hole by the field that gccd_field gives at the positions before it (that of a
+fresh list): at constant mobility its displacement is mu E dt and the diffusion
+step, which the oracle's normals give, in FP64.  In an order kept since the load
+the field differs by about 1e-6 of itself, 1e-7 um."""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("first", ["block", "default"])
+@pytest.mark.parametrize("n", [700, 10007])
+def test_field_of_a_step(n, first):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import oracle
+    from paper_2203_11043_amd import gccd as g
+    from paper_2203_11043_amd import workloads as W
+    w = W.single_cloud(n, 3, 300.0)
+    d = dict(W.DEVICE, mobility_model=1)
+    dev = [torch.as_tensor(v).cuda() for v in (w.x, w.y, w.z)]
+    run = g.gccd_init(g.Params.from_device(d))
+    g.gccd_set_precision(run, first)
+    g.gccd_load(run, *dev)
+    g.gccd_run(run, 10.0, 14)
+    g.gccd_set_precision(run, "block")
+    # the step after 14 others, with the field of the list that stands before it
+    before, _ = g.gccd_positions(run, n)
+    E = g.gccd_field(run, n).cpu().numpy()
+    g.gccd_run(run, 10.0, 1)
+    after, _ = g.gccd_positions(run, n)
+    before, after = before.cpu().numpy(), after.cpu().numpy()
+    mu = oracle.mobility(0.0, d["temperature_K"], 1)
+    sigma = np.sqrt(2.0 * oracle.thermal_voltage(d["temperature_K"]) * mu * 1e-11) * 1e4
+    normals = np.array([oracle.normals(d["seed"], j, 14) for j in range(n)]).T
+    E[2] += d["a1"] * before[2] - d["a2"]
+    want = before + mu * E * 1e-11 * 1e4 + sigma * normals
+    # FP64 rounding of positions of some 500 um and of the normals
+    assert np.max(np.abs(after - want)) <= 1e-11
+    g.gccd_destroy(run)
