@@ -30,15 +30,20 @@ constexpr int kPoll = 32;                       // steps between host reads of t
 // Steps that one order of a serial list serves (every hole a source).  The order
 // sets only which holes share blocks and boxes, never which are summed; keeping
 // it saves the sort and the gather after it and costs the Eq. (6) kernel some
-// of its far blocks as holes move apart.  us per step, order kept 1, 4, 8, 16, 32
-// steps (measured with sorts that took about twice as long):
-//   1,000 holes  37.3 23.9 21.8 19.2 20.4     30,000  274 245 248 267 308
-//   10,007       94.9 67.9 64.7 64.6 69.9     70,000  1054 1041 1071 1152 1146
-// With longer steps holes part sooner.  Steps of 160 and 1000 ps, order kept 1, 4
-// and 16 steps: 30,000 holes 287 254 291 and 316 265 332, 70,000 holes 996 1022
-// 1286 and 738 833 1273; so such loads keep no order above 40 ps.
+// of its far blocks as holes move apart, more so with longer steps.  us per step
+// over 64 steps from the load, order kept 1, 4, 8 and 16 steps:
+//                  steps of 10 ps              steps of 1000 ps
+//   1,000 holes     23.4  18.2  17.2  16.8      22.8  17.5  16.6  16.1
+//   8,000           56.6  46.3  45.0  44.0      63.9  47.8  46.3  49.1
+//   10,007          70.1  57.9  56.7  57.2      80.3  60.6  59.4  62.7
+//   12,000          82.3  69.4  69.4  71.5      89.1  67.1  67.6  72.1
+//   20,000           161   142   144   151       152   127   133   147
+// (40 and 160 ps lie close to 10.)  So 16 steps up to 1.2e8 pairs, then 4.  Above 2e9
+// pairs 4 steps gain 1.7 % at 10 ps (70,000 holes 1021 and 1004) and nothing from 40
+// ps on (1019 and 1019; at 160 and 1000 ps with older kernels 996 and 1022, 738 and
+// 833): no order is kept there.
 constexpr int kKeepSmall = 16, kKeepLarge = 4;
-constexpr double kKeepPairs = 4e8;              // pairs of the load's events: the line
+constexpr double kKeepPairs = 1.2e8;            // pairs of the load's events: the line
 constexpr double kKeepLongPairs = 2e9, kKeepLongPs = 40.0;
 // Holes per source tile from which a list is kept: a kept step takes a turn for each
 // tile, however few holes it has.  Kept 16 steps against sorted every step: 65536
