@@ -945,6 +945,7 @@ __device__ __forceinline__ void matrix_item(const FieldArgs& a, const FieldItem 
         uniform((float)(1.0001 * fmax(kPlainFraction * kPlainFraction * rho2, a.acc_box2)));
     const float glx = (float)(gl_x - ox), gly = (float)(gl_y - oy), glz = (float)(gl_z - oz),
                 ghx = (float)(gh_x - ox), ghy = (float)(gh_y - oy), ghz = (float)(gh_z - oz);
+    const bool has_targets = (ts & ~15u) < nt;  // of this lane's group
     const double eps2d = (double)a.eps2;
 
     double qx = 0.0, qy = 0.0, qz = 0.0;  // this lane's source of the next tile
@@ -1123,8 +1124,7 @@ __device__ __forceinline__ void matrix_item(const FieldArgs& a, const FieldItem 
             const float gy = fmaxf(0.0f, fmaxf(S.gbox[1][col] - ghy, gly - S.gbox[4][col]));
             const float gz = fmaxf(0.0f, fmaxf(S.gbox[2][col] - ghz, glz - S.gbox[5][col]));
             const float g2 = gx * gx + gy * gy + gz * gz;
-            // (a group without targets, its box empty, has no block)
-            bool valid = (uint32_t)col * 16u < cnt && glx <= ghx;
+            bool valid = (uint32_t)col * 16u < cnt && has_targets;
             if constexpr (CUT) {
                 valid = valid && g2 < near_a2;
                 const float mx = fmaxf(S.gbox[3][col] - glx, ghx - S.gbox[0][col]);
