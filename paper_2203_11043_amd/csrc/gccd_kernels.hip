@@ -1340,10 +1340,15 @@ void field_queue_matrix(FieldArgs a) {
 // and the sums.  Bound by VALU issue, 17 FP64 instructions at 4.3 cycles and the
 // estimate at 16: 6.5 ms at 1e5 holes, where 1/(q sqrt q) with IEEE square root
 // and division took 12.6.  q is held finite so that a pair farther apart than
-// 1e150 um adds nothing.  Same work items, tiles
+// 1e150 um adds nothing; since that also hides a NaN from r^-3, a hole with any NaN
+// coordinate takes part with three (whole_nan).  Same work items, tiles
 // and source dealing as field_tiles; the FP64 sum of group g is written as
 // the FP32 pair hi (group g) and lo (group G + g, G the event's groups),
 // which the FP64 reduction of the groups adds back exactly.
+__device__ __forceinline__ void whole_nan(double& x, double& y, double& z) {
+    if (x != x || y != y || z != z) x = y = z = __builtin_nan("");
+}
+
 template <int TPT>
 __global__ __launch_bounds__(kFieldThreads) void field_tiles_f64(FieldArgs a) {
     __shared__ double sh[2][3][kTile];
@@ -1373,6 +1378,7 @@ __global__ __launch_bounds__(kFieldThreads) void field_tiles_f64(FieldArgs a) {
             px[t] = a.px[off + ts];
             py[t] = a.py[off + ts];
             pz[t] = a.pz[off + ts];
+            whole_nan(px[t], py[t], pz[t]);
         }
         ax[t] = ay[t] = az[t] = 0.0;
     }
@@ -1385,6 +1391,7 @@ __global__ __launch_bounds__(kFieldThreads) void field_tiles_f64(FieldArgs a) {
             qx = a.px[off + i];
             qy = a.py[off + i];
             qz = a.pz[off + i];
+            whole_nan(qx, qy, qz);
         }
     };
     auto stage = [&](int b) {

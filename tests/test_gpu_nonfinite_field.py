@@ -13,7 +13,7 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("value", [np.nan, np.inf])
 @pytest.mark.parametrize("axis", [0, 1])
 @pytest.mark.parametrize("holes", [1, 300])
-@pytest.mark.parametrize("mode", ["default", "block", "event", "absolute", "compensated"])
+@pytest.mark.parametrize("mode", ["default", "block", "event", "absolute", "compensated", "fp64"])
 def test_field(mode, holes, axis, value):
     if not torch.cuda.is_available():
         pytest.skip("no GPU")
