@@ -949,10 +949,30 @@ int ensure_side(gccd_ctx* c) {
     return GCCD_OK;
 }
 
+// The closure's far field of target slots [0, nt) into group S: deposit, network,
+// interpolation.
+int closure_far(gccd_ctx* c, uint32_t nt, bool with_net) {
+    const uint32_t n = (uint32_t)c->n;
+    hipStream_t st = c->stream;
+    GCCD_HIP(c, launch_deposit(c->ps[0], c->ps[1], c->ps[2], n, c->gp, c->acc, st));
+    GCCD_HIP(c, launch_rho(c->acc, c->act + act_offset(kX0), c->rho_f32, st));
+    float* far = c->part + (size_t)c->near_chunks * 3 * n;
+    if (!with_net) {
+        GCCD_HIP(c, launch_fill_u32(reinterpret_cast<uint32_t*>(far), 3ull * n, 0u, st));
+        return GCCD_OK;
+    }
+    if (int r = run_network(c); r != GCCD_OK) return r;
+    GCCD_HIP(c, launch_far(c->fgrid, c->gp, c->ps[0], c->ps[1], c->ps[2], nt, far, far + n,
+                           far + 2 * (size_t)n, st));
+    return GCCD_OK;
+}
+
 // The closure's field of the current sorted list: near chunks into groups
 // [0, S), the far field of target slots [0, nt) into group S.  Once the grid is
 // placed the two parts are independent: the near sum, one launch that fills
 // the chip, runs on the side stream beside the far part's chain of short ones.
+// The context's stream waits for it also where a launch of the far part fails: the
+// next call writes what it reads.
 int closure_field(gccd_ctx* c, bool targets_all, uint32_t nt, bool with_net) {
     const uint32_t n = (uint32_t)c->n;
     const double eps2 = c->p.softening_um * c->p.softening_um;
@@ -964,21 +984,12 @@ int closure_field(gccd_ctx* c, bool targets_all, uint32_t nt, bool with_net) {
     GCCD_HIP(c, hipStreamWaitEvent(c->side, c->ev_grid, 0));
     FieldArgs fa = field_args(c, targets_all);
     GCCD_HIP(c, launch_near(fa, c->gp, n, c->n_items, (uint32_t)c->near_chunks, c->side));
-    GCCD_HIP(c, hipEventRecord(c->ev_near, c->side));
-    GCCD_HIP(c, launch_deposit(c->ps[0], c->ps[1], c->ps[2], n, c->gp, c->acc, st));
-    GCCD_HIP(c, launch_rho(c->acc, c->act + act_offset(kX0), c->rho_f32, st));
-    if (with_net) {
-        int r = run_network(c);
-        if (r != GCCD_OK) return r;
-    }
-    float* far = c->part + (size_t)c->near_chunks * 3 * n;
-    if (with_net)
-        GCCD_HIP(c, launch_far(c->fgrid, c->gp, c->ps[0], c->ps[1], c->ps[2], nt, far, far + n,
-                               far + 2 * (size_t)n, st));
-    else
-        GCCD_HIP(c, launch_fill_u32(reinterpret_cast<uint32_t*>(far), 3ull * n, 0u, st));
-    GCCD_HIP(c, hipStreamWaitEvent(st, c->ev_near, 0));
-    return GCCD_OK;
+    hipError_t e = hipEventRecord(c->ev_near, c->side);
+    const int r = e == hipSuccess ? closure_far(c, nt, with_net) : GCCD_OK;
+    if (e == hipSuccess) e = hipStreamWaitEvent(st, c->ev_near, 0);
+    if (e == hipSuccess) return r;
+    (void)hipStreamSynchronize(c->side);
+    return fail(c, GCCD_E_DEVICE, "closure: joining the near sum", e);
 }
 
 }  // namespace
