@@ -710,6 +710,14 @@ int gather(gccd_ctx* c) {
     return GCCD_OK;
 }
 
+// The positions in a kept list's order, where a call between runs left another's.
+int gather_kept(gccd_ctx* c) {
+    if (!c->kept || c->gathered) return GCCD_OK;
+    if (int r = gather(c); r != GCCD_OK) return r;
+    c->gathered = true;
+    return GCCD_OK;
+}
+
 // The sorted list from the keys in `unsorted` (clobbered; with run0 > 0 it
 // holds sorted runs of run0 keys): sort into keys[cur], count each event's
 // travelling holes, gather the positions.
@@ -1501,6 +1509,7 @@ int gccd_autotune(gccd_ctx* c, int32_t* targets_per_thread, int32_t* source_chun
     double best_ms = -1.0;
     int best_t = c->tpt_fixed, best_s = c->chunks_fixed, best_u = c->unit_fixed;
     if (c->list_mode && c->n_active > 0) {
+        if (int r = gather_kept(c); r != GCCD_OK) return r;
         hipEvent_t e0, e1;
         GCCD_HIP(c, hipEventCreate(&e0));
         GCCD_HIP(c, hipEventCreate(&e1));
@@ -1701,10 +1710,8 @@ int gccd_run(gccd_ctx* c, double dt_ps, int64_t max_steps, int64_t* steps_done,
         int r = finish_list(c, c->ukeys[c->u]);
         if (r != GCCD_OK) return r;
         c->kept = false;
-    } else if (c->kept && !c->gathered) {
-        int r = gather(c);
-        if (r != GCCD_OK) return r;
-        c->gathered = true;
+    } else if (int r = gather_kept(c); r != GCCD_OK) {
+        return r;
     }
     // Puts the list state in line with `pipelined`.
     auto enter_mode = [&]() -> int {
