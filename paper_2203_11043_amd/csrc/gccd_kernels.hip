@@ -1735,7 +1735,12 @@ template <int PREC>
 static hipError_t launch_field_prec(const FieldArgs& a, int tpt, uint32_t n_items,
                                     hipStream_t s) {
     switch (tpt) {
-        case 1: field_tiles<1, PREC><<<n_items, kFieldThreads, 0, s>>>(a); break;
+        case 1:
+            if constexpr (PREC == GCCD_PRECISION_DEFAULT)
+                return hipErrorInvalidValue;  // the matrix kernel's
+            else
+                field_tiles<1, PREC><<<n_items, kFieldThreads, 0, s>>>(a);
+            break;
         case 2: field_tiles<2, PREC><<<n_items, kFieldThreads, 0, s>>>(a); break;
         case 4: field_tiles<4, PREC><<<n_items, kFieldThreads, 0, s>>>(a); break;
         default: return hipErrorInvalidValue;
