@@ -25,7 +25,9 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 if ROOT not in sys.path:
     sys.path.insert(0, ROOT)
 
-PEAK_FP32_TFLOPS = 157.3       # MI355X published FP32 vector peak
+PEAK_FP32_TFLOPS = 157.3       # MI355X published FP32 vector peak, the yardstick of the pair
+                               # rate; part of a pair's flops (r^2 of far pairs) runs on the
+                               # matrix cores, so the fraction is no use of the vector units
 FLOP_PER_PAIR = 20             # N-body convention for one softened interaction
 TRAFFIC_RECORD = os.path.join(ROOT, "profiles", "field_tiles_cloud_n100000_traffic.json")
 
@@ -485,8 +487,8 @@ def main() -> int:
             "positions": "f64",
             "pair_arithmetic": ("f32, origin per workgroup; far 16x16 blocks of pairs with r^2 on "
                                 "the matrix cores (bf16 parts holding all 24 bits, f32 sums), "
-                                "near blocks with double-single differences, pairs within 64 "
-                                "softening lengths in f64"
+                                "nearer ones with f32 and near ones with double-single "
+                                "differences, pairs within 64 softening lengths in f64"
                                 if s1["targets_per_thread"] == 1 else
                                 "f32, origin per workgroup; pairs closer than rho/4 with "
                                 "double-single differences, pairs within 64 softening lengths "

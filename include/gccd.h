@@ -246,8 +246,10 @@ int gccd_autotune(gccd_ctx* c, int32_t* targets_per_thread, int32_t* source_chun
  *   ABSOLUTE  no origin: FP32 absolute coordinates, as the paper stores them
  *   COMPENSATED  workgroup origins; every pair's difference formed from the
  *             coordinates and their residuals (double-single differences)
- *   FP64      every pair in FP64 (difference, r^2, r^-3 = 1/(q sqrt q)) and
- *             FP64 sums; reference quality, several times slower */
+ *   FP64      every pair in FP64 (difference, r^2, r^-3 = q^(-3/2) from the
+ *             hardware's estimate of 1/sqrt(q), corrected to about 0.4 units
+ *             in the last place) and FP64 sums; reference quality, several
+ *             times slower */
 enum {
     GCCD_PRECISION_DEFAULT = 0,
     GCCD_PRECISION_BLOCK = 1,
@@ -286,8 +288,8 @@ int gccd_set_precision(gccd_ctx* c, int32_t mode);
  * Per-launch timing (gccd_set_timing) needs events around each field
  * launch, which graph replays do not provide: with timing on, GRAPH issues
  * its steps one by one.  Default: GRAPH, the fastest measured on MI355X:
- * replays save the launch gaps of the short steps of small loads (16.4
- * against 16.8 us per step at 1000 holes, 22.5 against 23.0 at 3000)
+ * replays save the launch gaps of the short steps of small loads (16.9
+ * against 17.5 us per step at 1000 holes, 23.0 against 23.6 at 3000)
  * and are level with GRID at 1e5 holes and at the 4096-cloud batch; the
  * queue costs a reset launch and an atomic per item and is never faster.
  * A later load of the same shape on the context replays the same graph.

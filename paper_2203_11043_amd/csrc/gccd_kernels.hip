@@ -1445,11 +1445,13 @@ __global__ __launch_bounds__(kFieldThreads) void field_tiles_f64(FieldArgs a) {
 }
 
 // The near part of the closure's split of Eq. (6): matrix_item with the cutoff.
-// Bound by VALU issue: of 4.1 ms at 1e6 holes, 1.6 go to source groups far from
-// all four target groups, 1.0 to single far blocks, 0.9 to near blocks, 0.1 to
-// staging.  A kernel on difference forms that culled 16-source groups against
-// 64 targets and staged whole tiles took 6.8 ms (the closure step 7.44 against
-// 4.92 ms).
+// Bound by VALU issue: 4.3 ms at 1e6 holes, of which (measured with the far limit at
+// rho/5, 4.1 ms) 1.6 go to source groups far from all four target groups, 1.0 to
+// single far blocks, 0.9 to nearer ones, 0.1 to staging.  A kernel on difference forms
+// that culled 16-source groups against 64 targets and staged whole tiles took 6.8.
+// rms error of the near sum against 64 bits, that kernel and this one, in its rms:
+// 65,536 holes 2.7e-7 and 1.7e-7, 70,001 3.3e-7 and 1.5e-7, 2e5 4.0e-7 and 2.0e-7, 1e6
+// 4.0e-7 and 1.7e-7.
 __global__ __launch_bounds__(kFieldThreads) __attribute__((amdgpu_waves_per_eu(4)))
 void near_matrix(FieldArgs a, const GridParams* gp) {
     __shared__ __align__(16) MatrixLds L;
@@ -1710,11 +1712,13 @@ __global__ __launch_bounds__(64) void near_waves(FieldArgs a, const GridParams* 
     }
 }
 
-// The matrix kernel for loads of at least kNearMatrixMin holes.  Below, near_waves
-// is faster (the closure's field at 5e4 holes 0.21 ms with it, 0.28 with the
-// matrix kernel), and the FP32 rounding of the near sum of a close pair,
-// which the order of summation sets, grows along a run: the smaller loads, which
-// the closure runs for many steps, keep the difference form and its order.
+// The matrix kernel for loads of at least kNearMatrixMin holes, where near_waves'
+// kNearTiles tiles per chunk end.  Below, the two are level: closure step at 2e4,
+// 3.3e4, 5e4 and 65,535 holes 170, 195, 220 and 247 us with near_waves, 170, 197, 216 and
+// 246 with the matrix kernel (measured down to 16,384); rms error of the near sum
+// 2.5e-7, 2.5e-7, 2.0e-7, 2.9e-7 and 2.1e-7, 2.2e-7, 1.3e-7, 1.8e-7.  near_waves stays for
+// its terms and their order, those that these loads' runs have always had: the FP32
+// rounding of a close pair's near sum grows along a run.
 hipError_t launch_near(const FieldArgs& a, const GridParams* gp, uint32_t n, uint32_t n_items,
                        uint32_t n_chunks, hipStream_t s) {
     if (n_items == 0) return hipSuccess;
@@ -2592,7 +2596,7 @@ hipError_t launch_step(const StepArgs& a, uint32_t n_slots, hipStream_t s) {
         // Atomics of many workgroups on the same words queue up (8 ns each): with
         // a set per workgroup a single step of 8 million holes took 755 us.  Above
         // kDriftAtomics workgroups each leaves its counts in memory and a second
-        // launch (3 us) adds them: 157 us.
+        // launch (6 us) adds them: 157 us.
         if (grid <= kDriftAtomics) d.counts = nullptr;
         drift_steps<<<grid, kStepThreads, 0, s>>>(d);
         if (d.counts) drift_counts<<<1, kDriftSum, 0, s>>>(d, grid);
