@@ -1687,8 +1687,13 @@ int gccd_run(gccd_ctx* c, double dt_ps, int64_t max_steps, int64_t* steps_done,
     // block mode, whose error grows with the extent of the blocks, as holes part: at
     // step 16 of a cloud of 10,007 holes it was 1.3e-6 of the rms field in an order kept
     // since the load and 6.7e-7 in a fresh one (the other modes' is the same in both).
+    // Not with 2 or 4 targets per thread in the default mode either, whose kernel tests
+    // each pair of near tiles and branches for the close ones: 10,007 holes in one
+    // chunk, steps of 160 ps, order kept 16 steps and none, 1338 and 1017 us per step
+    // (2 targets) and 2526 and 1885 (4); in the automatic chunks 82 and 99, 121 and 134.
     const bool keep_ok = c->list_mode && !use_closure && c->p.collected_are_sources &&
                          c->precision != GCCD_PRECISION_BLOCK &&
+                         (c->precision != GCCD_PRECISION_DEFAULT || c->tpt == 1) &&
                          c->n >= kKeepFill * (int64_t)c->n_tiles;
     double load_pairs = 0.0;
     for (uint32_t e = 0; e < c->n_events; ++e) {

@@ -1,6 +1,7 @@
 """The block mode rounds coordinates relative to the centre of each workgroup's
-targets, so its error grows with the extent of the blocks: its list is sorted
-every step.  A step deep between the sorts of the other modes has to move every
+targets, so its error grows with the extent of the blocks, and the default mode with 2
+or 4 targets per thread branches for close pairs, the more the older the order:
+their lists are sorted every step.  A step deep between the sorts of the other modes has to move every
 hole by the field that gccd_field gives at the positions before it (that of a
 fresh list): at constant mobility its displacement is mu E dt and the diffusion
 step, which the oracle's normals give, in FP64.  In an order kept since the load
@@ -13,9 +14,10 @@ torch = pytest.importorskip("torch")
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("first", ["block", "default"])
+@pytest.mark.parametrize("mode,targets", [("block", 0), ("default", 2), ("default", 4)])
+@pytest.mark.parametrize("changed", [False, True])
 @pytest.mark.parametrize("n", [700, 10007])
-def test_field_of_a_step(n, first):
+def test_field_of_a_step(n, changed, mode, targets):
     if not torch.cuda.is_available():
         pytest.skip("no GPU")
     import oracle
@@ -25,10 +27,13 @@ def test_field_of_a_step(n, first):
     d = dict(W.DEVICE, mobility_model=1)
     dev = [torch.as_tensor(v).cuda() for v in (w.x, w.y, w.z)]
     run = g.gccd_init(g.Params.from_device(d))
-    g.gccd_set_precision(run, first)
+    if not changed:
+        g.gccd_set_precision(run, mode)
+        g.gccd_set_launch(run, targets, 0)
     g.gccd_load(run, *dev)
     g.gccd_run(run, 10.0, 14)
-    g.gccd_set_precision(run, "block")
+    g.gccd_set_precision(run, mode)
+    g.gccd_set_launch(run, targets, 0)
     # the step after 14 others, with the field of the list that stands before it
     before, _ = g.gccd_positions(run, n)
     E = g.gccd_field(run, n).cpu().numpy()
