@@ -16,8 +16,6 @@
 #include "gccd_sort_dev.h"
 
 #include <math.h>
-
-#include <algorithm>
 #include <type_traits>
 
 namespace gccd {
@@ -2244,12 +2242,14 @@ constexpr uint32_t kDriftAtomics = 256;
 // The step's modes: list mode (a.list_mode, Coulomb on) leaving the new keys for
 // a sort of their own, the same for a load whose sort counts places (kRankMax: no
 // runs; latency-bound, so more loads in flight), or keeping the list's order
-// (a.keep).  Carrier mode is a kernel of its own (drift_steps).
-constexpr int kStepList = 0, kStepShort = 1, kStepKept = 2;
+// (a.keep), one tile per workgroup or (kStepTurns) several in turns: the loop over
+// them holds 51 more registers and takes 0.5 us more at 1000 holes.  Carrier mode is
+// a kernel of its own (drift_steps).
+constexpr int kStepList = 0, kStepShort = 1, kStepKept = 2, kStepTurns = 3;
 
 template <int MODE>
 __device__ __forceinline__ void step_body(const StepArgs& a) {
-    constexpr bool KEEP = MODE == kStepKept;
+    constexpr bool KEEP = MODE == kStepKept || MODE == kStepTurns;
     const uint32_t step = a.step + (a.step_base ? *a.step_base : 0u);
     // travelling holes at the start of this step, of the next one, and the
     // counter of the step after next (cleared now; nobody reads it)
@@ -2439,7 +2439,8 @@ __device__ __forceinline__ void step_body(const StepArgs& a) {
         if constexpr (KEEP) {
             __shared__ double red[6][kTile / 64];
             tile_boxes(turn, threadIdx.x, ti < tne, px, py, pz, a.tile_box, a.box_stride, red);
-            if (turn + gridDim.x < turns) __syncthreads();  // red is written again
+            if constexpr (MODE == kStepKept) break;
+            __syncthreads();  // red is written again
         }
         if (runs) {  // uniform: every thread of the workgroup takes each turn
             const uint32_t m = min((uint32_t)kStepThreads, a.n_all - base);
@@ -2576,14 +2577,18 @@ __global__ __launch_bounds__(kDriftSum) void drift_counts(StepArgs a, uint32_t n
 }
 
 hipError_t launch_step(const StepArgs& a, uint32_t n_slots, hipStream_t s) {
-    static_assert(kTile == kStepThreads, "a turn of the kept step takes one source tile");
+    static_assert(kTile == kStepThreads, "a turn of a kept step takes one source tile");
     if (a.keep) {
         if (!a.list_mode || !a.sources_all || a.n_tiles == 0) return hipErrorInvalidValue;
         // The workgroups' atomics on the same two words queue up (24 ns per workgroup):
         // 6553 events of 10 holes, a tile each, take 198 us per step in as many
         // workgroups, 109 in 512 (154 in 256, 112 in 1024); 1700 events of 1000 holes
         // 880, 849 (889, 862).
-        step_update<kStepKept><<<std::min(a.n_tiles, 512u), kStepThreads, 0, s>>>(a);
+        constexpr uint32_t kMax = 512;
+        if (a.n_tiles <= kMax)
+            step_update<kStepKept><<<a.n_tiles, kStepThreads, 0, s>>>(a);
+        else
+            step_update<kStepTurns><<<kMax, kStepThreads, 0, s>>>(a);
     } else if (a.list_mode && n_slots <= kRankMax) {
         step_update<kStepShort>
             <<<(n_slots + kStepThreads - 1) / kStepThreads, kStepThreads, 0, s>>>(a);
