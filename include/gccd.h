@@ -288,8 +288,8 @@ int gccd_set_precision(gccd_ctx* c, int32_t mode);
  * Per-launch timing (gccd_set_timing) needs events around each field
  * launch, which graph replays do not provide: with timing on, GRAPH issues
  * its steps one by one.  Default: GRAPH, the fastest measured on MI355X:
- * replays save the launch gaps of the short steps of small loads (16.9
- * against 17.5 us per step at 1000 holes, 23.0 against 23.6 at 3000)
+ * replays save the launch gaps of the short steps of small loads (16.4
+ * against 16.9 us per step at 1000 holes, 22.3 against 22.9 at 3000)
  * and are level with GRID at 1e5 holes and at the 4096-cloud batch; the
  * queue costs a reset launch and an atomic per item and is never faster.
  * A later load of the same shape on the context replays the same graph.

@@ -2154,7 +2154,7 @@ __device__ __forceinline__ double unit_open(uint32_t w) {
 //     collected holes copying theirs through; the next sort restores order.
 //   kept list (a.keep): a source tile per turn of a workgroup, one thread per slot.
 //     The order stays, so no key is made or sorted: the step writes the slots' new
-//     positions and its tile's boxes.  1,000 holes, latency-bound: 7.1 us.
+//     positions and its tile's boxes.  1,000 holes, latency-bound: 6.4 us.
 //   carrier mode: drift_steps.
 // ---------------------------------------------------------------------------
 // The FP64 functions of the step (gccd_fp64.h).  Carrier mode (no
